@@ -544,8 +544,10 @@ nt_status nt_triangle_mul_backward(const nt_layout* layout, int32_t direction, i
  * dq, dk, dv: bf16 [sum N^2, H*d] with row stride ld_dqkv, overwritten;
  * dbias: fp32, head h of cell c at dbias[c * ld_dbias + h * ld_dbias_head],
  * overwritten (NULL: not computed).  fp32 arithmetic, no atomics.
- * Workspace: 8 * H * sum N^2 bytes (the softmax statistics of every query),
- * nt_pair_row_attention_backward_workspace.
+ * Workspace: at least 8 * H * sum N^2 bytes (the softmax statistics of every
+ * query); with the size that nt_pair_row_attention_backward_workspace returns
+ * (two bias images behind them) the bias is read as whole tiles instead of
+ * value by value.
  * Errors: NT_ERR_INVALID_ARG, NT_ERR_UNSUPPORTED (axis, dtype, head_dim,
  * N_i > 512).                                                                */
 nt_status nt_pair_row_attention_backward(const nt_layout* layout, int32_t axis, int32_t heads, int32_t head_dim,

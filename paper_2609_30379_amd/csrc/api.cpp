@@ -596,7 +596,7 @@ nt_status nt_pair_row_attention_backward(const nt_layout* L, int32_t axis, int32
   if (bias && (ld_bias <= 0 || ld_bias_head <= 0)) return nt::fail(NT_ERR_INVALID_ARG, "bias strides must be positive");
   if (dbias && (ld_dbias <= 0 || ld_dbias_head <= 0)) return nt::fail(NT_ERR_INVALID_ARG, "dbias strides must be positive");
   if (!(scale == scale)) return nt::fail(NT_ERR_INVALID_ARG, "scale is NaN");
-  if (nt_status st = need_workspace(nt::attention_backward_workspace_bytes(*L, H), workspace, workspace_bytes,
+  if (nt_status st = need_workspace(nt::attention_backward_min_workspace_bytes(*L, H), workspace, workspace_bytes,
                                     "nt_pair_row_attention_backward_workspace"))
     return st;
   if (nt_status st = need_device(L)) return st;
@@ -608,7 +608,8 @@ nt_status nt_pair_row_attention_backward(const nt_layout* L, int32_t axis, int32
     return nt::fail(NT_ERR_INVALID_ARG, "misaligned pointer");
   return check_hip(nt::launch_attention_backward(*L, axis, H, q, k, v, ld_qkv, bias, ld_bias, ld_bias_head,
                                                  dout, ld_dout, scale, dq, dk, dv, ld_dqkv, dbias, ld_dbias,
-                                                 ld_dbias_head, workspace, static_cast<hipStream_t>(stream)),
+                                                 ld_dbias_head, workspace, (size_t)workspace_bytes,
+                                                 static_cast<hipStream_t>(stream)),
                    "nt_pair_row_attention_backward launch");
 }
 

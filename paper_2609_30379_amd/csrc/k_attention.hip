@@ -1104,10 +1104,22 @@ hipError_t noalloc_scratch(void** ptr) {
   return hipSuccess;
 }
 
+size_t bias_image_bytes(const nt_layout& L, int H) { return (size_t)H * (size_t)L.bias_tiles_total() * 512; }
+
+hipError_t launch_bias_image(const nt_layout& L, int axis, int H, const void* bias, int64_t ld_bias,
+                             int64_t ld_bias_head, float mul, void* img, hipStream_t s) {
+  const int64_t tiles = L.bias_tiles_total();
+  if (tiles == 0) return hipSuccess;
+  BiasImgArgs b{axis, L.batch, (const bf16*)bias, ld_bias, ld_bias_head, mul, (uint2*)img, tiles,
+                L.d_bias_tiles, L.d_cu_seqlens, L.d_cu_pairs};
+  bias_image_kernel<<<dim3((unsigned)((tiles + 3) / 4), (unsigned)H), dim3(256), 0, s>>>(b);
+  return hipGetLastError();
+}
+
 size_t attention_workspace_bytes(const nt_layout& L, int axis, int H, int D, nt_dtype dtype, bool has_bias) {
   // only the d = 32 pair kernel (N <= 512) reads the bias through an image
   if (!has_bias || dtype != NT_BF16 || D != 32 || axis == 2 || L.max_len > kAttnLongLen) return 0;
-  return (size_t)H * (size_t)L.bias_tiles_total() * 512;
+  return bias_image_bytes(L, H);
 }
 
 namespace {
@@ -1196,9 +1208,8 @@ hipError_t launch_attention(const nt_layout& L, int axis, int H, int D, const vo
     const uint2* img = nullptr;
     if (bias && tiles > 0) {
       // the caller's workspace receives the bias image
-      BiasImgArgs b{axis, L.batch, (const bf16*)bias, ld_bias, ld_bias_head, 1.f / scale, (uint2*)workspace, tiles,
-                    L.d_bias_tiles, L.d_cu_seqlens, L.d_cu_pairs};
-      bias_image_kernel<<<dim3((unsigned)((tiles + 3) / 4), (unsigned)H), dim3(256), 0, s>>>(b);
+      const hipError_t e = launch_bias_image(L, axis, H, bias, ld_bias, ld_bias_head, 1.f / scale, workspace, s);
+      if (e != hipSuccess) return e;
       img = (const uint2*)workspace;
     }
     PairAttnArgs a{axis, (const bf16*)q, (const bf16*)k, (const bf16*)v, ld_qkv, (const bf16*)bias, ld_bias,

@@ -7,16 +7,24 @@
 //   dQ_j = scale sum_k dS_jk K_k,  dK_k = scale sum_j dS_jk Q_j,
 //   dV_k = sum_j P_jk dO_j,        dB_jk = sum_r dS_jk   (the bias is shared by all rows).
 //
-// attn_bwd_rows_kernel: one workgroup per (pair row, head).  The row's q, k,
-// v and dO (N x 32 each) are staged in LDS; every thread first takes the
-// softmax statistics of its queries, then the query gradients (a thread per
-// query, keys broadcast from LDS), then the key and value gradients (a thread
-// per key, queries broadcast), so no sum crosses threads.  lse and D go to
-// the workspace for the bias gradient.
-// attn_bwd_bias_kernel: one workgroup per (sample, 16-query block, head); a
-// thread per key walks all pair rows and sums dS for its 16 queries, then
-// writes its column of the bias gradient once (no atomics).
-// Arithmetic is fp32 on the vector units.
+// Every product runs on the matrix cores with fp32 accumulation.  Q K^T and
+// dO V^T have bf16 operands as they are.  P and dS stay fp32: as operands of
+// dQ, dK and dV each is split into three bf16 parts (the upper, middle and
+// lower 8 bits of its significand, exact), one product per part, so no bit
+// of them is dropped.  Softmax arithmetic is fp32 on the vector units.
+//
+// attn_bwd_rows_kernel: one workgroup per (pair row, head); the row's q, k, v
+// and dO are copied into LDS.  Phase A: a wave per 16-query tile, first the
+// softmax statistics over all keys, then dQ; phase B: a wave per 16-key tile,
+// dK and dV.  lse and D go to the workspace for the bias gradient.
+// attn_bwd_bias_kernel: a wave per (sample, head, 16 queries, 64 keys) walks
+// all pair rows and keeps the 16 x 64 sums of dS in registers (no atomics).
+//
+// The vector units bound the rows kernel: per score it spends about 16 vector
+// instructions on the 3-way splits and one exponential in each of three
+// passes (statistics, dQ, dK/dV), against 30 products per 512 scores.  At
+// B=8, N 66..317, 4 heads: 568 us; one thread per query or key with fp32 FMAs
+// took 12.2 ms (and the bias gradient 5.8 ms, now 761 us).
 #include "nt_device.h"
 #include "nt_internal.h"
 
@@ -24,6 +32,7 @@ namespace nt {
 namespace {
 
 constexpr int kD = 32;                 // head_dim
+constexpr float kLog2e = 1.4426950408889634f;
 
 struct AttnBwdArgs {
   int axis, H;
@@ -42,244 +51,421 @@ struct AttnBwdArgs {
   int64_t ld_dqkv;
   float* dbias;
   int64_t ld_dbias, ld_dbias_head;
-  float* lse;                          // workspace: [sum N^2, H] per query element
+  float* lse;                          // workspace: [H][sum N^2], element cu + r n + j of row r, query j
   float* dsum;                         // workspace: D, same layout
+  int64_t cells;                       // sum N^2
   const int32_t* work;                 // (sample, row) pairs; -1 = idle
   const int32_t* cu_seqlens;
   const int32_t* cu_pairs;
-  const int32_t* cu_qblk;              // prefix of ceil(N_i / 16)
-  int batch;
+  // bias images (IMG instances): tile (a, b) of head h at
+  // (h * img_tiles + bias_tiles[i] + a * kti + b) * 64 + lane, kti = round_up(n, 64) / 16
+  const uint2* img_q;                  // lane l16 + 16 g: bias(16 a + l16, 16 b + 4 g + e)
+  const uint2* img_k;                  // lane l16 + 16 g: bias(16 b + 4 g + e, 16 a + l16)
+  int64_t img_tiles;
+  const int32_t* bias_tiles;
 };
 
-__device__ __forceinline__ void load32(const bf16* p, float* out) {
+__device__ __forceinline__ float exp_native(float x) { return __builtin_amdgcn_exp2f(x * kLog2e); }
+
+__device__ __forceinline__ uint32_t lds_addr(const bf16* ptr) {
+  return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) bf16*)ptr;
+}
+__device__ __forceinline__ bf16x8 pack_u2(uint2 lo, uint2 hi) {
+  const uint32_t w[4] = {lo.x, lo.y, hi.x, hi.y};
+  return __builtin_bit_cast(bf16x8, w);
+}
+
+// LDS image of 16 rows x 32 dims (1 KB): the 16-byte piece (row, dims 8 d ..
+// 8 d + 7) sits in slot 16 d + (row ^ 8 (d & 1)).  Read as a matrix-core
+// fragment (lane l16 + 16 g: row l16, dims 8 g ..) it is a permutation of the
+// whole 1 KB; the XOR puts the two pieces of a transposed read on different
+// banks.
+__device__ __forceinline__ int frag_offset(int l16, int g) { return (g * 16 + (l16 ^ ((g & 1) << 3))) * 8; }
+__device__ __forceinline__ bf16x8 frag(const bf16* T, int tile, int fo) {
+  return *reinterpret_cast<const bf16x8*>(T + tile * 512 + fo);
+}
+// Transposed fragments: ds_read_b64_tr_b16 hands lane 4q+m of each 16-lane
+// group element m of the 8-byte pieces addressed by lanes q, q+4, q+8, q+12;
+// pointing lane i at row 4 g + i/4, dims 4 (i%4) gives lane l16 rows 4 g ..
+// 4 g + 3 of dim l16.  Dims 16..31 are 512 bytes further on, the next tile
+// 1024 bytes.
+__device__ __forceinline__ uint32_t tr_offset(int l16, int g) {
+  const int row = 4 * g + (l16 >> 2), d = (l16 & 3) >> 1;
+  return (uint32_t)((d * 16 + (row ^ (d << 3))) * 16 + (l16 & 1) * 8);
+}
+// tiles t, t + 1 of T: f[0] dims 0-15, f[1] dims 16-31 (k slots: rows 4 g .. of tile t, then of t + 1)
+__device__ __forceinline__ void tr_frags(const bf16* T, int tile, uint32_t to, bf16x8 (&f)[2]) {
+  const uint32_t a = lds_addr(T + tile * 512) + to;
+  uint2 r[4];
+  asm volatile(
+      "ds_read_b64_tr_b16 %0, %4\n"
+      "ds_read_b64_tr_b16 %1, %4 offset:1024\n"
+      "ds_read_b64_tr_b16 %2, %4 offset:512\n"
+      "ds_read_b64_tr_b16 %3, %4 offset:1536\n"
+      "s_waitcnt lgkmcnt(0)"
+      : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3])
+      : "v"(a)
+      : "memory");
+  f[0] = pack_u2(r[0], r[1]);
+  f[1] = pack_u2(r[2], r[3]);
+}
+
+// x = part[0] + part[1] + part[2] for eight fp32 values (finite): the parts
+// are the upper, middle and lower 8 bits of the significand.
+__device__ __forceinline__ void split3(const float (&x)[8], bf16x8 (&part)[3]) {
+  uint32_t w[3][4];
 #pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    const uint4 t = *reinterpret_cast<const uint4*>(p + c * 8);
-    const uint32_t w[4] = {t.x, t.y, t.z, t.w};
+  for (int e = 0; e < 4; ++e) {
+    uint32_t h[2], m[2], l[2];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      out[c * 8 + 2 * j] = __uint_as_float(w[j] << 16);
-      out[c * 8 + 2 * j + 1] = __uint_as_float(w[j] & 0xffff0000u);
+    for (int u = 0; u < 2; ++u) {
+      h[u] = __float_as_uint(x[2 * e + u]);
+      const float r = x[2 * e + u] - __uint_as_float(h[u] & 0xffff0000u);
+      m[u] = __float_as_uint(r);
+      l[u] = __float_as_uint(r - __uint_as_float(m[u] & 0xffff0000u));
     }
+    w[0][e] = __builtin_amdgcn_perm(h[1], h[0], 0x07060302u);
+    w[1][e] = __builtin_amdgcn_perm(m[1], m[0], 0x07060302u);
+    w[2][e] = __builtin_amdgcn_perm(l[1], l[0], 0x07060302u);
   }
+#pragma unroll
+  for (int t = 0; t < 3; ++t) part[t] = __builtin_bit_cast(bf16x8, w[t]);
 }
 
-__device__ __forceinline__ float dot32(const float* a, const bf16* b) {
-  float t[kD];
-  load32(b, t);
-  float s = 0.f;
-#pragma unroll
-  for (int d = 0; d < kD; ++d) s = fmaf(a[d], t[d], s);
-  return s;
-}
-
-__device__ __forceinline__ void store32(bf16* p, const float* x, float mul) {
-#pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    bf16x8 t;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) t[e] = (bf16)(x[c * 8 + e] * mul);
-    *reinterpret_cast<bf16x8*>(p + c * 8) = t;
-  }
-}
-
-// head-h bias of (query j, key k) of sample i (axis 1: of cell (k, j))
+// head-h bias of (query j, key k) of a sample (axis 1: of cell (k, j))
 __device__ __forceinline__ float bias_at(const AttnBwdArgs& p, int64_t cu, int n, int j, int k, int h) {
   if (!p.bias) return 0.f;
   const int64_t cell = cu + (p.axis == 0 ? (int64_t)j * n + k : (int64_t)k * n + j);
   return (float)p.bias[cell * p.ld_bias + (int64_t)h * p.ld_bias_head];
 }
 
-template <int NMAX>
-__global__ void __launch_bounds__(256) attn_bwd_rows_kernel(AttnBwdArgs p) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  bf16* Qs = reinterpret_cast<bf16*>(smem);
-  bf16* Ks = Qs + NMAX * kD;
-  bf16* Vs = Ks + NMAX * kD;
-  bf16* Gs = Vs + NMAX * kD;
-  float* lse_s = reinterpret_cast<float*>(Gs + NMAX * kD);
-  float* d_s = lse_s + NMAX;
-  const int i = p.work[2 * blockIdx.x], r = p.work[2 * blockIdx.x + 1];
+// sum over the four lanes l16 + 16 g (g = 0..3)
+__device__ __forceinline__ float max_over_kgroups(float v) {
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+
+// 16 rows x 32 dims of a gradient: lane (l16, g) holds dims 4 g .. 4 g + 3
+// (acc[0]) and 16 + 4 g .. (acc[1]) of row l16.  Lane rows g, g ^ 1 trade
+// halves so that every lane stores 16 bytes.
+__device__ __forceinline__ void store_rows(bf16* row, bool valid, int g, const f32x4 (&acc)[2], float mul) {
+  uint32_t w[2][2];
+#pragma unroll
+  for (int dt = 0; dt < 2; ++dt) {
+    bf16x4 o;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o[e] = (bf16)(acc[dt][e] * mul);
+    const uint2 u = __builtin_bit_cast(uint2, o);
+    w[dt][0] = u.x;
+    w[dt][1] = u.y;
+  }
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+    const auto sw = __builtin_amdgcn_permlane16_swap(w[0][e], w[1][e], false, false);
+    w[0][e] = sw[0];
+    w[1][e] = sw[1];
+  }
+  if (valid) {
+    const int d0 = (g & 1) ? 16 + 4 * (g - 1) : 4 * g;
+    *reinterpret_cast<uint4*>(row + d0) = make_uint4(w[0][0], w[0][1], w[1][0], w[1][1]);
+  }
+}
+
+template <int NW, bool IMG>
+__global__ void __launch_bounds__(64 * NW, 4) attn_bwd_rows_kernel(AttnBwdArgs p, int nt_max) {
+  extern __shared__ __attribute__((aligned(16))) bf16 lds[];
+  // workgroup 8 (H k + h) + x runs on XCD x: the heads of a pair row, which
+  // share cache lines, run on one XCD one after the other
+  const int x = blockIdx.x % kXcds, t0 = blockIdx.x / kXcds;
+  const int h = t0 % p.H, pos = (t0 / p.H) * kXcds + x;
+  const int i = p.work[2 * pos], r = p.work[2 * pos + 1];
   if (i < 0) return;
-  const int h = blockIdx.y;
   const int n = p.cu_seqlens[i + 1] - p.cu_seqlens[i];
   const int64_t cu = p.cu_pairs[i];
+  const int nt = (n + 15) >> 4, nt2 = (nt + 1) & ~1;      // 16-row tiles, padded to whole 32-row steps
+  bf16* Qs = lds;
+  bf16* Ks = Qs + nt_max * 512;
+  bf16* Vs = Ks + nt_max * 512;
+  bf16* Gs = Vs + nt_max * 512;
+  float* lse_s = reinterpret_cast<float*>(Gs + nt_max * 512);
+  float* d_s = lse_s + nt_max * 16;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int l16 = lane & 15, g = lane >> 4;
   // element t of this row: packed row base + t * step
   const int64_t base = p.axis == 0 ? cu + (int64_t)r * n : cu + r;
   const int64_t step = p.axis == 0 ? 1 : n;
-  for (int e = threadIdx.x; e < n * 4; e += 256) {
-    const int t = e >> 2, c = (e & 3) * 8;
-    const int64_t row = base + (int64_t)t * step;
-    *reinterpret_cast<uint4*>(&Qs[t * kD + c]) = *reinterpret_cast<const uint4*>(p.q + row * p.ld_qkv + h * kD + c);
-    *reinterpret_cast<uint4*>(&Ks[t * kD + c]) = *reinterpret_cast<const uint4*>(p.k + row * p.ld_qkv + h * kD + c);
-    *reinterpret_cast<uint4*>(&Vs[t * kD + c]) = *reinterpret_cast<const uint4*>(p.v + row * p.ld_qkv + h * kD + c);
-    *reinterpret_cast<uint4*>(&Gs[t * kD + c]) =
-        *reinterpret_cast<const uint4*>(p.dout + row * p.ld_dout + h * kD + c);
+
+  // ---- copy the row's four operands; tiles up to nt2, rows past N repeat row N - 1
+  {
+    const int hD = h * kD, row16 = l16 ^ ((g & 1) << 3);
+    for (int t = wave; t < nt2 * 4; t += NW) {
+      const int tile = t >> 2, which = t & 3;
+      const int64_t row = base + (int64_t)min(tile * 16 + row16, n - 1) * step;
+      const bf16* src = (which == 0 ? p.q : which == 1 ? p.k : which == 2 ? p.v : p.dout) +
+                        row * (which == 3 ? p.ld_dout : p.ld_qkv) + hD + g * 8;
+      bf16* dst = lds + (which * nt_max + tile) * 512;
+      __builtin_amdgcn_global_load_lds((const void*)src, (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
+    }
   }
+  __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
-  // softmax statistics of every query, and D = sum_k P_jk (dO_j . V_k),
-  // accumulated with the running maximum (fp32, from the recomputed softmax)
-  for (int j = threadIdx.x; j < n; j += 256) {
-    float qv[kD], gv[kD];
-    load32(&Qs[j * kD], qv);
-    load32(&Gs[j * kD], gv);
+
+  const int fo = frag_offset(l16, g);
+  const uint32_t to = tr_offset(l16, g);
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+  const int kti = ((n + 63) >> 6) * 4;
+  const int64_t img0 = IMG ? ((int64_t)h * p.img_tiles + p.bias_tiles[i]) * 64 + lane : 0;
+
+  // bias of the two tiles (a, b), (a, b + 1): values of lane (l16, g), -inf
+  // outside the sample.  BYQ: query 16 a + l16, keys 16 b + 4 g + e; else
+  // key 16 a + l16, queries 16 b + 4 g + e.
+  auto bias8 = [&](bool byq, int a, int b, float (&out)[8]) {
+    if constexpr (IMG) {
+      const uint2* img = (byq ? p.img_q : p.img_k) + img0 + ((int64_t)a * kti + b) * 64;
+      const uint2 u[2] = {img[0], img[64]};
+#pragma unroll
+      for (int w = 0; w < 2; ++w) {
+        out[4 * w] = __uint_as_float(u[w].x << 16);
+        out[4 * w + 1] = __uint_as_float(u[w].x & 0xffff0000u);
+        out[4 * w + 2] = __uint_as_float(u[w].y << 16);
+        out[4 * w + 3] = __uint_as_float(u[w].y & 0xffff0000u);
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int ai = 16 * a + l16, bi = 16 * (b + (e >> 2)) + 4 * g + (e & 3);
+        out[e] = -INFINITY;
+        if (ai < n && bi < n) out[e] = byq ? bias_at(p, cu, n, ai, bi, h) : bias_at(p, cu, n, bi, ai, h);
+      }
+    }
+  };
+
+  // ---- phase A: statistics and dQ, a wave per 16 queries
+  for (int qt = wave; qt < nt; qt += NW) {
+    const bf16x8 qf = frag(Qs, qt, fo), gf = frag(Gs, qt, fo);
+    const int j = qt * 16 + l16;
+    // every lane runs its own maximum over its keys (4 g + e of each tile)
     float m = -INFINITY, l = 0.f, acc = 0.f;
-    for (int k = 0; k < n; ++k) {
-      const float sv = p.scale * dot32(qv, &Ks[k * kD]) + bias_at(p, cu, n, j, k, h);
-      const float dp = dot32(gv, &Vs[k * kD]);
-      if (sv > m) {
-        const float c = __expf(m - sv);
-        l = l * c + 1.f;
-        acc = acc * c + dp;
-        m = sv;
-      } else {
-        const float e = __expf(sv - m);
-        l += e;
-        acc = fmaf(e, dp, acc);
+    for (int kt = 0; kt < nt2; kt += 2) {
+      const f32x4 s0 = mfma16(frag(Ks, kt, fo), qf, zero), s1 = mfma16(frag(Ks, kt + 1, fo), qf, zero);
+      const f32x4 d0 = mfma16(frag(Vs, kt, fo), gf, zero), d1 = mfma16(frag(Vs, kt + 1, fo), gf, zero);
+      float b[8];
+      bias8(true, qt, kt, b);
+      float sv[8], mx = m;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        sv[e] = fmaf(e < 4 ? s0[e & 3] : s1[e & 3], p.scale, b[e]);
+        mx = fmaxf(mx, sv[e]);
+      }
+      const float ms = mx == -INFINITY ? 0.f : mx;       // nothing but masked keys so far: every weight 0
+      const float c = exp_native(m - ms);
+      l *= c;
+      acc *= c;
+      m = mx;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float w = exp_native(sv[e] - ms);
+        l += w;
+        acc = fmaf(w, e < 4 ? d0[e & 3] : d1[e & 3], acc);
       }
     }
-    const int64_t row = base + (int64_t)j * step;
-    const float dsum = acc / l;
-    const float ls = m + __logf(l);
-    lse_s[j] = ls;
-    d_s[j] = dsum;
-    p.lse[row * p.H + h] = ls;
-    p.dsum[row * p.H + h] = dsum;
+    const float mm = max_over_kgroups(m);
+    const float c = m == -INFINITY ? 0.f : exp_native(m - mm);
+    l = sum_over_kgroups(l * c);
+    acc = sum_over_kgroups(acc * c);
+    const float ls = mm + __logf(l), ds = acc / l;
+    if (g == 0) {
+      const bool ok = j < n;
+      lse_s[j] = ok ? ls : 0.f;                          // queries past N weigh nothing in phase B
+      d_s[j] = ok ? ds : 0.f;
+      if (ok) {
+        const int64_t at = (int64_t)h * p.cells + cu + (int64_t)r * n + j;
+        p.lse[at] = ls;
+        p.dsum[at] = ds;
+      }
+    }
+    // dQ^T += K^T dS^T
+    f32x4 dq[2] = {zero, zero};
+    for (int kt = 0; kt < nt2; kt += 2) {
+      const f32x4 s0 = mfma16(frag(Ks, kt, fo), qf, zero), s1 = mfma16(frag(Ks, kt + 1, fo), qf, zero);
+      const f32x4 d0 = mfma16(frag(Vs, kt, fo), gf, zero), d1 = mfma16(frag(Vs, kt + 1, fo), gf, zero);
+      float b[8], dsv[8];
+      bias8(true, qt, kt, b);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float pr = exp_native(fmaf(e < 4 ? s0[e & 3] : s1[e & 3], p.scale, b[e]) - ls);
+        dsv[e] = pr * ((e < 4 ? d0[e & 3] : d1[e & 3]) - ds);
+      }
+      bf16x8 part[3], kf[2];
+      split3(dsv, part);
+      tr_frags(Ks, kt, to, kf);
+#pragma unroll
+      for (int t = 0; t < 3; ++t) {
+        dq[0] = mfma16(kf[0], part[t], dq[0]);
+        dq[1] = mfma16(kf[1], part[t], dq[1]);
+      }
+    }
+    store_rows(p.dq + (base + (int64_t)j * step) * p.ld_dqkv + h * kD, j < n, g, dq, p.scale);
+  }
+  if (nt2 > nt && threadIdx.x < 16) {                     // the padded tile's statistics
+    lse_s[nt * 16 + threadIdx.x] = 0.f;
+    d_s[nt * 16 + threadIdx.x] = 0.f;
   }
   __syncthreads();
-  // dQ_j = scale sum_k P_jk (dO_j . V_k - D_j) K_k
-  for (int j = threadIdx.x; j < n; j += 256) {
-    float qv[kD], gv[kD], acc[kD];
-    load32(&Qs[j * kD], qv);
-    load32(&Gs[j * kD], gv);
+
+  // ---- phase B: dK and dV, a wave per 16 keys
+  for (int kt = wave; kt < nt; kt += NW) {
+    const bf16x8 kf = frag(Ks, kt, fo), vf = frag(Vs, kt, fo);
+    f32x4 dk[2] = {zero, zero}, dv[2] = {zero, zero};
+    for (int qt = 0; qt < nt2; qt += 2) {
+      const f32x4 s0 = mfma16(frag(Qs, qt, fo), kf, zero), s1 = mfma16(frag(Qs, qt + 1, fo), kf, zero);
+      const f32x4 d0 = mfma16(frag(Gs, qt, fo), vf, zero), d1 = mfma16(frag(Gs, qt + 1, fo), vf, zero);
+      float b[8], pr[8], dsv[8];
+      bias8(false, kt, qt, b);
+      const float4 la = *reinterpret_cast<const float4*>(lse_s + qt * 16 + 4 * g);
+      const float4 lb = *reinterpret_cast<const float4*>(lse_s + qt * 16 + 16 + 4 * g);
+      const float4 da = *reinterpret_cast<const float4*>(d_s + qt * 16 + 4 * g);
+      const float4 db = *reinterpret_cast<const float4*>(d_s + qt * 16 + 16 + 4 * g);
+      const float ls[8] = {la.x, la.y, la.z, la.w, lb.x, lb.y, lb.z, lb.w};
+      const float dd[8] = {da.x, da.y, da.z, da.w, db.x, db.y, db.z, db.w};
 #pragma unroll
-    for (int d = 0; d < kD; ++d) acc[d] = 0.f;
-    const float ls = lse_s[j], dsum = d_s[j];
-    for (int k = 0; k < n; ++k) {
-      float kv[kD];
-      load32(&Ks[k * kD], kv);
-      float sv = 0.f;
-#pragma unroll
-      for (int d = 0; d < kD; ++d) sv = fmaf(qv[d], kv[d], sv);
-      const float pr = __expf(p.scale * sv + bias_at(p, cu, n, j, k, h) - ls);
-      const float ds = pr * (dot32(gv, &Vs[k * kD]) - dsum);
-#pragma unroll
-      for (int d = 0; d < kD; ++d) acc[d] = fmaf(ds, kv[d], acc[d]);
-    }
-    store32(p.dq + (base + (int64_t)j * step) * p.ld_dqkv + h * kD, acc, p.scale);
-  }
-  // dK_k = scale sum_j dS_jk Q_j,  dV_k = sum_j P_jk dO_j
-  for (int k = threadIdx.x; k < n; k += 256) {
-    float kv[kD], vv[kD], ak[kD], av[kD];
-    load32(&Ks[k * kD], kv);
-    load32(&Vs[k * kD], vv);
-#pragma unroll
-    for (int d = 0; d < kD; ++d) ak[d] = av[d] = 0.f;
-    for (int j = 0; j < n; ++j) {
-      float qv[kD], gv[kD];
-      load32(&Qs[j * kD], qv);
-      load32(&Gs[j * kD], gv);
-      float sv = 0.f, dp = 0.f;
-#pragma unroll
-      for (int d = 0; d < kD; ++d) {
-        sv = fmaf(qv[d], kv[d], sv);
-        dp = fmaf(gv[d], vv[d], dp);
+      for (int e = 0; e < 8; ++e) {
+        pr[e] = exp_native(fmaf(e < 4 ? s0[e & 3] : s1[e & 3], p.scale, b[e]) - ls[e]);
+        dsv[e] = pr[e] * ((e < 4 ? d0[e & 3] : d1[e & 3]) - dd[e]);
       }
-      const float pr = __expf(p.scale * sv + bias_at(p, cu, n, j, k, h) - lse_s[j]);
-      const float ds = pr * (dp - d_s[j]);
+      bf16x8 part[3], tf[2];
+      split3(dsv, part);
+      tr_frags(Qs, qt, to, tf);
 #pragma unroll
-      for (int d = 0; d < kD; ++d) {
-        ak[d] = fmaf(ds, qv[d], ak[d]);
-        av[d] = fmaf(pr, gv[d], av[d]);
+      for (int t = 0; t < 3; ++t) {
+        dk[0] = mfma16(tf[0], part[t], dk[0]);
+        dk[1] = mfma16(tf[1], part[t], dk[1]);
+      }
+      split3(pr, part);
+      tr_frags(Gs, qt, to, tf);
+#pragma unroll
+      for (int t = 0; t < 3; ++t) {
+        dv[0] = mfma16(tf[0], part[t], dv[0]);
+        dv[1] = mfma16(tf[1], part[t], dv[1]);
       }
     }
-    const int64_t row = base + (int64_t)k * step;
-    store32(p.dk + row * p.ld_dqkv + h * kD, ak, p.scale);
-    store32(p.dv + row * p.ld_dqkv + h * kD, av, 1.f);
+    const int key = kt * 16 + l16;
+    const int64_t at = (base + (int64_t)key * step) * p.ld_dqkv + h * kD;
+    store_rows(p.dk + at, key < n, g, dk, p.scale);
+    store_rows(p.dv + at, key < n, g, dv, 1.f);
   }
 }
 
-// Bias gradient: workgroup (sample, 16-query block, head); thread t owns keys
-// t and t + 256 (N <= 512).
-__global__ void __launch_bounds__(256) attn_bwd_bias_kernel(AttnBwdArgs p) {
-  __shared__ __attribute__((aligned(16))) bf16 qs[16 * kD], gs[16 * kD];
-  __shared__ float ls[16], dsm[16];
-  const int blk = blockIdx.x, h = blockIdx.y;
-  int lo = 0, hi = p.batch - 1;                   // sample: largest i with cu_qblk[i] <= blk
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (p.cu_qblk[mid] <= blk) lo = mid; else hi = mid - 1;
-  }
-  const int i = lo;
+// Bias gradient: wave = (sample, head, 16 queries, 64 keys).  The items of a
+// sample are cut into eight equal stretches, one per XCD, ordered by head, so
+// the q, k, v and dO rows that the waves of an XCD walk together come from
+// its own L2.  kRows pair rows are loaded at once (their fragments straight
+// from global memory), so a row's latency is paid once per kRows rows.
+constexpr int kBiasKeys = 64, kBiasRows = 2;
+
+__global__ void __launch_bounds__(256) attn_bwd_bias_kernel(AttnBwdArgs p, int nb) {
+  const int i = blockIdx.x / nb, blk = blockIdx.x % nb;   // nb workgroups per sample, a multiple of 8
   const int n = p.cu_seqlens[i + 1] - p.cu_seqlens[i];
-  const int j0 = (blk - p.cu_qblk[i]) * 16;
-  const int nj = min(16, n - j0);
+  const int nq = (n + 15) >> 4, nk = (n + kBiasKeys - 1) / kBiasKeys;
+  const int items = p.H * nq * nk;                        // (head, 16-query tile, 64-key block)
+  const int per = (items + kXcds - 1) / kXcds;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int slot = (blk / kXcds) * 4 + wave;
+  const int item = (blk % kXcds) * per + slot;
+  if (slot >= per || item >= items) return;
+  const int h = item / (nq * nk), qt = (item / nk) % nq, kb = item % nk;
+  const int lane = threadIdx.x & 63, l16 = lane & 15, g = lane >> 4;
   const int64_t cu = p.cu_pairs[i];
-  const int64_t step = p.axis == 0 ? 1 : n;
-  float acc[2][16];
+  const int64_t step = p.axis == 0 ? 1 : n, rstep = p.axis == 0 ? n : 1;
+  const int j = qt * 16 + l16, k0 = kb * kBiasKeys;
+  constexpr int KT = kBiasKeys / 16;
+  // this lane's rows, past N clamped to the last one (their sums are not stored)
+  const int64_t jrow = cu + (int64_t)min(j, n - 1) * step;
+  const bf16* qp = p.q + jrow * p.ld_qkv + h * kD + g * 8;
+  const bf16* gp = p.dout + jrow * p.ld_dout + h * kD + g * 8;
+  int64_t koff[KT];
 #pragma unroll
-  for (int u = 0; u < 2; ++u)
+  for (int t = 0; t < KT; ++t)
+    koff[t] = (cu + (int64_t)min(k0 + 16 * t + l16, n - 1) * step) * p.ld_qkv + h * kD + g * 8;
+  const float* lp = p.lse + (int64_t)h * p.cells + cu + min(j, n - 1);
+  const float* dp = p.dsum + (int64_t)h * p.cells + cu + min(j, n - 1);
+  float b[KT][4];
 #pragma unroll
-    for (int jj = 0; jj < 16; ++jj) acc[u][jj] = 0.f;
-  for (int r = 0; r < n; ++r) {
-    const int64_t base = p.axis == 0 ? cu + (int64_t)r * n : cu + r;
-    __syncthreads();                              // the previous row's staging is consumed
-    if (threadIdx.x < nj * 4) {
-      const int jj = threadIdx.x >> 2, c = (threadIdx.x & 3) * 8;
-      const int64_t row = base + (int64_t)(j0 + jj) * step;
-      *reinterpret_cast<uint4*>(&qs[jj * kD + c]) = *reinterpret_cast<const uint4*>(p.q + row * p.ld_qkv + h * kD + c);
-      *reinterpret_cast<uint4*>(&gs[jj * kD + c]) =
-          *reinterpret_cast<const uint4*>(p.dout + row * p.ld_dout + h * kD + c);
+  for (int t = 0; t < KT; ++t)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int k = k0 + 16 * t + 4 * g + e;
+      b[t][e] = j < n && k < n ? bias_at(p, cu, n, j, k, h) : 0.f;
     }
-    if (threadIdx.x < nj) {
-      const int64_t row = base + (int64_t)(j0 + threadIdx.x) * step;
-      ls[threadIdx.x] = p.lse[row * p.H + h];
-      dsm[threadIdx.x] = p.dsum[row * p.H + h];
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+  f32x4 acc[KT];
+#pragma unroll
+  for (int t = 0; t < KT; ++t) acc[t] = zero;
+  for (int r0 = 0; r0 < n; r0 += kBiasRows) {
+    bf16x8 qf[kBiasRows], gf[kBiasRows], kf[kBiasRows][KT], vf[kBiasRows][KT];
+    float ls[kBiasRows], ds[kBiasRows];
+#pragma unroll
+    for (int u = 0; u < kBiasRows; ++u) {
+      const int64_t r = min(r0 + u, n - 1);
+      const int64_t ro = r * rstep * p.ld_qkv;
+      qf[u] = *reinterpret_cast<const bf16x8*>(qp + ro);
+      gf[u] = *reinterpret_cast<const bf16x8*>(gp + r * rstep * p.ld_dout);
+#pragma unroll
+      for (int t = 0; t < KT; ++t) {
+        kf[u][t] = *reinterpret_cast<const bf16x8*>(p.k + koff[t] + ro);
+        vf[u][t] = *reinterpret_cast<const bf16x8*>(p.v + koff[t] + ro);
+      }
+      ls[u] = lp[r * n];
+      ds[u] = dp[r * n];
     }
-    __syncthreads();
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int k = threadIdx.x + 256 * u;
-      if (k >= n) continue;
-      const int64_t krow = base + (int64_t)k * step;
-      float kv[kD], vv[kD];
-      load32(p.k + krow * p.ld_qkv + h * kD, kv);
-      load32(p.v + krow * p.ld_qkv + h * kD, vv);
+    for (int u = 0; u < kBiasRows; ++u) {
+      if (r0 + u >= n) break;
 #pragma unroll
-      for (int jj = 0; jj < 16; ++jj) {
-        if (jj >= nj) break;
-        float qv[kD], gv[kD];
-        load32(&qs[jj * kD], qv);
-        load32(&gs[jj * kD], gv);
-        float sv = 0.f, dp = 0.f;
+      for (int t = 0; t < KT; ++t) {
+        const f32x4 s = mfma16(kf[u][t], qf[u], zero), d = mfma16(vf[u][t], gf[u], zero);
 #pragma unroll
-        for (int d = 0; d < kD; ++d) {
-          sv = fmaf(qv[d], kv[d], sv);
-          dp = fmaf(gv[d], vv[d], dp);
-        }
-        const float pr = __expf(p.scale * sv + bias_at(p, cu, n, j0 + jj, k, h) - ls[jj]);
-        acc[u][jj] += pr * (dp - dsm[jj]);
+        for (int e = 0; e < 4; ++e)
+          acc[t][e] = fmaf(exp_native(fmaf(s[e], p.scale, b[t][e]) - ls[u]), d[e] - ds[u], acc[t][e]);
       }
     }
   }
+  if (j >= n) return;
 #pragma unroll
-  for (int u = 0; u < 2; ++u) {
-    const int k = threadIdx.x + 256 * u;
-    if (k >= n) continue;
+  for (int t = 0; t < KT; ++t)
 #pragma unroll
-    for (int jj = 0; jj < 16; ++jj) {
-      if (jj >= nj) break;
-      const int j = j0 + jj;
+    for (int e = 0; e < 4; ++e) {
+      const int k = k0 + 16 * t + 4 * g + e;
+      if (k >= n) continue;
       const int64_t cell = cu + (p.axis == 0 ? (int64_t)j * n + k : (int64_t)k * n + j);
-      p.dbias[cell * p.ld_dbias + (int64_t)h * p.ld_dbias_head] = acc[u][jj];
+      p.dbias[cell * p.ld_dbias + (int64_t)h * p.ld_dbias_head] = acc[t][e];
     }
-  }
 }
+
+template <int NW>
+hipError_t launch_rows(const AttnBwdArgs& a, int nt_max, unsigned grid, size_t smem, hipStream_t s) {
+  const void* fn = a.img_q ? (const void*)attn_bwd_rows_kernel<NW, true> : (const void*)attn_bwd_rows_kernel<NW, false>;
+  const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+  if (e != hipSuccess) return e;
+  if (a.img_q) attn_bwd_rows_kernel<NW, true><<<dim3(grid), dim3(64 * NW), smem, s>>>(a, nt_max);
+  else attn_bwd_rows_kernel<NW, false><<<dim3(grid), dim3(64 * NW), smem, s>>>(a, nt_max);
+  return hipGetLastError();
+}
+
+// bytes of the softmax statistics, rounded up so that the bias images behind
+// them are aligned
+size_t stats_bytes(const nt_layout& L, int H) { return 2 * (size_t)L.sum_n2 * (size_t)H * sizeof(float); }
+size_t images_offset(const nt_layout& L, int H) { return (stats_bytes(L, H) + 255) / 256 * 256; }
 
 }  // namespace
 
+size_t attention_backward_min_workspace_bytes(const nt_layout& L, int H) { return stats_bytes(L, H); }
+
 size_t attention_backward_workspace_bytes(const nt_layout& L, int H) {
-  return 2 * (size_t)L.sum_n2 * (size_t)H * sizeof(float);
+  if (L.sum_n2 == 0) return 0;
+  return images_offset(L, H) + 2 * bias_image_bytes(L, H);
 }
 
 hipError_t launch_attention_backward(const nt_layout& L, int axis, int H, const void* q, const void* k,
@@ -287,28 +473,38 @@ hipError_t launch_attention_backward(const nt_layout& L, int axis, int H, const 
                                      int64_t ld_bias_head, const void* dout,
                                      int64_t ld_dout, float scale, void* dq, void* dk, void* dv, int64_t ld_dqkv,
                                      float* dbias, int64_t ld_dbias, int64_t ld_dbias_head, void* workspace,
-                                     hipStream_t s) {
+                                     size_t workspace_bytes, hipStream_t s) {
   if (L.attn_items() == 0) return hipSuccess;
   float* lse = static_cast<float*>(workspace);
   AttnBwdArgs a{axis, H, (const bf16*)q, (const bf16*)k, (const bf16*)v, ld_qkv, (const bf16*)bias, ld_bias,
                 ld_bias_head, (const bf16*)dout, ld_dout, scale, (bf16*)dq, (bf16*)dk,
-                (bf16*)dv, ld_dqkv, dbias, ld_dbias, ld_dbias_head, lse, lse + L.sum_n2 * H, L.d_attn_work,
-                L.d_cu_seqlens, L.d_cu_pairs, L.d_cu_qblk, L.batch};
-  const dim3 grid((unsigned)L.attn_items(), (unsigned)H);
-  if (L.max_len <= 256) {
-    const size_t smem = (size_t)4 * 256 * kD * sizeof(bf16) + 2 * 256 * sizeof(float);
-    hipFuncSetAttribute((const void*)attn_bwd_rows_kernel<256>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-    attn_bwd_rows_kernel<256><<<grid, dim3(256), smem, s>>>(a);
-  } else {
-    const size_t smem = (size_t)4 * 512 * kD * sizeof(bf16) + 2 * 512 * sizeof(float);
-    hipFuncSetAttribute((const void*)attn_bwd_rows_kernel<512>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-    attn_bwd_rows_kernel<512><<<grid, dim3(256), smem, s>>>(a);
+                (bf16*)dv, ld_dqkv, dbias, ld_dbias, ld_dbias_head, lse, lse + L.sum_n2 * H, L.sum_n2, L.d_attn_work,
+                L.d_cu_seqlens, L.d_cu_pairs, nullptr, nullptr, L.bias_tiles_total(), L.d_bias_tiles};
+  // A workspace that also holds two bias images lets both phases read the
+  // bias as whole 512-byte tiles; with one of the minimum size (statistics
+  // only) every score gathers its own two bytes.
+  if (bias && workspace_bytes >= attention_backward_workspace_bytes(L, H)) {
+    char* img = static_cast<char*>(workspace) + images_offset(L, H);
+    a.img_q = reinterpret_cast<const uint2*>(img);
+    a.img_k = reinterpret_cast<const uint2*>(img + bias_image_bytes(L, H));
+    hipError_t e = launch_bias_image(L, axis, H, bias, ld_bias, ld_bias_head, 1.f, (void*)a.img_q, s);
+    // by keys: the image of the transposed bias
+    if (e == hipSuccess) e = launch_bias_image(L, 1 - axis, H, bias, ld_bias, ld_bias_head, 1.f, (void*)a.img_k, s);
+    if (e != hipSuccess) return e;
   }
-  hipError_t e = hipGetLastError();
+  const int nt_max = (L.max_len + 31) / 32 * 2;
+  const size_t smem = (size_t)nt_max * (4 * 1024 + 2 * 16 * sizeof(float));
+  const unsigned grid = (unsigned)(L.attn_items() * H);
+  // Waves per workgroup: as many as keep four waves on each SIMD with the
+  // workgroups that fit a CU's 160 KB of LDS, and no more than the tiles.
+  hipError_t e = nt_max <= 8 ? launch_rows<4>(a, nt_max, grid, smem, s)
+                 : smem <= 80 * 1024 ? launch_rows<8>(a, nt_max, grid, smem, s)
+                                     : launch_rows<16>(a, nt_max, grid, smem, s);
   if (e != hipSuccess || !dbias) return e;
-  const int64_t qblocks = L.cu_qblk.back();
-  if (qblocks == 0) return hipSuccess;
-  attn_bwd_bias_kernel<<<dim3((unsigned)qblocks, (unsigned)H), dim3(256), 0, s>>>(a);
+  const int64_t nq = (L.max_len + 15) / 16, nk = (L.max_len + kBiasKeys - 1) / kBiasKeys;
+  const int64_t per = (nq * nk * H + kXcds - 1) / kXcds;     // waves per XCD of the longest sample
+  const int64_t nb = (per + 3) / 4 * kXcds;
+  attn_bwd_bias_kernel<<<dim3((unsigned)(nb * L.batch)), dim3(256), 0, s>>>(a, (int)nb);
   return hipGetLastError();
 }
 

@@ -195,14 +195,24 @@ hipError_t launch_linear_backward(const nt_linear_bwd_args& a, void* ws, hipStre
 
 // Attention backward (k_attention_backward.hip): bf16, head_dim 32, axes 0
 // and 1, N_i <= 512.  Workspace: the softmax statistics of every query
-// element, attention_backward_workspace_bytes(L, H) bytes.
+// element
+// and two bias images; a call with at least
+// attention_backward_min_workspace_bytes(L, H) (the statistics alone) also
+// runs, gathering the bias.
+size_t attention_backward_min_workspace_bytes(const nt_layout& L, int H);
 size_t attention_backward_workspace_bytes(const nt_layout& L, int H);
 hipError_t launch_attention_backward(const nt_layout& L, int axis, int H, const void* q, const void* k,
                                      const void* v, int64_t ld_qkv, const void* bias, int64_t ld_bias,
                                      int64_t ld_bias_head, const void* dout,
                                      int64_t ld_dout, float scale, void* dq, void* dk, void* dv, int64_t ld_dqkv,
                                      float* dbias, int64_t ld_dbias, int64_t ld_dbias_head, void* workspace,
-                                     hipStream_t s);
+                                     size_t workspace_bytes, hipStream_t s);
+
+// Image of a pair bias (k_attention.hip, bias_image_kernel): bias(j, k) *
+// mul rounded to bf16, in the lanes' register order, -inf past N.
+size_t bias_image_bytes(const nt_layout& L, int H);
+hipError_t launch_bias_image(const nt_layout& L, int axis, int H, const void* bias, int64_t ld_bias,
+                             int64_t ld_bias_head, float mul, void* img, hipStream_t s);
 
 // Bias-image bytes of a pair attention call (0: none).
 size_t attention_workspace_bytes(const nt_layout& L, int axis, int H, int D, nt_dtype dtype, bool has_bias);
