@@ -546,8 +546,9 @@ nt_status nt_triangle_mul_backward(const nt_layout* layout, int32_t direction, i
  * overwritten (NULL: not computed).  fp32 arithmetic, no atomics.
  * Workspace: at least 8 * H * sum N^2 bytes (the softmax statistics of every
  * query); with the size that nt_pair_row_attention_backward_workspace returns
- * (two bias images behind them) the bias is read as whole tiles instead of
- * value by value.
+ * (two bias images and partial sums of the bias gradient behind them) the bias
+ * is read as whole tiles and the bias gradient summed in row chunks instead of
+ * value by value over all rows.
  * Errors: NT_ERR_INVALID_ARG, NT_ERR_UNSUPPORTED (axis, dtype, head_dim,
  * N_i > 512).                                                                */
 nt_status nt_pair_row_attention_backward(const nt_layout* layout, int32_t axis, int32_t heads, int32_t head_dim,

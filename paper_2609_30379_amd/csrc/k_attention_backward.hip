@@ -17,14 +17,14 @@
 // and dO are copied into LDS.  Phase A: a wave per 16-query tile, first the
 // softmax statistics over all keys, then dQ; phase B: a wave per 16-key tile,
 // dK and dV.  lse and D go to the workspace for the bias gradient.
-// attn_bwd_bias_kernel: a wave per (sample, head, 16 queries, 64 keys) walks
-// all pair rows and keeps the 16 x 64 sums of dS in registers (no atomics).
+// attn_bwd_bias_kernel: a workgroup per (sample, head, 64 queries, 64 keys)
+// walks all pair rows and keeps its sums of dS in registers (no atomics).
 //
 // The vector units bound the rows kernel: per score it spends about 16 vector
 // instructions on the 3-way splits and one exponential in each of three
 // passes (statistics, dQ, dK/dV), against 30 products per 512 scores.  At
 // B=8, N 66..317, 4 heads: 568 us; one thread per query or key with fp32 FMAs
-// took 12.2 ms (and the bias gradient 5.8 ms, now 761 us).
+// took 12.2 ms (and the bias gradient 5.8 ms).
 #include "nt_device.h"
 #include "nt_internal.h"
 
@@ -358,90 +358,153 @@ __global__ void __launch_bounds__(64 * NW, 4) attn_bwd_rows_kernel(AttnBwdArgs p
   }
 }
 
-// Bias gradient: wave = (sample, head, 16 queries, 64 keys).  The items of a
-// sample are cut into eight equal stretches, one per XCD, ordered by head, so
-// the q, k, v and dO rows that the waves of an XCD walk together come from
-// its own L2.  kRows pair rows are loaded at once (their fragments straight
-// from global memory), so a row's latency is paid once per kRows rows.
-constexpr int kBiasKeys = 64, kBiasRows = 2;
+// Bias gradient: workgroup = (sample, head, 64 queries, 64 keys), 8 waves of
+// 16 x 32 sums each.  It walks all pair rows; a row's 64 q, dO, k and v rows
+// (16 KB) and softmax statistics are copied into one of kBiasStages LDS
+// stages, kBiasStages - 1 rows ahead, with one barrier per row.  The items of
+// a sample are cut into eight equal stretches, one per XCD, ordered by head,
+// so the rows that the workgroups of an XCD walk together come from its own
+// L2.  The texture-address unit bounds it (each copy instruction gathers 16
+// rows of 64 bytes), so operands are shared by 64 x 64 blocks: a wave loading
+// its own 16 x 64 block straight into registers took 761 us at B=8,
+// N 66..317, 4 heads (2.5 KB per 256 scores instead of 1 KB, and every row's
+// latency exposed).  With room for partial sums a workgroup walks
+// kBiasChunk rows only and bias_grad_sum_kernel adds the chunks in order:
+// walking all N rows, the workgroups of an XCD drift apart and each fetches
+// its rows past the L2 again (12 M misses, 358 us at the same sizes).
+constexpr int kBiasBlk = 64, kBiasStages = 3, kBiasChunk = 64;
+constexpr int kBiasStageBytes = 16 * 1024 + 512;          // 4 tiles each of q, dO, k, v; 64 lse, 64 D
 
-__global__ void __launch_bounds__(256) attn_bwd_bias_kernel(AttnBwdArgs p, int nb) {
+__device__ __forceinline__ void wait_vm(int left) {
+  // at most `left` vector-memory operations outstanding (the other counters free)
+  switch (left) {
+    case 0: __builtin_amdgcn_s_waitcnt(0x0F70); break;
+    case 2: __builtin_amdgcn_s_waitcnt(0x0F72); break;
+    case 3: __builtin_amdgcn_s_waitcnt(0x0F73); break;
+  }
+}
+
+__global__ void __launch_bounds__(512, 4) attn_bwd_bias_kernel(AttnBwdArgs p, int nb, int chunk, float* partial) {
+  __shared__ __attribute__((aligned(16))) unsigned char stages[kBiasStages * kBiasStageBytes];
   const int i = blockIdx.x / nb, blk = blockIdx.x % nb;   // nb workgroups per sample, a multiple of 8
   const int n = p.cu_seqlens[i + 1] - p.cu_seqlens[i];
-  const int nq = (n + 15) >> 4, nk = (n + kBiasKeys - 1) / kBiasKeys;
-  const int items = p.H * nq * nk;                        // (head, 16-query tile, 64-key block)
+  const int nq = (n + kBiasBlk - 1) / kBiasBlk;
+  const int nc = (n + chunk - 1) / chunk;
+  const int items = p.H * nc * nq * nq;                   // (head, row chunk, query block, key block)
   const int per = (items + kXcds - 1) / kXcds;
-  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-  const int slot = (blk / kXcds) * 4 + wave;
-  const int item = (blk % kXcds) * per + slot;
+  const int slot = blk / kXcds, item = (blk % kXcds) * per + slot;
   if (slot >= per || item >= items) return;
-  const int h = item / (nq * nk), qt = (item / nk) % nq, kb = item % nk;
-  const int lane = threadIdx.x & 63, l16 = lane & 15, g = lane >> 4;
+  const int hc = item / (nq * nq), h = hc / nc, rc = hc % nc;
+  const int j0 = (item / nq) % nq * kBiasBlk, k0 = item % nq * kBiasBlk;
+  const int r_first = rc * chunk, r_end = min(n, r_first + chunk);
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int l16 = lane & 15, g = lane >> 4;
   const int64_t cu = p.cu_pairs[i];
   const int64_t step = p.axis == 0 ? 1 : n, rstep = p.axis == 0 ? n : 1;
-  const int j = qt * 16 + l16, k0 = kb * kBiasKeys;
-  constexpr int KT = kBiasKeys / 16;
-  // this lane's rows, past N clamped to the last one (their sums are not stored)
-  const int64_t jrow = cu + (int64_t)min(j, n - 1) * step;
-  const bf16* qp = p.q + jrow * p.ld_qkv + h * kD + g * 8;
-  const bf16* gp = p.dout + jrow * p.ld_dout + h * kD + g * 8;
-  int64_t koff[KT];
+
+  // copies of this wave: tiles 2 w, 2 w + 1 of [q 0-3 | dO 4-7 | k 8-11 | v 12-15],
+  // rows past N repeat row N - 1 (their sums are not stored); waves 0 and 1
+  // also copy the 64 queries' lse and D
+  const int which = wave >> 1;
+  const int64_t ld = which == 1 ? p.ld_dout : p.ld_qkv;
+  const bf16* src = (which == 0 ? p.q : which == 1 ? p.dout : which == 2 ? p.k : p.v) + h * kD + g * 8;
+  const int first = (which < 2 ? j0 : k0) + (wave & 1) * 32 + (l16 ^ ((g & 1) << 3));
+  const bf16* s0 = src + (cu + (int64_t)min(first, n - 1) * step) * ld;
+  const bf16* s1 = src + (cu + (int64_t)min(first + 16, n - 1) * step) * ld;
+  const int64_t rld = rstep * ld;
+  const float* stat = (wave == 0 ? p.lse : p.dsum) + (int64_t)h * p.cells + cu + min(j0 + lane, n - 1);
+  auto copy_row = [&](int r, int stage) {
+    unsigned char* st = stages + stage * kBiasStageBytes;
+    unsigned char* dst = st + wave * 2048;
+    __builtin_amdgcn_global_load_lds((const void*)(s0 + r * rld), (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
+    __builtin_amdgcn_global_load_lds((const void*)(s1 + r * rld), (__attribute__((address_space(3))) void*)(dst + 1024), 16, 0, 0);
+    if (wave < 2)
+      __builtin_amdgcn_global_load_lds((const void*)(stat + (int64_t)r * n),
+                                       (__attribute__((address_space(3))) void*)(st + 16384 + wave * 256), 4, 0, 0);
+  };
+
+  // this wave's sums: queries j0 + 16 qw + l16, keys k0 + 32 kw + 16 t + 4 g + e
+  const int qw = wave >> 1, kw = wave & 1;
+  const int j = j0 + 16 * qw + l16, kk = k0 + 32 * kw + 4 * g;
+  float b[2][4];
 #pragma unroll
-  for (int t = 0; t < KT; ++t)
-    koff[t] = (cu + (int64_t)min(k0 + 16 * t + l16, n - 1) * step) * p.ld_qkv + h * kD + g * 8;
-  const float* lp = p.lse + (int64_t)h * p.cells + cu + min(j, n - 1);
-  const float* dp = p.dsum + (int64_t)h * p.cells + cu + min(j, n - 1);
-  float b[KT][4];
+  for (int t = 0; t < 2; ++t)
 #pragma unroll
-  for (int t = 0; t < KT; ++t)
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int k = k0 + 16 * t + 4 * g + e;
-      b[t][e] = j < n && k < n ? bias_at(p, cu, n, j, k, h) : 0.f;
-    }
+    for (int e = 0; e < 4; ++e) b[t][e] = j < n && kk + 16 * t + e < n ? bias_at(p, cu, n, j, kk + 16 * t + e, h) : 0.f;
   const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-  f32x4 acc[KT];
+  f32x4 acc[2] = {zero, zero};
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) unsigned char*)stages;
+  const uint32_t fo = frag_offset(l16, g) * 2;
+  const uint32_t aq = lds0 + qw * 1024 + fo, ak = lds0 + 8192 + kw * 2048 + fo, as = lds0 + 16384 + (16 * qw + l16) * 4;
+
+  // the first kBiasStages - 1 rows in flight; copies past the last row repeat
+  // it, so every wave always has the same number outstanding
+  __builtin_amdgcn_s_waitcnt(0x0F70);                     // the bias loads: only copies are counted below
 #pragma unroll
-  for (int t = 0; t < KT; ++t) acc[t] = zero;
-  for (int r0 = 0; r0 < n; r0 += kBiasRows) {
-    bf16x8 qf[kBiasRows], gf[kBiasRows], kf[kBiasRows][KT], vf[kBiasRows][KT];
-    float ls[kBiasRows], ds[kBiasRows];
+  for (int r = 0; r < kBiasStages - 1; ++r) copy_row(min(r_first + r, r_end - 1), r);
+  int stage = 0;
+  for (int r = r_first; r < r_end; ++r) {
+    // this wave's copies of row r have landed (those of row r + 1 may be in
+    // flight); past the barrier everyone's have, and row r - 1's stage is free
+    static_assert(kBiasStages == 3, "one later row in flight");
+    wait_vm(wave < 2 ? 3 : 2);
+    __builtin_amdgcn_s_barrier();
+    const int next = stage == 0 ? kBiasStages - 1 : stage - 1;
+    copy_row(min(r + kBiasStages - 1, r_end - 1), next);
+    uint4 f[6];
+    float ls, ds;
+    const uint32_t so = stage * kBiasStageBytes;
+    asm volatile(
+        "ds_read_b128 %0, %8\n"
+        "ds_read_b128 %1, %9\n"
+        "ds_read_b128 %2, %8 offset:4096\n"
+        "ds_read_b128 %3, %9 offset:4096\n"
+        "ds_read_b128 %4, %9 offset:1024\n"
+        "ds_read_b128 %5, %9 offset:5120\n"
+        "ds_read_b32 %6, %10\n"
+        "ds_read_b32 %7, %10 offset:256\n"
+        "s_waitcnt lgkmcnt(0)"
+        : "=&v"(f[0]), "=&v"(f[1]), "=&v"(f[2]), "=&v"(f[3]), "=&v"(f[4]), "=&v"(f[5]), "=&v"(ls), "=&v"(ds)
+        : "v"(aq + so), "v"(ak + so), "v"(as + so)
+        : "memory");
+    const bf16x8 qf = __builtin_bit_cast(bf16x8, f[0]), gf = __builtin_bit_cast(bf16x8, f[2]);
 #pragma unroll
-    for (int u = 0; u < kBiasRows; ++u) {
-      const int64_t r = min(r0 + u, n - 1);
-      const int64_t ro = r * rstep * p.ld_qkv;
-      qf[u] = *reinterpret_cast<const bf16x8*>(qp + ro);
-      gf[u] = *reinterpret_cast<const bf16x8*>(gp + r * rstep * p.ld_dout);
+    for (int t = 0; t < 2; ++t) {
+      const f32x4 s = mfma16(__builtin_bit_cast(bf16x8, f[t ? 4 : 1]), qf, zero);
+      const f32x4 d = mfma16(__builtin_bit_cast(bf16x8, f[t ? 5 : 3]), gf, zero);
 #pragma unroll
-      for (int t = 0; t < KT; ++t) {
-        kf[u][t] = *reinterpret_cast<const bf16x8*>(p.k + koff[t] + ro);
-        vf[u][t] = *reinterpret_cast<const bf16x8*>(p.v + koff[t] + ro);
-      }
-      ls[u] = lp[r * n];
-      ds[u] = dp[r * n];
+      for (int e = 0; e < 4; ++e)
+        acc[t][e] = fmaf(exp_native(fmaf(s[e], p.scale, b[t][e]) - ls), d[e] - ds, acc[t][e]);
     }
-#pragma unroll
-    for (int u = 0; u < kBiasRows; ++u) {
-      if (r0 + u >= n) break;
-#pragma unroll
-      for (int t = 0; t < KT; ++t) {
-        const f32x4 s = mfma16(kf[u][t], qf[u], zero), d = mfma16(vf[u][t], gf[u], zero);
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          acc[t][e] = fmaf(exp_native(fmaf(s[e], p.scale, b[t][e]) - ls[u]), d[e] - ds[u], acc[t][e]);
-      }
-    }
+    stage = stage == kBiasStages - 1 ? 0 : stage + 1;
   }
+  __builtin_amdgcn_s_waitcnt(0);                          // no copy into LDS outlives the workgroup
   if (j >= n) return;
 #pragma unroll
-  for (int t = 0; t < KT; ++t)
+  for (int t = 0; t < 2; ++t)
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const int k = k0 + 16 * t + 4 * g + e;
+      const int k = kk + 16 * t + e;
       if (k >= n) continue;
       const int64_t cell = cu + (p.axis == 0 ? (int64_t)j * n + k : (int64_t)k * n + j);
-      p.dbias[cell * p.ld_dbias + (int64_t)h * p.ld_dbias_head] = acc[t][e];
+      if (partial) partial[((int64_t)rc * p.H + h) * p.cells + cell] = acc[t][e];
+      else p.dbias[cell * p.ld_dbias + (int64_t)h * p.ld_dbias_head] = acc[t][e];
     }
+}
+
+// Sums the row chunks' partials of every cell and head in chunk order.
+__global__ void __launch_bounds__(256) bias_grad_sum_kernel(AttnBwdArgs p, int batch, int chunk, const float* partial) {
+  const int64_t cell = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (cell >= p.cells) return;
+  int lo = 0, hi = batch - 1;                             // sample: largest i with cu_pairs[i] <= cell
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (p.cu_pairs[mid] <= cell) lo = mid; else hi = mid - 1;
+  }
+  const int n = p.cu_seqlens[lo + 1] - p.cu_seqlens[lo], nc = (n + chunk - 1) / chunk, h = blockIdx.y;
+  float s = 0.f;
+  for (int c = 0; c < nc; ++c) s += partial[((int64_t)c * p.H + h) * p.cells + cell];
+  p.dbias[cell * p.ld_dbias + (int64_t)h * p.ld_dbias_head] = s;
 }
 
 template <int NW>
@@ -458,6 +521,7 @@ hipError_t launch_rows(const AttnBwdArgs& a, int nt_max, unsigned grid, size_t s
 // them are aligned
 size_t stats_bytes(const nt_layout& L, int H) { return 2 * (size_t)L.sum_n2 * (size_t)H * sizeof(float); }
 size_t images_offset(const nt_layout& L, int H) { return (stats_bytes(L, H) + 255) / 256 * 256; }
+int bias_chunks(const nt_layout& L) { return (L.max_len + kBiasChunk - 1) / kBiasChunk; }
 
 }  // namespace
 
@@ -465,7 +529,7 @@ size_t attention_backward_min_workspace_bytes(const nt_layout& L, int H) { retur
 
 size_t attention_backward_workspace_bytes(const nt_layout& L, int H) {
   if (L.sum_n2 == 0) return 0;
-  return images_offset(L, H) + 2 * bias_image_bytes(L, H);
+  return images_offset(L, H) + 2 * bias_image_bytes(L, H) + (size_t)bias_chunks(L) * H * L.sum_n2 * sizeof(float);
 }
 
 hipError_t launch_attention_backward(const nt_layout& L, int axis, int H, const void* q, const void* k,
@@ -480,10 +544,12 @@ hipError_t launch_attention_backward(const nt_layout& L, int axis, int H, const 
                 ld_bias_head, (const bf16*)dout, ld_dout, scale, (bf16*)dq, (bf16*)dk,
                 (bf16*)dv, ld_dqkv, dbias, ld_dbias, ld_dbias_head, lse, lse + L.sum_n2 * H, L.sum_n2, L.d_attn_work,
                 L.d_cu_seqlens, L.d_cu_pairs, nullptr, nullptr, L.bias_tiles_total(), L.d_bias_tiles};
-  // A workspace that also holds two bias images lets both phases read the
-  // bias as whole 512-byte tiles; with one of the minimum size (statistics
-  // only) every score gathers its own two bytes.
-  if (bias && workspace_bytes >= attention_backward_workspace_bytes(L, H)) {
+  // A workspace of the full size also holds two bias images, so that both
+  // phases read the bias as whole 512-byte tiles, and the bias gradient's
+  // partial sums; with one of the minimum size (statistics only) every score
+  // gathers its own two bytes and a workgroup walks all pair rows.
+  const bool full = workspace_bytes >= attention_backward_workspace_bytes(L, H);
+  if (bias && full) {
     char* img = static_cast<char*>(workspace) + images_offset(L, H);
     a.img_q = reinterpret_cast<const uint2*>(img);
     a.img_k = reinterpret_cast<const uint2*>(img + bias_image_bytes(L, H));
@@ -501,10 +567,15 @@ hipError_t launch_attention_backward(const nt_layout& L, int axis, int H, const 
                  : smem <= 80 * 1024 ? launch_rows<8>(a, nt_max, grid, smem, s)
                                      : launch_rows<16>(a, nt_max, grid, smem, s);
   if (e != hipSuccess || !dbias) return e;
-  const int64_t nq = (L.max_len + 15) / 16, nk = (L.max_len + kBiasKeys - 1) / kBiasKeys;
-  const int64_t per = (nq * nk * H + kXcds - 1) / kXcds;     // waves per XCD of the longest sample
-  const int64_t nb = (per + 3) / 4 * kXcds;
-  attn_bwd_bias_kernel<<<dim3((unsigned)(nb * L.batch)), dim3(256), 0, s>>>(a, (int)nb);
+  const int64_t nq = (L.max_len + kBiasBlk - 1) / kBiasBlk;
+  const int chunk = full ? kBiasChunk : kAttnLongLen, nc = (L.max_len + chunk - 1) / chunk;
+  float* partial = nc > 1 ? reinterpret_cast<float*>(static_cast<char*>(workspace) + images_offset(L, H) + 2 * bias_image_bytes(L, H))
+                          : nullptr;
+  const int64_t nb = (nq * nq * nc * H + kXcds - 1) / kXcds * kXcds;   // workgroups of the longest sample
+  attn_bwd_bias_kernel<<<dim3((unsigned)(nb * L.batch)), dim3(512), 0, s>>>(a, (int)nb, chunk, partial);
+  e = hipGetLastError();
+  if (e != hipSuccess || !partial) return e;
+  bias_grad_sum_kernel<<<dim3((unsigned)((L.sum_n2 + 255) / 256), (unsigned)H), dim3(256), 0, s>>>(a, L.batch, chunk, partial);
   return hipGetLastError();
 }
 

@@ -196,7 +196,8 @@ hipError_t launch_linear_backward(const nt_linear_bwd_args& a, void* ws, hipStre
 // Attention backward (k_attention_backward.hip): bf16, head_dim 32, axes 0
 // and 1, N_i <= 512.  Workspace: the softmax statistics of every query
 // element
-// and two bias images; a call with at least
+// and, for the full size, two bias images and the bias gradient's partial
+// sums; a call with at least
 // attention_backward_min_workspace_bytes(L, H) (the statistics alone) also
 // runs, gathering the bias.
 size_t attention_backward_min_workspace_bytes(const nt_layout& L, int H);
