@@ -400,6 +400,15 @@ nt_status nt_pair_row_attention_workspace(const nt_layout* layout, int32_t axis,
                                           int32_t head_dim, nt_dtype dtype, int32_t has_bias,
                                           uint64_t* bytes);
 
+/* Workspace with which nt_pair_row_attention runs its fastest path, in bytes:
+ * the minimum, or where a sample is longer than 512 and no workspace is
+ * needed, the size of the bias image (H * T * 512 bytes, see above), which
+ * the kernel for those samples reads instead of gathering the bias.
+ * Errors: NT_ERR_INVALID_ARG.                                               */
+nt_status nt_pair_row_attention_full_workspace(const nt_layout* layout, int32_t axis, int32_t heads,
+                                          int32_t head_dim, nt_dtype dtype, int32_t has_bias,
+                                          uint64_t* bytes);
+
 /* ---------------------------------------------------------------- triangle
  * Triangle multiplicative update, channelwise (Sec. 4.3, after the AlphaFold 3
  * Pairformer; reading: no gates, no output projection), accumulated into z:

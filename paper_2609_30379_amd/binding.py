@@ -94,6 +94,7 @@ def load(path: str = LIB_PATH):
         "nt_layernorm_linear_workspace": [C.POINTER(LinearArgs), C.POINTER(u64)],
         "nt_pair_row_attention": [vp, i32, i32, i32, vp, vp, vp, i64, vp, i64, i64, f32, vp, i64, C.c_int, vp, u64, vp],
         "nt_pair_row_attention_workspace": [vp, i32, i32, i32, C.c_int, i32, C.POINTER(u64)],
+        "nt_pair_row_attention_full_workspace": [vp, i32, i32, i32, C.c_int, i32, C.POINTER(u64)],
         "nt_cross_attention": [vp, vp, i32, i32, vp, i64, vp, vp, i64, f32, vp, i64, C.c_int, vp],
         "nt_pair_row_attention_gated": [vp, i32, i32, i32, vp, vp, vp, i64, vp, i64, vp, i64, i64, f32, vp, i64,
                                         C.c_int, vp, u64, vp],
@@ -328,6 +329,17 @@ def attention_workspace_bytes(layout: NestedLayout, axis: int, heads: int, head_
     return int(n.value)
 
 
+def attention_full_workspace_bytes(layout: NestedLayout, axis: int, heads: int, head_dim: int, dtype: str = "bf16",
+                                   has_bias: bool = True) -> int:
+    """As attention_workspace_bytes, with room for the bias image of samples
+    longer than 512, which run faster with one."""
+    n = C.c_uint64()
+    _check(load().nt_pair_row_attention_full_workspace(layout.handle, int(axis), int(heads), int(head_dim),
+                                                       NT_BF16 if dtype == "bf16" else NT_F32, int(bool(has_bias)),
+                                                       C.byref(n)))
+    return int(n.value)
+
+
 def nt_pair_row_attention(layout: NestedLayout, axis: int, heads: int, head_dim: int, q, k, v, o,
                           bias=None, scale: float | None = None, bias_layout: str = "cells", workspace=None,
                           gate=None):
@@ -355,8 +367,9 @@ def nt_pair_row_attention(layout: NestedLayout, axis: int, heads: int, head_dim:
     scale = 1.0 / float(np.sqrt(head_dim)) if scale is None else float(scale)
     dt = _dtype(q)
     if workspace is None:
-        workspace = workspace_tensor(attention_workspace_bytes(layout, axis, heads, head_dim,
-                                                               "bf16" if dt == NT_BF16 else "f32", bias is not None))
+        workspace = workspace_tensor(attention_full_workspace_bytes(layout, axis, heads, head_dim,
+                                                                    "bf16" if dt == NT_BF16 else "f32",
+                                                                    bias is not None))
     pw, nw = _ws(workspace)
     if gate is not None:
         pg, ldg = _mat(gate, "gate")

@@ -106,7 +106,7 @@ class PairWorkspace:
         self.m = torch.empty((S, c_z), dtype=torch.float32, device=device)
         # op scratch: the attention bias image (both axes) and the
         # transition's weight image, used one op at a time on one stream
-        need = max(B.attention_workspace_bytes(layout, ax, heads, c_z // heads, dtype, True) for ax in (0, 1))
+        need = max(B.attention_full_workspace_bytes(layout, ax, heads, c_z // heads, dtype, True) for ax in (0, 1))
         need = max(need, B.layernorm_linear_workspace_bytes(R, c_z, c_z, dtype, epilogue="swiglu_residual",
                                                             hidden=4 * c_z))
         if gated:

@@ -55,6 +55,7 @@ nt_status upload(nt_layout* L, hipStream_t s) {
       {&L->cu_pairs, &L->d_cu_pairs},     {&L->cu_pad, &L->d_cu_pad},
       {&L->row_splits2, &L->d_row_splits2}, {&L->row_sample, &L->d_row_sample},
       {&L->attn_work, &L->d_attn_work},   {&L->tri_work, &L->d_tri_work},
+      {&L->lattn_work, &L->d_lattn_work},
       {&L->seq_work, &L->d_seq_work},
       {&L->blk_prow, &L->d_blk_prow},
       {&L->pattn_work, &L->d_pattn_work}, {&L->bias_tiles, &L->d_bias_tiles},
@@ -495,6 +496,10 @@ nt_status pair_row_attention(const nt_layout* L, int32_t axis, int32_t H, int32_
   if (nt_status st = need_workspace(nt::attention_workspace_bytes(*L, axis, H, D, dtype, bias != nullptr), workspace,
                                     workspace_bytes, "nt_pair_row_attention_workspace"))
     return st;
+  // a workspace too small for the bias image (or misaligned) is not used
+  if (workspace && (!aligned16(workspace) ||
+                    workspace_bytes < nt::attention_full_workspace_bytes(*L, axis, H, D, dtype, bias != nullptr)))
+    workspace = nullptr;
   if (nt_status st = need_device(L)) return st;
   if (rows == 0) return NT_OK;
   if (!q || !k || !v || !o) return nt::fail(NT_ERR_INVALID_ARG, "q, k, v and o must be non-NULL");
@@ -642,6 +647,16 @@ nt_status nt_pair_row_attention_workspace(const nt_layout* L, int32_t axis, int3
   if (axis < 0 || axis > 3 || H <= 0 || D <= 0 || !valid_dtype(dtype) || (has_bias != 0 && has_bias != 1))
     return nt::fail(NT_ERR_INVALID_ARG, "bad axis, heads, head_dim, dtype or has_bias");
   *bytes = nt::attention_workspace_bytes(*L, axis, H, D, dtype, has_bias != 0);
+  return NT_OK;
+}
+
+nt_status nt_pair_row_attention_full_workspace(const nt_layout* L, int32_t axis, int32_t H, int32_t D, nt_dtype dtype,
+                                          int32_t has_bias, uint64_t* bytes) {
+  g_last_error.clear();
+  if (!L || !bytes) return nt::fail(NT_ERR_INVALID_ARG, "NULL argument");
+  if (axis < 0 || axis > 3 || H <= 0 || D <= 0 || !valid_dtype(dtype) || (has_bias != 0 && has_bias != 1))
+    return nt::fail(NT_ERR_INVALID_ARG, "bad axis, heads, head_dim, dtype or has_bias");
+  *bytes = nt::attention_full_workspace_bytes(*L, axis, H, D, dtype, has_bias != 0);
   return NT_OK;
 }
 

@@ -353,6 +353,30 @@ __device__ __forceinline__ void vt_frags2(const bf16* Vr, int kb, const VtLane& 
   f[2] = pack_u2(r[4], r[5]);
   f[3] = pack_u2(r[6], r[7]);
 }
+// Values of a pair row staged in LDS, 1 KB per 16 keys: the 16-byte piece
+// (key, dims 8 d ..) sits in slot 16 d + (key ^ 8 (d & 1)), so that the pieces
+// of a transposed read fall on different banks.  Lane i of a 16-lane group
+// points at key 4 g + i/4, dims 4 (i%4) and receives keys 4 g .. 4 g + 3 of dim
+// l16 (see vt_lane); dims 16..31 are 512 bytes further on, the next 16 keys
+// 1024.  f[0] dims 0-15, f[1] dims 16-31 of 32 keys.
+__device__ __forceinline__ uint32_t row_tr_offset(int l16, int g) {
+  const int row = 4 * g + (l16 >> 2), d = (l16 & 3) >> 1;
+  return (uint32_t)((d * 16 + (row ^ (d << 3))) * 16 + (l16 & 1) * 8);
+}
+__device__ __forceinline__ void row_tr_frags(uint32_t a, bf16x8 (&f)[2]) {
+  uint2 r[4];
+  asm volatile(
+      "ds_read_b64_tr_b16 %0, %4\n"
+      "ds_read_b64_tr_b16 %1, %4 offset:1024\n"
+      "ds_read_b64_tr_b16 %2, %4 offset:512\n"
+      "ds_read_b64_tr_b16 %3, %4 offset:1536\n"
+      "s_waitcnt lgkmcnt(0)"
+      : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3])
+      : "v"(a)
+      : "memory");
+  f[0] = pack_u2(r[0], r[1]);
+  f[1] = pack_u2(r[2], r[3]);
+}
 // maximum over the four lanes l16 + 16 g holding one query: the swaps pair
 // lane l with l ^ 16, then with l ^ 32, and leave both values in place
 __device__ __forceinline__ float query_max(float v) {
@@ -802,6 +826,201 @@ __global__ void __launch_bounds__(64 * NW, (NMAX <= 256 || KS) ? 4 : 2) attentio
   }
 }
 
+// ---------------------------------------------------------------- pair attention, a workgroup per pair row
+// Pair attention for head_dim 32 (axes 0 and 1) and samples longer than
+// kAttnLongLen: a workgroup of W waves copies the keys and values of one pair
+// row of one head into LDS (128 bytes per key), and its waves take the row's
+// 16-query tiles in turn, all keys of the row per tile.  The copy is the only
+// barrier.  The bias of a tile is read in 64-key chunks from the bias image
+// (bf16, lane order, 512 bytes per 16 x 16 tile), one chunk ahead and across
+// tiles, so any row length that the LDS holds runs the same loop: registers
+// for the whole row's bias, as attention_pair_kernel keeps them, would take
+// the occupancy.  On shorter samples that kernel is the faster one (172 us
+// here against 136 there at B=8, N 208..224, 4 heads: a row's copy has no
+// other row's work to hide behind in its own workgroup).
+//
+// Scores are kept transposed (S^T = K Q^T + bias / scale).  The running
+// maximum is moved, and the accumulators rescaled, only where a score exceeds
+// it by more than 8 in log2 units, so most chunks need no exchange between
+// lanes.  A chunk whose keys are all masked (-inf) leaves a maximum of -inf
+// and weights of 0.
+template <int W, bool GATE, bool BIAS>
+__global__ void __launch_bounds__(64 * W, 4) attention_row_kernel(PairAttnArgs p) {
+  constexpr int D = 32;
+  extern __shared__ __attribute__((aligned(16))) bf16 lds[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, g = lane >> 4;
+  auto uni = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
+  // workgroup 8 (H k + h) + x runs on XCD x: the heads of a pair row, which
+  // share cache lines, follow each other on one XCD
+  const int x = blockIdx.x % kXcds, t0 = blockIdx.x / kXcds;
+  const int h = uni(t0 % p.H), pos = uni(t0 / p.H) * kXcds + x;
+  const int i = uni(p.work[2 * pos]), r = uni(p.work[2 * pos + 1]);
+  if (i < 0) return;
+  const int n = uni(p.cu_seqlens[i + 1] - p.cu_seqlens[i]);
+  const int nch = (n + 63) >> 6, nt = 4 * nch;          // 64-key chunks, key tiles
+  const int64_t cu = uni(p.cu_pairs[i]);
+  const int64_t base = p.axis == 0 ? cu + (int64_t)r * n : cu + r, st = p.axis == 0 ? 1 : n;
+  // rows of tile `tile` (16 elements of the pair row): a uniform 64-bit base
+  // and a 32-bit byte offset per lane (the launcher checks that 16 rows span
+  // less than 4 GB); rows (and whole tiles) past N repeat rows below N
+  auto at = [&](const bf16* b, int tile, int row_in_tile, int64_t ld, int dim) {
+    tile = min(tile, (n - 1) >> 4);
+    const int rl = min(row_in_tile, n - 1 - 16 * tile);
+    const char* u = reinterpret_cast<const char*>(b + (int64_t)(16 * tile) * st * ld);
+    return u + ((uint32_t)rl * (uint32_t)(st * ld) + (uint32_t)dim) * 2u;
+  };
+  const int64_t qoff = base * p.ld_qkv + h * D;
+
+  // ---- keys and values: [keys | values][tile] of 1 KB
+  {
+    const int row16 = l16 ^ ((g & 1) << 3);
+    for (int tile = wave; tile < nt; tile += W) {
+      __builtin_amdgcn_global_load_lds((const void*)at(p.k + qoff, tile, row16, p.ld_qkv, g * 8),
+                                       (__attribute__((address_space(3))) void*)(lds + tile * 512), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds((const void*)at(p.v + qoff, tile, row16, p.ld_qkv, g * 8),
+                                       (__attribute__((address_space(3))) void*)(lds + (nt + tile) * 512), 16, 0, 0);
+    }
+  }
+  const int nq = (n + 15) >> 4;
+  const uint2* img = BIAS ? p.bias_img + (int64_t)h * p.img_head + (int64_t)uni(p.bias_tiles[i]) * 64 : nullptr;
+  auto load_bias = [&](int qt, int c, uint2 (&b)[4]) {
+    if constexpr (BIAS) {
+      const uint2* u = img + (int64_t)(qt * nt + 4 * c) * 64;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) b[t] = u[(uint32_t)(t * 64 + lane)];
+    }
+  };
+  auto load_q = [&](int qt) { return *reinterpret_cast<const bf16x8*>(at(p.q + qoff, qt, l16, p.ld_qkv, g * 8)); };
+  // the (query tile, chunk) steps of this wave, in order
+  int c = 0, qt = wave;
+  uint2 b0[4], b1[4];
+  bf16x8 qf = bf16x8{}, qn = bf16x8{};
+  if (qt < nq) {
+    load_bias(qt, 0, b0);
+    qn = load_q(qt);
+  }
+  __builtin_amdgcn_s_waitcnt(0);
+  __syncthreads();
+  if (qt >= nq) return;
+
+  const uint32_t lds0 = lds_addr(lds), fo = (uint32_t)((g * 16 + (l16 ^ ((g & 1) << 3))) * 16), to = row_tr_offset(l16, g);
+  const float sc = p.scale_log2, slack = 8.f / sc;
+  const bf16x8 ones = ones_bf16x8();
+  float m_s = -INFINITY, nm = 0.f;                      // running maximum of bias/scale + q.k, and -m_s sc
+  f32x4 O[3];                                           // dims 0-15, 16-31, row sum
+  // one step with the bias in b; the next step's bias is read into bn.
+  // Returns false after the last step.
+  auto step = [&](const uint2 (&b)[4], uint2 (&bn)[4]) -> bool {
+    const bool last = c + 1 == nch;
+    const int qtn = last && qt + W < nq ? qt + W : qt;    // after the last tile: a read that nothing uses
+    load_bias(qtn, last ? 0 : c + 1, bn);
+    if (c == 0) {
+      qf = qn;
+      m_s = -INFINITY;
+      nm = 0.f;
+#pragma unroll
+      for (int u = 0; u < 3; ++u) O[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    uint2 gt[2];
+    if (last) {
+      qn = load_q(qtn);
+      if constexpr (GATE) {
+        const char* gr = at(p.gate + base * p.ld_gate + h * D, qt, l16, p.ld_gate, 4 * g);
+        gt[0] = *reinterpret_cast<const uint2*>(gr);
+        gt[1] = *reinterpret_cast<const uint2*>(gr + 32);
+      }
+    }
+    const uint32_t kt0 = (uint32_t)(4 * c * 1024);
+    const unsigned char* ks = reinterpret_cast<const unsigned char*>(lds) + kt0 + fo;
+    f32x4 S[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      S[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if constexpr (BIAS)
+        S[t] = f32x4{__uint_as_float(b[t].x << 16), __uint_as_float(b[t].x & 0xffff0000u),
+                     __uint_as_float(b[t].y << 16), __uint_as_float(b[t].y & 0xffff0000u)};
+      S[t] = mfma16(*reinterpret_cast<const bf16x8*>(ks + t * 1024), qf, S[t]);
+    }
+    if constexpr (!BIAS) {                              // keys past N (the image masks them)
+      if (64 * c + 64 > n) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (64 * c + 16 * t + 4 * g + e >= n) S[t][e] = -INFINITY;
+      }
+    }
+    float mx = S[0][0];
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) mx = fmaxf(mx, S[t][e]);
+    if (__any(mx > m_s + slack)) {
+      const float m_new = fmaxf(m_s, query_max(mx));
+      nm = m_new == -INFINITY ? 0.f : -m_new * sc;
+      const float alpha = __builtin_amdgcn_exp2f(fmaf(m_s, sc, nm));
+      m_s = m_new;
+#pragma unroll
+      for (int u = 0; u < 3; ++u) O[u] *= alpha;
+    }
+    bf16x8 P[2];
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        P[t >> 1][(t & 1) * 4 + e] = (bf16)__builtin_amdgcn_exp2f(fmaf(S[t][e], sc, nm));
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      bf16x8 vf[2];
+      row_tr_frags(lds0 + kt0 + (uint32_t)(nt * 1024 + u * 2048) + to, vf);
+      O[0] = mfma16(vf[0], P[u], O[0]);
+      O[1] = mfma16(vf[1], P[u], O[1]);
+      O[2] = mfma16(ones, P[u], O[2]);
+    }
+    if (last) {
+      // lane (l16, g) holds dims 4g .. 4g+3 and 16 + 4g .. +3 of its query;
+      // the rows g, g ^ 1 trade halves so that every lane stores 16 bytes
+      const float inv = 1.f / O[2][0];
+      uint32_t ow[2][2];
+#pragma unroll
+      for (int dt = 0; dt < 2; ++dt) {
+        float gs[4] = {1.f, 1.f, 1.f, 1.f};
+        if constexpr (GATE) {
+          const float gl[4] = {__uint_as_float(gt[dt].x << 16), __uint_as_float(gt[dt].x & 0xffff0000u),
+                               __uint_as_float(gt[dt].y << 16), __uint_as_float(gt[dt].y & 0xffff0000u)};
+#pragma unroll
+          for (int e = 0; e < 4; ++e) gs[e] = __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-gl[e] * kLog2e));
+        }
+        bf16x4 ov;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) ov[e] = (bf16)(O[dt][e] * inv * gs[e]);
+        const uint2 u = __builtin_bit_cast(uint2, ov);
+        ow[dt][0] = u.x;
+        ow[dt][1] = u.y;
+      }
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        const auto sw = __builtin_amdgcn_permlane16_swap(ow[0][e], ow[1][e], false, false);
+        ow[0][e] = sw[0];
+        ow[1][e] = sw[1];
+      }
+      if (qt * 16 + l16 < n) {
+        const int d0 = (g & 1) ? 16 + 4 * (g - 1) : 4 * g;
+        *reinterpret_cast<uint4*>(const_cast<char*>(at(p.o + base * p.ld_o + h * D, qt, l16, p.ld_o, d0))) =
+            make_uint4(ow[0][0], ow[0][1], ow[1][0], ow[1][1]);
+      }
+      if (qt + W >= nq) return false;
+      qt = qtn;
+      c = 0;
+      return true;
+    }
+    ++c;
+    return true;
+  };
+  while (step(b0, b1) && step(b1, b0)) {}
+}
+
 // ---------------------------------------------------------------- 1-D attention, head_dim 32 / 64
 // Variable-length attention over each sample's tokens (Sec. 3.3 "Attention
 // through packed blocks"), head_dim D in {32, 64}, at most NMAX keys per
@@ -1116,10 +1335,14 @@ hipError_t launch_bias_image(const nt_layout& L, int axis, int H, const void* bi
   return hipGetLastError();
 }
 
+size_t attention_full_workspace_bytes(const nt_layout& L, int axis, int H, int D, nt_dtype dtype, bool has_bias) {
+  // only the d = 32 pair kernels read the bias through an image
+  return !has_bias || dtype != NT_BF16 || D != 32 || axis == 2 ? 0 : bias_image_bytes(L, H);
+}
+
 size_t attention_workspace_bytes(const nt_layout& L, int axis, int H, int D, nt_dtype dtype, bool has_bias) {
-  // only the d = 32 pair kernel (N <= 512) reads the bias through an image
-  if (!has_bias || dtype != NT_BF16 || D != 32 || axis == 2 || L.max_len > kAttnLongLen) return 0;
-  return bias_image_bytes(L, H);
+  // past kAttnLongLen the image is optional: without it the per-row kernel gathers the bias
+  return L.max_len > kAttnLongLen ? 0 : attention_full_workspace_bytes(L, axis, H, D, dtype, has_bias);
 }
 
 namespace {
@@ -1177,6 +1400,24 @@ hipError_t launch_cross_attention(const nt_layout& Lq, const nt_layout& Lkv, int
   return hipGetLastError();
 }
 
+namespace {
+template <int W>
+hipError_t launch_attention_rows(const PairAttnArgs& a, int64_t items, int max_keys, hipStream_t s) {
+  const dim3 grid((unsigned)(items * a.H)), block(64 * W);
+  const size_t smem = (size_t)max_keys * 128;
+  const bool gate = a.gate != nullptr, bias = a.bias_img != nullptr;
+  const void* fn = gate ? (bias ? (const void*)attention_row_kernel<W, true, true> : (const void*)attention_row_kernel<W, true, false>)
+                        : (bias ? (const void*)attention_row_kernel<W, false, true> : (const void*)attention_row_kernel<W, false, false>);
+  const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+  if (e != hipSuccess) return e;
+  if (gate && bias) attention_row_kernel<W, true, true><<<grid, block, smem, s>>>(a);
+  else if (gate) attention_row_kernel<W, true, false><<<grid, block, smem, s>>>(a);
+  else if (bias) attention_row_kernel<W, false, true><<<grid, block, smem, s>>>(a);
+  else attention_row_kernel<W, false, false><<<grid, block, smem, s>>>(a);
+  return hipGetLastError();
+}
+}  // namespace
+
 hipError_t launch_attention(const nt_layout& L, int axis, int H, int D, const void* q, const void* k,
                             const void* v, int64_t ld_qkv, const void* bias, int64_t ld_bias, int64_t ld_bias_head,
                             float scale, void* o, int64_t ld_o, nt_dtype dtype, void* workspace, hipStream_t s,
@@ -1201,8 +1442,14 @@ hipError_t launch_attention(const nt_layout& L, int axis, int H, int D, const vo
   const int npad = (L.max_len + 63) & ~63;
   if (axis == 2 && L.max_len <= kAttnLongLen)
     return launch_seq_attention(L, L.d_cu_seqlens, L.max_len, H, D, q, ld_qkv, k, v, ld_qkv, scale, o, ld_o, s);
-  if (D == 32 && axis != 2 && L.max_len <= kAttnLongLen) {
-    if (L.pattn_items() == 0) return hipSuccess;
+  // Samples longer than kAttnLongLen go to the row kernel, which needs the
+  // bias image in the workspace and 32-bit lane offsets (16 rows of a tensor
+  // within 4 GB); without either the per-row kernel below takes the batch.
+  const bool longer = L.max_len > kAttnLongLen;
+  const int64_t ld_max = std::max(std::max(ld_qkv, ld_o), gate ? ld_gate : 0);
+  const bool rows_ok = axis <= 1 && (!bias || workspace) && 32 * ld_max * L.max_len < (int64_t(1) << 32);
+  if (D == 32 && axis != 2 && (!longer || rows_ok)) {
+    if (!longer && L.pattn_items() == 0) return hipSuccess;
     const int nmax = L.max_len <= kAttnShortLen ? kAttnShortLen : kAttnLongLen;
     const int64_t tiles = L.bias_tiles_total();
     const uint2* img = nullptr;
@@ -1223,6 +1470,15 @@ hipError_t launch_attention(const nt_layout& L, int axis, int H, int D, const vo
     // use 16 slots from its start
     const size_t smem_ksg = sizeof(bf16) * 4 * (size_t)kAttnLongLen * 32 +
                             std::max<size_t>(kAttnHandBytes + kAttnGateBytes / 2, kAttnGateBytes);
+    if (longer) {
+      PairAttnArgs al = a;
+      al.work = L.d_lattn_work;
+      const int keys = (L.max_len + 63) & ~63;
+      // 8 waves where two workgroups share a CU's 160 KB of LDS, else 16: four waves per SIMD either way
+      const hipError_t e = keys <= 640 ? launch_attention_rows<8>(al, L.lattn_items(), keys, s)
+                                       : launch_attention_rows<16>(al, L.lattn_items(), keys, s);
+      if (e != hipSuccess || L.pattn_items() == 0) return e;
+    }
     if (gate) {
       // gated output (axes 0 and 1): the GATE instances of the same kernels
       if (nmax == kAttnShortLen) {

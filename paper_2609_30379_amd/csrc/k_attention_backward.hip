@@ -65,6 +65,9 @@ struct AttnBwdArgs {
   const int32_t* bias_tiles;
 };
 
+// a value that is the same in all lanes, as a scalar
+__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
 __device__ __forceinline__ float exp_native(float x) { return __builtin_amdgcn_exp2f(x * kLog2e); }
 
 __device__ __forceinline__ uint32_t lds_addr(const bf16* ptr) {
@@ -179,11 +182,12 @@ __global__ void __launch_bounds__(64 * NW, 4) attn_bwd_rows_kernel(AttnBwdArgs p
   // workgroup 8 (H k + h) + x runs on XCD x: the heads of a pair row, which
   // share cache lines, run on one XCD one after the other
   const int x = blockIdx.x % kXcds, t0 = blockIdx.x / kXcds;
-  const int h = t0 % p.H, pos = (t0 / p.H) * kXcds + x;
-  const int i = p.work[2 * pos], r = p.work[2 * pos + 1];
+  // everything derived from the block index is the same in all lanes: kept in scalars
+  const int h = uni(t0 % p.H), pos = uni(t0 / p.H) * kXcds + x;
+  const int i = uni(p.work[2 * pos]), r = uni(p.work[2 * pos + 1]);
   if (i < 0) return;
-  const int n = p.cu_seqlens[i + 1] - p.cu_seqlens[i];
-  const int64_t cu = p.cu_pairs[i];
+  const int n = uni(p.cu_seqlens[i + 1] - p.cu_seqlens[i]);
+  const int64_t cu = uni(p.cu_pairs[i]);
   const int nt = (n + 15) >> 4, nt2 = (nt + 1) & ~1;      // 16-row tiles, padded to whole 32-row steps
   bf16* Qs = lds;
   bf16* Ks = Qs + nt_max * 512;
@@ -216,7 +220,7 @@ __global__ void __launch_bounds__(64 * NW, 4) attn_bwd_rows_kernel(AttnBwdArgs p
   const uint32_t to = tr_offset(l16, g);
   const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
   const int kti = ((n + 63) >> 6) * 4;
-  const int64_t img0 = IMG ? ((int64_t)h * p.img_tiles + p.bias_tiles[i]) * 64 + lane : 0;
+  const int64_t img0 = IMG ? ((int64_t)h * p.img_tiles + uni(p.bias_tiles[i])) * 64 : 0;
 
   // bias of the two tiles (a, b), (a, b + 1): values of lane (l16, g), -inf
   // outside the sample.  BYQ: query 16 a + l16, keys 16 b + 4 g + e; else
@@ -224,7 +228,7 @@ __global__ void __launch_bounds__(64 * NW, 4) attn_bwd_rows_kernel(AttnBwdArgs p
   auto bias8 = [&](bool byq, int a, int b, float (&out)[8]) {
     if constexpr (IMG) {
       const uint2* img = (byq ? p.img_q : p.img_k) + img0 + ((int64_t)a * kti + b) * 64;
-      const uint2 u[2] = {img[0], img[64]};
+      const uint2 u[2] = {img[(uint32_t)lane], img[(uint32_t)lane + 64]};
 #pragma unroll
       for (int w = 0; w < 2; ++w) {
         out[4 * w] = __uint_as_float(u[w].x << 16);
@@ -386,20 +390,21 @@ __device__ __forceinline__ void wait_vm(int left) {
 
 __global__ void __launch_bounds__(512, 4) attn_bwd_bias_kernel(AttnBwdArgs p, int nb, int chunk, float* partial) {
   __shared__ __attribute__((aligned(16))) unsigned char stages[kBiasStages * kBiasStageBytes];
-  const int i = blockIdx.x / nb, blk = blockIdx.x % nb;   // nb workgroups per sample, a multiple of 8
-  const int n = p.cu_seqlens[i + 1] - p.cu_seqlens[i];
+  const int i = uni(blockIdx.x / nb), blk = uni(blockIdx.x % nb);   // nb workgroups per sample, a multiple of 8
+  const int n = uni(p.cu_seqlens[i + 1] - p.cu_seqlens[i]);
   const int nq = (n + kBiasBlk - 1) / kBiasBlk;
-  const int nc = (n + chunk - 1) / chunk;
+  const int nc = uni((n + chunk - 1) / chunk);
   const int items = p.H * nc * nq * nq;                   // (head, row chunk, query block, key block)
   const int per = (items + kXcds - 1) / kXcds;
   const int slot = blk / kXcds, item = (blk % kXcds) * per + slot;
   if (slot >= per || item >= items) return;
-  const int hc = item / (nq * nq), h = hc / nc, rc = hc % nc;
-  const int j0 = (item / nq) % nq * kBiasBlk, k0 = item % nq * kBiasBlk;
+  const int hc = uni(item / (nq * nq)), h = uni(hc / nc), rc = hc - h * nc;
+  const int qk = item - hc * nq * nq, qb = uni(qk / nq);
+  const int j0 = qb * kBiasBlk, k0 = (qk - qb * nq) * kBiasBlk;
   const int r_first = rc * chunk, r_end = min(n, r_first + chunk);
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int l16 = lane & 15, g = lane >> 4;
-  const int64_t cu = p.cu_pairs[i];
+  const int64_t cu = uni(p.cu_pairs[i]);
   const int64_t step = p.axis == 0 ? 1 : n, rstep = p.axis == 0 ? n : 1;
 
   // copies of this wave: tiles 2 w, 2 w + 1 of [q 0-3 | dO 4-7 | k 8-11 | v 12-15],

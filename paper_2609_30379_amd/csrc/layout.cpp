@@ -189,18 +189,21 @@ nt_status plan_layout(const int32_t* lengths, int32_t batch, nt_layout* L, const
   L->cu_qblk.assign(batch + 1, 0);
   for (int32_t i = 0; i < batch; ++i) L->cu_qblk[i + 1] = L->cu_qblk[i] + (lengths[i] + 15) / 16;
 
-  // pair-row attention: one item per (sample, pair row), cost N_i^2
-  {
+  // pair-row attention: one item per (sample, pair row), cost N_i^2; and the
+  // same for the samples longer than kAttnLongLen alone
+  auto pair_row_items = [&](int32_t longer_than) {
     std::vector<std::array<int32_t, 2>> items;
     std::vector<double> cost;
     items.reserve(sn);
     for (int32_t i = 0; i < batch; ++i)
-      for (int32_t r = 0; r < lengths[i]; ++r) {
+      for (int32_t r = 0; r < lengths[i] && lengths[i] > longer_than; ++r) {
         items.push_back({i, r});
         cost.push_back((double)lengths[i] * lengths[i]);
       }
-    L->attn_work = xcd_order<2>(items, cost);
-  }
+    return xcd_order<2>(items, cost);
+  };
+  L->attn_work = pair_row_items(0);
+  L->lattn_work = pair_row_items(kAttnLongLen);
   // pair attention: a sample's 16-query tiles are split evenly over
   // ceil(tiles / W) blocks of at most W tiles (items: sample, first tile, row
   // group, tile count), so no block leaves most of its waves idle; generation
@@ -209,12 +212,13 @@ nt_status plan_layout(const int32_t* lengths, int32_t batch, nt_layout* L, const
   // (N <= 512) W is 16 for samples up to 256 long (a wave per query tile) and
   // 8 for longer ones (a wave pair per query tile); the N <= 256 persistent
   // instance needs no list (its workgroups find their rows from the prefix
-  // sums).
+  // sums).  Samples longer than kAttnLongLen have no items here.
   auto pair_attn_items = [&](auto W_of) {
     std::vector<std::array<int32_t, 4>> items;
     std::vector<double> cost;
     for (int32_t i = 0; i < batch; ++i) {
       const int32_t n = lengths[i], tiles = (n + 15) / 16, W = W_of(n);
+      if (n > kAttnLongLen) continue;               // their rows are in lattn_work
       const int32_t blocks = (tiles + W - 1) / W;
       for (int32_t rg = 0; rg * kAttnRG < n; ++rg)
         for (int32_t b = 0; b < blocks; ++b) {

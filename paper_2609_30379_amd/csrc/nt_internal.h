@@ -50,6 +50,7 @@ struct nt_layout {
   std::vector<int32_t> row_splits2;  // [sum N + 1]
   std::vector<int32_t> row_sample;   // [sum N]
   std::vector<int32_t> attn_work;    // pairs (sample, row); count multiple of 8; (-1,-1) = idle
+  std::vector<int32_t> lattn_work;   // as attn_work, samples longer than kAttnLongLen only
   std::vector<int32_t> tri_work;     // quads (sample, xt, yt, first item of the sample); count multiple of 8
   std::vector<int32_t> tri_split;    // [9] cost-balanced item ranges of the 8 XCDs
   int32_t tri_xcd_items = 0;         // largest item count of one XCD
@@ -71,6 +72,7 @@ struct nt_layout {
   const int32_t* d_row_splits2 = nullptr;
   const int32_t* d_row_sample = nullptr;
   const int32_t* d_attn_work = nullptr;
+  const int32_t* d_lattn_work = nullptr;
   const int32_t* d_tri_work = nullptr;
   const int32_t* d_seq_work = nullptr;
   const int32_t* d_pattn_work = nullptr;
@@ -84,6 +86,7 @@ struct nt_layout {
   const int32_t* d_col_sample = nullptr;
 
   int64_t attn_items() const { return (int64_t)attn_work.size() / 2; }
+  int64_t lattn_items() const { return (int64_t)lattn_work.size() / 2; }
   int64_t tri_items() const { return (int64_t)tri_work.size() / 4; }
   int64_t seq_items() const { return (int64_t)seq_work.size() / 2; }
   int64_t pattn_items() const { return (int64_t)pattn_work.size() / 4; }
@@ -215,10 +218,13 @@ size_t bias_image_bytes(const nt_layout& L, int H);
 hipError_t launch_bias_image(const nt_layout& L, int axis, int H, const void* bias, int64_t ld_bias,
                              int64_t ld_bias_head, float mul, void* img, hipStream_t s);
 
-// Bias-image bytes of a pair attention call (0: none).
+// Bias-image bytes that a pair attention call must be given (0: none), and
+// those of its fastest path: a call with a sample longer than kAttnLongLen
+// runs without an image too, on the per-row kernel.
 size_t attention_workspace_bytes(const nt_layout& L, int axis, int H, int D, nt_dtype dtype, bool has_bias);
+size_t attention_full_workspace_bytes(const nt_layout& L, int axis, int H, int D, nt_dtype dtype, bool has_bias);
 // bias element (cell c, head h) at bias[c * ld_bias + h * ld_bias_head];
-// workspace: attention_workspace_bytes(...) bytes.
+// workspace: attention_full_workspace_bytes(...) bytes, or NULL where attention_workspace_bytes(...) is 0.
 // gate (axes 0 and 1, or NULL): o = sigmoid(gate) * attention, gate element
 // (cell, channel) at gate[cell * ld_gate + channel].
 hipError_t launch_attention(const nt_layout& L, int axis, int H, int D,
