@@ -58,7 +58,8 @@ nt_status upload(nt_layout* L, hipStream_t s) {
       {&L->lattn_work, &L->d_lattn_work},
       {&L->seq_work, &L->d_seq_work},
       {&L->blk_prow, &L->d_blk_prow},
-      {&L->pattn_work, &L->d_pattn_work}, {&L->bias_tiles, &L->d_bias_tiles},
+      {&L->cu_short, &L->d_cu_short},
+      {&L->cu_short_cost, &L->d_cu_short_cost}, {&L->bias_tiles, &L->d_bias_tiles},
       {&L->sattn_work, &L->d_sattn_work},
       {&L->bc_cu_tiles, &L->d_bc_cu_tiles},
       {&L->cu_qblk, &L->d_cu_qblk},       {&L->tri_split, &L->d_tri_split},

@@ -209,7 +209,7 @@ struct PairAttnArgs {
   float scale_log2;
   bf16* o;
   int64_t ld_o;
-  const int32_t* work;   // quads (sample, first 16-query tile, row group, tile count)
+  const int32_t* work;   // axis 3: quads (sample, first 16-query tile, 0, tile count); row kernel: (sample, row) pairs
   const int32_t* cu_seqlens;
   const int32_t* cu_pairs;
   int H;                 // heads (interleaved in the grid)
@@ -217,7 +217,8 @@ struct PairAttnArgs {
   int64_t img_head;      // uint2 entries per head of the image
   const int32_t* bias_tiles;
   int batch;             // samples (persistent instance: rows are found from cu_seqlens)
-  int64_t total_rows;    // sum of N_i (persistent instance)
+  const int32_t* cu_short;   // persistent instance: prefix of the short samples' rows and of their cost
+  const int64_t* cu_cost;
   const bf16* gate;      // gated output: o = sigmoid(gate) * attention, gate [rows, >= H*D] (GATE instances)
   int64_t ld_gate;
 };
@@ -386,10 +387,6 @@ __device__ __forceinline__ float query_max(float v) {
   return fmaxf(__uint_as_float(s32[0]), __uint_as_float(s32[1]));
 }
 
-// key-split hand-over: 10 floats per lane of 8 query slots
-constexpr int kAttnHandBytes = 10 * 8 * 64 * 4;
-constexpr int kAttnGateBytes = 16 * 1024;        // gate slots: 16 waves x 1 KB (8 when the keys are split)
-
 // ---------------------------------------------------------------- pair attention, head_dim 32
 // Pair attention for head_dim 32 and N_i <= kAttnLongLen, organised so that
 // the exponentials are nearly the only vector work.  A workgroup of NW waves
@@ -412,28 +409,15 @@ constexpr int kAttnGateBytes = 16 * 1024;        // gate slots: 16 waves x 1 KB 
 //   * N <= 256, persistent, with 16 waves (all queries of a row in one
 //     workgroup, so a row's keys and values are copied once per CU; 64 KB of
 //     LDS, four waves per SIMD, one workgroup per CU with an equal share of
-//     the rows);
-//   * N <= 512, key split (KS): 16 waves from a work list of (sample, query
-//     block, group of 16 rows) items.  A sample longer than 256 splits its
-//     keys between wave pairs: waves w and w + 8 hold the same 16 queries,
-//     one the keys below the cut (half the row rounded up to 32 keys) and
-//     the other the rest, each with the bias registers of at most 16 key
-//     tiles (as the N <= 256 instance), and the second
-//     hands its running maximum and accumulators to the first through LDS,
-//     which merges them (rescaled to the larger maximum) and stores the row;
-//     a block then holds 8 query tiles.  Shorter samples use all 16 waves as
-//     query tiles.  128 KB of key/value buffers and 20 KB for the hand-over
-//     (the gated instance adds 8 KB of gate rows) keep one workgroup per CU
-//     at four waves per SIMD;
+//     the rows' cost; samples longer than 256 are skipped, their rows are
+//     attention_row_kernel's);
 //   * N <= 512, 8 waves, each wave all keys (the single attention of axis 3,
 //     one row per sample).
-template <int NMAX, int NW, bool PERSIST, bool GATE = false, bool KS = false>
-__global__ void __launch_bounds__(64 * NW, (NMAX <= 256 || KS) ? 4 : 2) attention_pair_kernel(PairAttnArgs p) {
+template <int NMAX, int NW, bool PERSIST, bool GATE = false>
+__global__ void __launch_bounds__(64 * NW, NMAX <= 256 ? 4 : 2) attention_pair_kernel(PairAttnArgs p) {
   constexpr int D = 32;
   constexpr int KT16 = NMAX / 16;               // key tiles
-  constexpr int BT = KS ? 16 : KT16;            // key tiles of bias kept per lane
   static_assert(!PERSIST || NW * 16 >= NMAX, "the persistent instance covers all queries of a row");
-  static_assert(!KS || (NMAX == 512 && NW == 16 && !PERSIST), "the key-split instance: 16 waves, N <= 512");
   extern __shared__ __attribute__((aligned(16))) bf16 lds[];
   bf16* Kb0 = lds;                                         // key images: tile of 16 keys -> 512 elements
   bf16* Kb1 = Kb0 + NMAX * D;
@@ -444,34 +428,48 @@ __global__ void __launch_bounds__(64 * NW, (NMAX <= 256 || KS) ? 4 : 2) attentio
 
   // ---- rows of this workgroup: packed rows [row, row_end) of one head, a
   // query block starting at tile qt0.
-  //   * work-list instance: workgroup 8 (H k + h) + x runs on XCD x and takes
-  //     work position pos = 8 k + x, head h: the H heads of a position are
-  //     consecutive workgroups of one XCD, so they read the same q|k|v cache
-  //     lines at about the same time; rows of one sample only.
+  //   * work-list instance (axis 3): workgroup 8 (H k + h) + x runs on XCD x
+  //     and takes work position pos = 8 k + x, head h: the H heads of a
+  //     position are consecutive workgroups of one XCD; one row per sample.
   //   * persistent instance (one workgroup per CU): XCD x takes the x-th
-  //     eighth of all packed rows, and its workgroups split that range among
-  //     the heads, workgroup k taking head k % H and the (k / H)-th of the
-  //     equal slices of that head, so every CU gets the same number of rows
-  //     (crossing sample boundaries) and the heads of a row still run on one
-  //     XCD together.
+  //     eighth of the cost of all short samples' rows, and its workgroups
+  //     split that range among the heads, workgroup k taking head k % H and
+  //     the (k / H)-th of the equal slices of that head (crossing sample
+  //     boundaries), so the heads of a row still run on one XCD together.
+  //     A row costs its 16-key tiles plus four for what does not depend on
+  //     its length.  Rows are counted by rows[], where longer samples have none.
   int h, i, qt0, nqt_w = 0;
   int64_t row, row_end;
-  bool split = false;                           // key split between wave pairs (KS, N > 256)
+  const int32_t* rows = PERSIST ? p.cu_short : p.cu_seqlens;
   if constexpr (PERSIST) {
     const int x = blockIdx.x % kXcds, k = blockIdx.x / kXcds, per = (int)(gridDim.x / kXcds);
     h = k % p.H;
     const int m = k / p.H, M = (per - h + p.H - 1) / p.H;
-    const int64_t xa = p.total_rows * x / kXcds, xb = p.total_rows * (x + 1) / kXcds;
-    row = xa + (xb - xa) * m / M;
-    row_end = xa + (xb - xa) * (m + 1) / M;
+    const int64_t total = p.cu_cost[p.batch];
+    const int64_t xa = total * x / kXcds, xb = total * (x + 1) / kXcds;
+    // xa + (xb - xa) q / M, in 32 bits where they suffice (a 64-bit division costs about a microsecond)
+    auto slice = [&](int q) -> int64_t {
+      if (total < (int64_t(1) << 26)) return xa + (int64_t)((uint32_t)(xb - xa) * (uint32_t)q / (uint32_t)M);
+      return xa + (xb - xa) * q / M;
+    };
+    // first row whose cost starts at or past t, and its sample
+    auto row_at = [&](int64_t t, int& sample) -> int64_t {
+      int lo = 0, hi = p.batch;                 // cu_cost[lo] <= t, t < cu_cost[hi] (or hi = batch)
+      while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (p.cu_cost[mid] <= t) lo = mid;
+        else hi = mid;
+      }
+      const int nn = rows[lo + 1] - rows[lo], w = (nn + 15) / 16 + kAttnRowCost;
+      sample = lo;
+      return rows[lo] + min(nn, (int)(((uint32_t)(t - p.cu_cost[lo]) + (uint32_t)w - 1u) / (uint32_t)w));
+    };
+    row = row_at(slice(m), i);
+    int unused;
+    row_end = row_at(slice(m + 1), unused);
     if (row >= row_end) return;
-    int lo = 0, hi = p.batch;                   // cu_seqlens[lo] <= row < cu_seqlens[hi]
-    while (hi - lo > 1) {
-      const int mid = (lo + hi) >> 1;
-      if (p.cu_seqlens[mid] <= row) lo = mid;
-      else hi = mid;
-    }
-    i = __builtin_amdgcn_readfirstlane(lo);
+    while (rows[i + 1] <= row) ++i;
+    i = __builtin_amdgcn_readfirstlane(i);
     qt0 = 0;
   } else {
     const int x = blockIdx.x % kXcds, t = blockIdx.x / kXcds;
@@ -481,21 +479,12 @@ __global__ void __launch_bounds__(64 * NW, (NMAX <= 256 || KS) ? 4 : 2) attentio
     i = w4.x;
     if (i < 0) return;
     qt0 = w4.y;
-    const int nn = p.cu_seqlens[i + 1] - p.cu_seqlens[i];
-    const int r0 = w4.z * kAttnRG;
-    row = p.cu_seqlens[i] + r0;
-    row_end = p.axis == 3 ? row + 1 : p.cu_seqlens[i] + min(nn, r0 + kAttnRG);   // axis 3: one row per sample
+    row = p.cu_seqlens[i];
+    row_end = row + 1;
     nqt_w = w4.w;
-    if constexpr (KS) split = nn > 256;
   }
-  // query slot and key half of this wave (key split: waves w, w + 8 share slot w % 8)
-  const int qs = __builtin_amdgcn_readfirstlane(KS && split ? wave & 7 : wave);
-  const int kh = __builtin_amdgcn_readfirstlane(KS && split ? wave >> 3 : 0);
   const int j0 = qt0 * 16;
-  const int jw = j0 + 16 * qs + l16;            // this lane's query
-  // gate rows of this wave (gated key-split instance): 1 KB slots after the
-  // key/value buffers, past the hand-over when the keys are split
-  bf16* gslot = lds + 4 * NMAX * D + (split ? kAttnHandBytes / 2 : 0) + qs * 512;
+  const int jw = j0 + 16 * wave + l16;          // this lane's query
 
   // ---- per-row staging: straight global -> LDS copies ---------------------
   // Each wave copies its key tiles (wave, wave + NW, ...; 16 keys each) with
@@ -547,42 +536,29 @@ __global__ void __launch_bounds__(64 * NW, (NMAX <= 256 || KS) ? 4 : 2) attentio
   int n = 0;
   int64_t cu = 0, sr = 0, st = 0;               // cell(r, t) = cu + r*sr + t*st
   bool wave_has_queries = false, qvalid = false;
-  // keys of this wave: [16 kto, kend).  A split row is cut at half its
-  // length rounded up to 32 keys (at most 256 on either side), so both waves
-  // of a pair run about the same number of key tiles.
-  int kto = 0, kend = 0;
   // lane's bias: query 16*wave + l16, keys 16*kt + 4g .. +3 of every key
   // tile, read from the bias image (one contiguous 512 bytes per wave and tile)
-  uint2 bias_r[BT];
+  uint2 bias_r[KT16];
   auto set_sample = [&](int si, int sn, int64_t scu) {
     n = sn;
     cu = scu;
     sr = p.axis == 0 ? n : (p.axis == 1 ? 1 : 0);
     st = p.axis == 1 ? n : 1;
-    wave_has_queries = qs < (PERSIST ? (n + 15) / 16 : nqt_w) && j0 + 16 * qs < n;
+    wave_has_queries = wave < (PERSIST ? (n + 15) / 16 : nqt_w) && j0 + 16 * wave < n;
     qvalid = jw < n;
-    if (KS && split) {
-      const int cut = __builtin_amdgcn_readfirstlane(min(n, ((n + 1) / 2 + 31) & ~31));
-      kto = kh ? cut / 16 : 0;
-      kend = kh ? n : cut;
-    } else {
-      kto = 0;
-      kend = n;
-    }
     const int kti = ((n + 63) & ~63) / 16;
     const uint2* img = p.bias_img && wave_has_queries
-                           ? p.bias_img + h * p.img_head + ((int64_t)p.bias_tiles[si] + (int64_t)(qt0 + qs) * kti) * 64 + lane
+                           ? p.bias_img + h * p.img_head + ((int64_t)p.bias_tiles[si] + (int64_t)(qt0 + wave) * kti) * 64 + lane
                            : nullptr;
 #pragma unroll
-    for (int kt = 0; kt < BT; ++kt) {
-      const int kk = kto + kt;                  // key tile of this wave's half
-      bias_r[kt] = img && kk < kti ? img[kk * 64] : make_uint2(0u, 0u);
+    for (int kt = 0; kt < KT16; ++kt) {
+      bias_r[kt] = img && kt < kti ? img[kt * 64] : make_uint2(0u, 0u);
     }
   };
   // first cell of the sample: pair offset, or for axis 3 its first token
   set_sample(i, __builtin_amdgcn_readfirstlane(p.cu_seqlens[i + 1] - p.cu_seqlens[i]),
              p.axis == 3 ? p.cu_seqlens[i] : p.cu_pairs[i]);
-  int r = __builtin_amdgcn_readfirstlane((int)(row - p.cu_seqlens[i]));
+  int r = __builtin_amdgcn_readfirstlane((int)(row - rows[i]));
   bf16x8 qf = load_q(n, cu, r);
   dma_kv(n, cu, r, Kb0, Vb0);
   __builtin_amdgcn_s_waitcnt(0);                // this wave's copies have landed
@@ -601,9 +577,9 @@ __global__ void __launch_bounds__(64 * NW, (NMAX <= 256 || KS) ? 4 : 2) attentio
     int64_t cu2 = cu;
     if (more && r2 >= n) {
       i2 = i + 1;
-      while (p.cu_seqlens[i2 + 1] <= row + 1) ++i2;
+      while (rows[i2 + 1] <= row + 1) ++i2;
       r2 = 0;
-      n2 = p.cu_seqlens[i2 + 1] - p.cu_seqlens[i2];
+      n2 = rows[i2 + 1] - rows[i2];
       cu2 = p.axis == 3 ? p.cu_seqlens[i2] : p.cu_pairs[i2];
     }
     i2 = __builtin_amdgcn_readfirstlane(i2);
@@ -614,20 +590,9 @@ __global__ void __launch_bounds__(64 * NW, (NMAX <= 256 || KS) ? 4 : 2) attentio
     // gate of this lane's outputs (GATE): issued before the next row's
     // copies, so waiting for it leaves those in flight; the query index is
     // clamped into the row, so the load is unconditional
-    // (key-split instance: the wave's 16 gate rows are copied into its LDS
-    // slot, lane l taking dims 8 (l % 4) .. +7 of query l / 4; held in
-    // registers across the row they were spilled, and each reload waited for
-    // the copies in flight mid-row)
     uint2 gt[2];
-    if constexpr (GATE && KS) {
-      if (wave_has_queries && kh == 0) {
-        const int lq = opaque(lane);
-        const int jq = min(j0 + 16 * qs + (lq >> 2), n - 1);
-        const bf16* gr = gbase + (cu + (int64_t)r * sr + (int64_t)jq * st) * p.ld_gate + 8 * (lq & 3);
-        __builtin_amdgcn_global_load_lds((const void*)gr, (__attribute__((address_space(3))) void*)gslot, 16, 0, 0);
-      }
-    } else if constexpr (GATE) {
-      if (wave_has_queries && kh == 0) {
+    if constexpr (GATE) {
+      if (wave_has_queries) {
         const bf16* gr = gbase + (cu + (int64_t)r * sr + (int64_t)min(jw, n - 1) * st) * p.ld_gate + 4 * g;
         gt[0] = *reinterpret_cast<const uint2*>(gr);
         gt[1] = *reinterpret_cast<const uint2*>(gr + 16);
@@ -641,7 +606,7 @@ __global__ void __launch_bounds__(64 * NW, (NMAX <= 256 || KS) ? 4 : 2) attentio
     // keep the bias packed: converting it once outside the row loop would
     // double its registers
 #pragma unroll
-    for (int kt = 0; kt < BT; ++kt) asm volatile("" : "+v"(bias_r[kt].x), "+v"(bias_r[kt].y));
+    for (int kt = 0; kt < KT16; ++kt) asm volatile("" : "+v"(bias_r[kt].x), "+v"(bias_r[kt].y));
     float m_s = -INFINITY;                        // running max of bias/scale + q.k
     f32x4 O[3];                                   // dims 0-15, 16-31, row sum
 #pragma unroll
@@ -651,20 +616,17 @@ __global__ void __launch_bounds__(64 * NW, (NMAX <= 256 || KS) ? 4 : 2) attentio
       // 2, 4 or 6 tiles that hold keys: all score products of a super-chunk
       // are issued together, one maximum per query, then the exponentials
       // and the value products.  Tiles read stay below the staged length.
-      // first key tile of this wave's half (key split), uniform
-      const bf16* Kh = Kb + kto * 512;
-      const bf16* Vh = Vb + kto * 512;
       auto super_chunk = [&](auto sc_c, auto nt_c) {
         constexpr int SC = decltype(sc_c)::value, NT = decltype(nt_c)::value;
-        constexpr int T0 = SC * 8;                // first key tile (of this wave's half)
-        const int kc = kto * 16 + SC * 128;
+        constexpr int T0 = SC * 8;                // first key tile
+        const int kc = SC * 128;
         f32x4 S[NT];
 #pragma unroll
         for (int kt = 0; kt < NT; ++kt) {
           const uint2 bb = bias_r[T0 + kt];
           S[kt] = f32x4{__uint_as_float(bb.x << 16), __uint_as_float(bb.x & 0xffff0000u),
                         __uint_as_float(bb.y << 16), __uint_as_float(bb.y & 0xffff0000u)};
-          const bf16x8 kf = *reinterpret_cast<const bf16x8*>(&Kh[(T0 + kt) * 512 + lane * 8]);
+          const bf16x8 kf = *reinterpret_cast<const bf16x8*>(&Kb[(T0 + kt) * 512 + lane * 8]);
           S[kt] = mfma16(kf, qf, S[kt]);
           // at most four key fragments in flight (registers)
           if (kt % 4 == 3) __builtin_amdgcn_sched_barrier(0);
@@ -703,7 +665,7 @@ __global__ void __launch_bounds__(64 * NW, (NMAX <= 256 || KS) ? 4 : 2) attentio
 #pragma unroll
         for (int pp = 0; pp + 1 < NT / 2; pp += 2) {
           bf16x8 vf[4];
-          v_frags2(Vh, SC * 4 + pp, vf);
+          v_frags2(Vb, SC * 4 + pp, vf);
           O[0] = mfma16(vf[0], P[pp], O[0]);
           O[1] = mfma16(vf[1], P[pp], O[1]);
           O[2] = mfma16(ones, P[pp], O[2]);
@@ -713,7 +675,7 @@ __global__ void __launch_bounds__(64 * NW, (NMAX <= 256 || KS) ? 4 : 2) attentio
         }
         if constexpr ((NT / 2) % 2 == 1) {
           bf16x8 vf[2];
-          v_frags1(Vh, SC * 4 + NT / 2 - 1, vf);
+          v_frags1(Vb, SC * 4 + NT / 2 - 1, vf);
           O[0] = mfma16(vf[0], P[NT / 2 - 1], O[0]);
           O[1] = mfma16(vf[1], P[NT / 2 - 1], O[1]);
           O[2] = mfma16(ones, P[NT / 2 - 1], O[2]);
@@ -723,7 +685,7 @@ __global__ void __launch_bounds__(64 * NW, (NMAX <= 256 || KS) ? 4 : 2) attentio
       // staged length, a multiple of 64, then reaches 128 past kc)
       auto run_sc = [&](auto sc_c) {
         constexpr int SC = decltype(sc_c)::value;
-        const int rem = kend - kto * 16 - SC * 128;
+        const int rem = n - SC * 128;
         if (rem <= 0) return;
         if (rem > 96) super_chunk(sc_c, std::integral_constant<int, 8>{});
         else if (rem > 64) super_chunk(sc_c, std::integral_constant<int, 6>{});
@@ -732,54 +694,17 @@ __global__ void __launch_bounds__(64 * NW, (NMAX <= 256 || KS) ? 4 : 2) attentio
       };
       run_sc(std::integral_constant<int, 0>{});
       run_sc(std::integral_constant<int, 1>{});
-      if constexpr (NMAX > 256 && !KS) {
+      if constexpr (NMAX > 256) {
         run_sc(std::integral_constant<int, 2>{});
         run_sc(std::integral_constant<int, 3>{});
       }
     }
-    if constexpr (KS) {
-      if (split) {
-        // the upper key half hands (max, accumulators) to its partner, which
-        // merges the two partial softmax sums rescaled to the larger maximum
-        // [10][8 slots][64 lanes]: the maximum, dims 4g .. +3 and 16 + 4g .. +3,
-        // and the denominator (the ones product gives it in all four elements)
-        float* xf = reinterpret_cast<float*>(lds + 4 * NMAX * D);
-        if (kh == 1 && wave_has_queries) {
-          xf[(0 * 8 + qs) * 64 + lane] = m_s;
-#pragma unroll
-          for (int u = 0; u < 2; ++u)
-#pragma unroll
-            for (int ii = 0; ii < 4; ++ii) xf[((1 + 4 * u + ii) * 8 + qs) * 64 + lane] = O[u][ii];
-          xf[(9 * 8 + qs) * 64 + lane] = O[2][0];
-        }
-        __builtin_amdgcn_s_waitcnt(0xC07F);     // lgkmcnt(0): the hand-over is written (copies stay in flight)
-        __builtin_amdgcn_s_barrier();
-        if (kh == 0 && wave_has_queries) {
-          const float m1 = xf[(0 * 8 + qs) * 64 + lane];
-          const float mm = fmaxf(m_s, m1);
-          const float a0 = __builtin_amdgcn_exp2f((m_s - mm) * c), a1 = __builtin_amdgcn_exp2f((m1 - mm) * c);
-#pragma unroll
-          for (int u = 0; u < 2; ++u)
-#pragma unroll
-            for (int ii = 0; ii < 4; ++ii) O[u][ii] = O[u][ii] * a0 + xf[((1 + 4 * u + ii) * 8 + qs) * 64 + lane] * a1;
-          O[2][0] = O[2][0] * a0 + xf[(9 * 8 + qs) * 64 + lane] * a1;
-        }
-      }
-    }
-    if (wave_has_queries && kh == 0) {
+    if (wave_has_queries) {
       // lane (l16, g) holds dims 4g .. 4g+3 and 16 + 4g .. +3 of its query;
       // the rows g, g ^ 1 trade halves so that an even row holds dims
       // 4g .. 4g+7 and an odd one 16 + 4(g-1) .. +7: one 16-byte store per
       // lane instead of two 8-byte ones (each store instruction gathers 16
       // cells and holds the texture-address unit the copies also need)
-      if constexpr (GATE && KS) {
-        // the gate copy has landed (so have the next row's copies, which the
-        // row end waits for anyway); lane (l16, g): dims 4g .. +3, 16 + 4g .. +3
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        const bf16* gl = gslot + l16 * 32 + 4 * g;
-        gt[0] = *reinterpret_cast<const uint2*>(gl);
-        gt[1] = *reinterpret_cast<const uint2*>(gl + 16);
-      }
       const float inv = 1.f / O[2][0];
       uint32_t ow[2][2];
 #pragma unroll
@@ -828,7 +753,7 @@ __global__ void __launch_bounds__(64 * NW, (NMAX <= 256 || KS) ? 4 : 2) attentio
 
 // ---------------------------------------------------------------- pair attention, a workgroup per pair row
 // Pair attention for head_dim 32 (axes 0 and 1) and samples longer than
-// kAttnLongLen: a workgroup of W waves copies the keys and values of one pair
+// kAttnShortLen: a workgroup of W waves copies the keys and values of one pair
 // row of one head into LDS (128 bytes per key), and its waves take the row's
 // 16-query tiles in turn, all keys of the row per tile.  The copy is the only
 // barrier.  The bias of a tile is read in 64-key chunks from the bias image
@@ -1439,18 +1364,19 @@ hipError_t launch_attention(const nt_layout& L, int axis, int H, int D, const vo
     }
     return hipGetLastError();
   }
-  const int npad = (L.max_len + 63) & ~63;
-  if (axis == 2 && L.max_len <= kAttnLongLen)
-    return launch_seq_attention(L, L.d_cu_seqlens, L.max_len, H, D, q, ld_qkv, k, v, ld_qkv, scale, o, ld_o, s);
-  // Samples longer than kAttnLongLen go to the row kernel, which needs the
-  // bias image in the workspace and 32-bit lane offsets (16 rows of a tensor
-  // within 4 GB); without either the per-row kernel below takes the batch.
-  const bool longer = L.max_len > kAttnLongLen;
+  // Samples longer than kAttnShortLen go to the row kernel, the others to the
+  // persistent one.  The row kernel wants the bias image in the workspace and
+  // 32-bit lane offsets (16 rows of a tensor within 4 GB); without either the
+  // per-row kernel below takes the batch.  The line is where one workgroup of
+  // 16 waves stops covering a row's queries: splitting the keys of longer rows
+  // between wave pairs of a persistent instance took 412 us on the four-block
+  // stack (N 48..420), its rows past 256 on the row kernel 221 us and the rest
+  // on the persistent one 118 us; with the line at 320 or 400 the row kernel
+  // and that instance took 416 and 406 us together.
+  const bool longer = L.max_len > kAttnShortLen;
   const int64_t ld_max = std::max(std::max(ld_qkv, ld_o), gate ? ld_gate : 0);
-  const bool rows_ok = axis <= 1 && (!bias || workspace) && 32 * ld_max * L.max_len < (int64_t(1) << 32);
-  if (D == 32 && axis != 2 && (!longer || rows_ok)) {
-    if (!longer && L.pattn_items() == 0) return hipSuccess;
-    const int nmax = L.max_len <= kAttnShortLen ? kAttnShortLen : kAttnLongLen;
+  const bool rows_ok = (!bias || workspace) && 32 * ld_max * L.max_len < (int64_t(1) << 32);
+  if (D == 32 && (axis == 3 || (axis <= 1 && (!longer || rows_ok)))) {
     const int64_t tiles = L.bias_tiles_total();
     const uint2* img = nullptr;
     if (bias && tiles > 0) {
@@ -1460,16 +1386,18 @@ hipError_t launch_attention(const nt_layout& L, int axis, int H, int D, const vo
       img = (const uint2*)workspace;
     }
     PairAttnArgs a{axis, (const bf16*)q, (const bf16*)k, (const bf16*)v, ld_qkv, (const bf16*)bias, ld_bias,
-                   ld_bias_head, scale * kLog2e, (bf16*)o, ld_o, L.d_pattn_work, L.d_cu_seqlens, L.d_cu_pairs, H,
-                   img, tiles * 64, L.d_bias_tiles, L.batch, L.sum_n, (const bf16*)gate, ld_gate};
-    const size_t smem = sizeof(bf16) * 4 * (size_t)nmax * 32;
-    const dim3 grid((unsigned)(L.pattn_items() * H));
-    // the key-split instance also holds the hand-over of the upper key halves
-    const size_t smem_ks = sizeof(bf16) * 4 * (size_t)kAttnLongLen * 32 + kAttnHandBytes;
-    // gated: split rows add 8 gate slots past the hand-over, unsplit rows
-    // use 16 slots from its start
-    const size_t smem_ksg = sizeof(bf16) * 4 * (size_t)kAttnLongLen * 32 +
-                            std::max<size_t>(kAttnHandBytes + kAttnGateBytes / 2, kAttnGateBytes);
+                   ld_bias_head, scale * kLog2e, (bf16*)o, ld_o, L.d_sattn_work, L.d_cu_seqlens, L.d_cu_pairs, H,
+                   img, tiles * 64, L.d_bias_tiles, L.batch, L.d_cu_short,
+                   reinterpret_cast<const int64_t*>(L.d_cu_short_cost), (const bf16*)gate, ld_gate};
+    if (axis == 3) {
+      // single attention with pair bias: one row per sample, the 8-wave
+      // instance over the 1-D attention's (sample, 128-query block) items
+      if (L.sattn_items() == 0) return hipSuccess;
+      const size_t smem3 = sizeof(bf16) * 4 * (size_t)kAttnLongLen * 32;
+      hipFuncSetAttribute((const void*)attention_pair_kernel<kAttnLongLen, 8, false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem3);
+      attention_pair_kernel<kAttnLongLen, 8, false><<<dim3((unsigned)(L.sattn_items() * H)), dim3(512), smem3, s>>>(a);
+      return hipGetLastError();
+    }
     if (longer) {
       PairAttnArgs al = a;
       al.work = L.d_lattn_work;
@@ -1477,41 +1405,26 @@ hipError_t launch_attention(const nt_layout& L, int axis, int H, int D, const vo
       // 8 waves where two workgroups share a CU's 160 KB of LDS, else 16: four waves per SIMD either way
       const hipError_t e = keys <= 640 ? launch_attention_rows<8>(al, L.lattn_items(), keys, s)
                                        : launch_attention_rows<16>(al, L.lattn_items(), keys, s);
-      if (e != hipSuccess || L.pattn_items() == 0) return e;
+      if (e != hipSuccess) return e;
     }
+    if (L.short_rows() == 0) return hipSuccess;
+    // persistent: one workgroup of 16 waves per CU (all queries of a row); per
+    // XCD a multiple of H workgroups, at least H, so every head gets an equal
+    // share of each XCD's rows
+    const size_t smem = sizeof(bf16) * 4 * (size_t)kAttnShortLen * 32;
+    const dim3 gridp((unsigned)(std::max(H, compute_units() / kXcds / H * H) * kXcds));
     if (gate) {
-      // gated output (axes 0 and 1): the GATE instances of the same kernels
-      if (nmax == kAttnShortLen) {
-        const int per_xcd = std::max(H, compute_units() / kXcds / H * H);
-        const dim3 gridp((unsigned)(per_xcd * kXcds));
-        hipFuncSetAttribute((const void*)attention_pair_kernel<kAttnShortLen, 16, true, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-        attention_pair_kernel<kAttnShortLen, 16, true, true><<<gridp, dim3(1024), smem, s>>>(a);
-      } else {
-        hipFuncSetAttribute((const void*)attention_pair_kernel<kAttnLongLen, 16, false, true, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem_ksg);
-        attention_pair_kernel<kAttnLongLen, 16, false, true, true><<<grid, dim3(1024), smem_ksg, s>>>(a);
-      }
-    } else if (axis == 3) {
-      // single attention with pair bias: one row per sample, the 8-wave
-      // instance over the 1-D attention's (sample, 128-query block) items
-      if (L.sattn_items() == 0) return hipSuccess;
-      a.work = L.d_sattn_work;
-      const size_t smem3 = sizeof(bf16) * 4 * (size_t)kAttnLongLen * 32;
-      hipFuncSetAttribute((const void*)attention_pair_kernel<kAttnLongLen, 8, false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem3);
-      attention_pair_kernel<kAttnLongLen, 8, false><<<dim3((unsigned)(L.sattn_items() * H)), dim3(512), smem3, s>>>(a);
-    } else if (nmax == kAttnShortLen) {
-      // persistent: one workgroup of 16 waves per CU (all queries of a row);
-      // per XCD a multiple of H workgroups, at least H, so every head gets an
-      // equal share of each XCD's rows
-      const int per_xcd = std::max(H, compute_units() / kXcds / H * H);
-      const dim3 gridp((unsigned)(per_xcd * kXcds));
+      hipFuncSetAttribute((const void*)attention_pair_kernel<kAttnShortLen, 16, true, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+      attention_pair_kernel<kAttnShortLen, 16, true, true><<<gridp, dim3(1024), smem, s>>>(a);
+    } else {
       hipFuncSetAttribute((const void*)attention_pair_kernel<kAttnShortLen, 16, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
       attention_pair_kernel<kAttnShortLen, 16, true><<<gridp, dim3(1024), smem, s>>>(a);
-    } else {
-      hipFuncSetAttribute((const void*)attention_pair_kernel<kAttnLongLen, 16, false, false, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem_ks);
-      attention_pair_kernel<kAttnLongLen, 16, false, false, true><<<grid, dim3(1024), smem_ks, s>>>(a);
     }
     return hipGetLastError();
   }
+  const int npad = (L.max_len + 63) & ~63;
+  if (axis == 2 && L.max_len <= kAttnLongLen)
+    return launch_seq_attention(L, L.d_cu_seqlens, L.max_len, H, D, q, ld_qkv, k, v, ld_qkv, scale, o, ld_o, s);
   const int vstride = (npad + 127) / 128 * 128 + 4;
   AttnArgs a{axis, H, (const bf16*)q, (const bf16*)k, (const bf16*)v, ld_qkv, (const bf16*)bias, ld_bias,
              ld_bias_head, scale * kLog2e, (bf16*)o, ld_o, work, L.d_cu_seqlens, L.d_cu_pairs, vstride,

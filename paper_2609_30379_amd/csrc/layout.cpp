@@ -5,6 +5,7 @@
 #include <algorithm>
 #include <array>
 #include <climits>
+#include <cstring>
 #include <numeric>
 
 #include "nt_internal.h"
@@ -190,7 +191,7 @@ nt_status plan_layout(const int32_t* lengths, int32_t batch, nt_layout* L, const
   for (int32_t i = 0; i < batch; ++i) L->cu_qblk[i + 1] = L->cu_qblk[i] + (lengths[i] + 15) / 16;
 
   // pair-row attention: one item per (sample, pair row), cost N_i^2; and the
-  // same for the samples longer than kAttnLongLen alone
+  // same for the samples longer than kAttnShortLen alone
   auto pair_row_items = [&](int32_t longer_than) {
     std::vector<std::array<int32_t, 2>> items;
     std::vector<double> cost;
@@ -203,35 +204,20 @@ nt_status plan_layout(const int32_t* lengths, int32_t batch, nt_layout* L, const
     return xcd_order<2>(items, cost);
   };
   L->attn_work = pair_row_items(0);
-  L->lattn_work = pair_row_items(kAttnLongLen);
-  // pair attention: a sample's 16-query tiles are split evenly over
-  // ceil(tiles / W) blocks of at most W tiles (items: sample, first tile, row
-  // group, tile count), so no block leaves most of its waves idle; generation
-  // order is kept in each XCD's queue so the blocks of a row group stay
-  // adjacent and share keys and values.  For the 16-wave key-split instance
-  // (N <= 512) W is 16 for samples up to 256 long (a wave per query tile) and
-  // 8 for longer ones (a wave pair per query tile); the N <= 256 persistent
-  // instance needs no list (its workgroups find their rows from the prefix
-  // sums).  Samples longer than kAttnLongLen have no items here.
-  auto pair_attn_items = [&](auto W_of) {
-    std::vector<std::array<int32_t, 4>> items;
-    std::vector<double> cost;
-    for (int32_t i = 0; i < batch; ++i) {
-      const int32_t n = lengths[i], tiles = (n + 15) / 16, W = W_of(n);
-      if (n > kAttnLongLen) continue;               // their rows are in lattn_work
-      const int32_t blocks = (tiles + W - 1) / W;
-      for (int32_t rg = 0; rg * kAttnRG < n; ++rg)
-        for (int32_t b = 0; b < blocks; ++b) {
-          const int32_t t0 = b * tiles / blocks, t1 = (b + 1) * tiles / blocks;
-          items.push_back({i, t0, rg, t1 - t0});
-          cost.push_back((double)std::min(kAttnRG, n - rg * kAttnRG) * std::min(16 * (t1 - t0), n - 16 * t0) * n);
-        }
-    }
-    return xcd_order<4>(items, cost, false);
-  };
-  L->pattn_work = pair_attn_items([](int32_t n) { return n <= kAttnShortLen ? 16 : 8; });
-  // 1-D attention: the same even split of a sample's 16-query tiles over
-  // blocks of at most kAttnQB queries, one item per block
+  L->lattn_work = pair_row_items(kAttnShortLen);
+  // pair rows of the samples up to kAttnShortLen, in packed order (the
+  // persistent pair attention walks them; longer samples are in lattn_work)
+  L->cu_short.assign(batch + 1, 0);
+  std::vector<int64_t> cost(batch + 1, 0);
+  for (int32_t i = 0; i < batch; ++i) {
+    const int32_t n = lengths[i] <= kAttnShortLen ? lengths[i] : 0;
+    L->cu_short[i + 1] = L->cu_short[i] + n;
+    cost[i + 1] = cost[i] + (int64_t)n * ((n + 15) / 16 + kAttnRowCost);
+  }
+  L->cu_short_cost.assign(2 * (size_t)(batch + 1), 0);
+  std::memcpy(L->cu_short_cost.data(), cost.data(), cost.size() * sizeof(int64_t));
+  // 1-D attention: a sample's 16-query tiles are split evenly over blocks of
+  // at most kAttnQB queries, one item per block
   {
     std::vector<std::array<int32_t, 4>> items;
     std::vector<double> cost;

@@ -17,9 +17,9 @@ constexpr int kTriTile = 64;      // triangle output tile: 64 x 64 cells
 constexpr int kSeqQBlock = 64;    // 1-D attention: queries per workgroup
 constexpr int kLinRows = 128;     // rows per projection workgroup (pair-row table granularity)
 constexpr int kAttnQB = 128;      // pair attention (head_dim 32): queries per workgroup (8 waves x 16)
-constexpr int kAttnRG = 16;       // pair attention (head_dim 32): pair rows per workgroup
-constexpr int kAttnShortLen = 256;  // its instance with two workgroups per CU: longest sample
-constexpr int kAttnLongLen = 512;   // its instance with one workgroup per CU: longest sample
+constexpr int kAttnShortLen = 256;  // longest sample of the persistent pair attention and of the 256-key 1-D kernel
+constexpr int kAttnRowCost = 4;     // persistent pair attention: cost of a row besides its 16-key tiles, in tiles
+constexpr int kAttnLongLen = 512;   // longest sample of the 512-key instances (axes 2 and 3, cross-attention)
 
 // Samples whose tables the pair-tiled projection kernels cache in LDS.
 constexpr int kPairTiledMaxSamples = 1024;
@@ -50,12 +50,13 @@ struct nt_layout {
   std::vector<int32_t> row_splits2;  // [sum N + 1]
   std::vector<int32_t> row_sample;   // [sum N]
   std::vector<int32_t> attn_work;    // pairs (sample, row); count multiple of 8; (-1,-1) = idle
-  std::vector<int32_t> lattn_work;   // as attn_work, samples longer than kAttnLongLen only
+  std::vector<int32_t> lattn_work;   // as attn_work, samples longer than kAttnShortLen only
   std::vector<int32_t> tri_work;     // quads (sample, xt, yt, first item of the sample); count multiple of 8
   std::vector<int32_t> tri_split;    // [9] cost-balanced item ranges of the 8 XCDs
   int32_t tri_xcd_items = 0;         // largest item count of one XCD
   std::vector<int32_t> seq_work;     // pairs (sample, query block); count multiple of 8
-  std::vector<int32_t> pattn_work;  // quads (sample, first 16-query tile, row group, tile count)
+  std::vector<int32_t> cu_short;     // [B+1] prefix of N_i over the samples up to kAttnShortLen (0 for longer ones)
+  std::vector<int32_t> cu_short_cost;  // [B+1] int64 prefix of their rows' cost, N_i (ceil(N_i/16) + kAttnRowCost)
   std::vector<int32_t> bias_tiles;   // [B+1] prefix of ceil(N_i/16) * round_up(N_i,64)/16: bias image tiles
   std::vector<int32_t> sattn_work;   // 1-D attention: quads (sample, first 16-query tile, 0, tile count)
   std::vector<int32_t> blk_prow;     // [ceil(sum N^2 / kLinRows)] pair row holding cell kLinRows*b
@@ -75,7 +76,8 @@ struct nt_layout {
   const int32_t* d_lattn_work = nullptr;
   const int32_t* d_tri_work = nullptr;
   const int32_t* d_seq_work = nullptr;
-  const int32_t* d_pattn_work = nullptr;
+  const int32_t* d_cu_short = nullptr;
+  const int32_t* d_cu_short_cost = nullptr;
   const int32_t* d_blk_prow = nullptr;
   const int32_t* d_bias_tiles = nullptr;
   const int32_t* d_sattn_work = nullptr;
@@ -89,7 +91,7 @@ struct nt_layout {
   int64_t lattn_items() const { return (int64_t)lattn_work.size() / 2; }
   int64_t tri_items() const { return (int64_t)tri_work.size() / 4; }
   int64_t seq_items() const { return (int64_t)seq_work.size() / 2; }
-  int64_t pattn_items() const { return (int64_t)pattn_work.size() / 4; }
+  int64_t short_rows() const { return cu_short.empty() ? 0 : cu_short.back(); }
   int64_t sattn_items() const { return (int64_t)sattn_work.size() / 4; }
   int64_t bias_tiles_total() const { return bias_tiles.empty() ? 0 : bias_tiles.back(); }
 };
