@@ -80,7 +80,6 @@ __device__ __forceinline__ int32_t pair_tiled_pos(const LinArgs& p, int m) {
   return tiled_cell_pos(p.cu_pad[i], n, lo - p.cu_seqlens[i], m - p.row_splits2[lo], p.tail_mode == kTailPairTiledT);
 }
 
-__device__ __forceinline__ float gelu_erf(float v) { return 0.5f * v * (1.f + erff(v * 0.70710678118654752f)); }
 
 // Raw (unnormalised) global data of one k-step, held in registers while the
 // previous step computes.
@@ -273,7 +272,7 @@ __global__ void __launch_bounds__(256) linear_mfma_kernel(LinArgs p) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         r[i] = acc[a][b][i] + ((p.bias && n + i < p.N) ? p.bias[n + i] : 0.f);
-        if constexpr (EPI == NT_EPI_GELU) r[i] = gelu_erf(r[i]);
+        if constexpr (EPI == NT_EPI_GELU) r[i] = gelu(r[i]);
       }
       if (n + 4 <= p.n_main) {
         if constexpr (EPI == NT_EPI_GATED_RESIDUAL) {
@@ -478,7 +477,7 @@ __global__ void __launch_bounds__(256) linear_res_kernel(LinArgs p) {
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
             rr[i] = acc[a][b][i] + ((p.bias && n + i < p.N) ? p.bias[n + i] : 0.f);
-            if constexpr (EPI == NT_EPI_GELU) rr[i] = gelu_erf(rr[i]);
+            if constexpr (EPI == NT_EPI_GELU) rr[i] = gelu(rr[i]);
           }
           if (n + 4 <= p.n_main) {
             if constexpr (EPI == NT_EPI_RESIDUAL) {
@@ -583,7 +582,7 @@ __global__ void __launch_bounds__(64 * kSmallWaves) linear_small_kernel(LinArgs 
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     r[i] = r4[i] + ((p.bias && n + i < p.N) ? p.bias[n + i] : 0.f);
-    if constexpr (EPI == NT_EPI_GELU) r[i] = gelu_erf(r[i]);
+    if constexpr (EPI == NT_EPI_GELU) r[i] = gelu(r[i]);
   }
   if (n + 4 <= p.N) {
     if constexpr (EPI == NT_EPI_RESIDUAL) {
@@ -807,7 +806,7 @@ __global__ void __launch_bounds__(kStreamThreads, 2) linear_stream_kernel(LinArg
         float r[4] = {acc[j][0] + bq.x, acc[j][1] + bq.y, acc[j][2] + bq.z, acc[j][3] + bq.w};
         if constexpr (EPI == NT_EPI_GELU) {
 #pragma unroll
-          for (int ii = 0; ii < 4; ++ii) r[ii] = gelu_erf(r[ii]);
+          for (int ii = 0; ii < 4; ++ii) r[ii] = gelu(r[ii]);
         }
         if (stage && n + 4 <= p.n_main) {
           if constexpr (RES) *reinterpret_cast<float4*>(&ysf(i & 1)[rl * NS + n]) = make_float4(r[0], r[1], r[2], r[3]);
@@ -1131,7 +1130,7 @@ __global__ void __launch_bounds__(kWaveThreads, 1) linear_wave_kernel(LinArgs p)
         float r[4] = {acc[j][0], acc[j][1], acc[j][2], acc[j][3]};
         if constexpr (EPI == NT_EPI_GELU) {
 #pragma unroll
-          for (int ii = 0; ii < 4; ++ii) r[ii] = gelu_erf(r[ii]);
+          for (int ii = 0; ii < 4; ++ii) r[ii] = gelu(r[ii]);
         }
         if constexpr (RES) *reinterpret_cast<float4*>(stage + (size_t)(l16 * SS + j * 16 + 4 * g) * 4) = make_float4(r[0], r[1], r[2], r[3]);
         else {
@@ -1192,7 +1191,7 @@ __global__ void __launch_bounds__(kWaveThreads, 1) linear_wave_kernel(LinArgs p)
         for (int ii = 0; ii < 4; ++ii) {
           const int nn = ct * 16 + 4 * g + ii;
           float r = acc[ii];
-          if constexpr (EPI == NT_EPI_GELU) r = gelu_erf(r);
+          if constexpr (EPI == NT_EPI_GELU) r = gelu(r);
           if (nn >= p.n_main && nn < p.N) p.y_tail[(int64_t)(nn - p.n_main) * p.ld_tail + m] = (bf16)r;
         }
       }
@@ -1923,7 +1922,13 @@ hipError_t launch_linear(const LinearPlan& plan, hipStream_t s) {
   }
 
   const bool tiled = p.y_tail && p.tail_mode != kTailChannelMajor;
-  if (!a.ln_gamma && a.n_tail == 0 && a.c_in % 32 == 0 && rows <= kSmallRows) {
+  // Few rows without a LayerNorm.  Its 16 x 64 blocks read every operand once
+  // per block, so past one block per CU the tiled product is faster where it
+  // applies (K = 768, N = 768: 230 rows 6.3 us here and 8.0 there, 460 rows 9.5
+  // and 8.2, 1019 rows 12.9 and 8.2; K = N = 384: 460 rows 4.3 and 5.4, 1019
+  // rows 5.9 and 5.4).
+  const int64_t small_blocks = (int64_t)((rows + 15) / 16) * ((a.c_out + 63) / 64);
+  if (!a.ln_gamma && a.n_tail == 0 && a.c_in % 32 == 0 && rows <= kSmallRows && !(uses_gemm(a) && small_blocks > compute_units())) {
     const dim3 g1((unsigned)((rows + 15) / 16), (unsigned)((a.c_out + 63) / 64)), b1(64 * kSmallWaves);
 #define NT_SM(XT, EPI) linear_small_kernel<XT, EPI><<<g1, b1, 0, s>>>(p)
 #define NT_SM_X(EPI) do { if (xf) NT_SM(float, EPI); else NT_SM(bf16, EPI); } while (0)
