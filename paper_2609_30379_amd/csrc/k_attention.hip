@@ -231,8 +231,8 @@ struct PairAttnArgs {
 // hold -inf (for queries inside N), so the scores they seed are masked
 // without further work; queries past N hold 0.
 // bias(j, k) is the head-h bias of cell(j, k) for axis 0 and of cell(k, j)
-// for axis 1, read at cell * ld_bias + h * ld_bias_head.  One wave per tile,
-// the sample found by bisection.
+// for axis 1, read at cell * ld_bias + h * ld_bias_head; the sample is found by
+// bisection.
 struct BiasImgArgs {
   int axis, batch;
   const bf16* bias;
@@ -245,8 +245,12 @@ struct BiasImgArgs {
   const int32_t* cu_pairs;
 };
 
+// One wave per four key tiles of a query tile (the tile count of a sample is a
+// multiple of four).  Where the keys of a query are adjacent (axes 0 and 3, unit
+// cell stride) a lane reads its four values at once, at whatever 2-byte
+// boundary they start: 12 heads of N 32..512, B = 8 took 27 us value by value.
 __global__ void __launch_bounds__(256) bias_image_kernel(BiasImgArgs p) {
-  const int64_t tile = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int64_t tile = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * 4;
   if (tile >= p.tiles) return;
   const int h = blockIdx.y, lane = threadIdx.x & 63, l16 = lane & 15, g = lane >> 4;
   int lo = 0, hi = p.batch - 1;                 // sample: largest i with bias_tiles[i] <= tile
@@ -254,21 +258,39 @@ __global__ void __launch_bounds__(256) bias_image_kernel(BiasImgArgs p) {
     const int mid = (lo + hi + 1) >> 1;
     if (p.bias_tiles[mid] <= tile) lo = mid; else hi = mid - 1;
   }
-  const int i = lo;
+  const int i = __builtin_amdgcn_readfirstlane(lo);
   const int n = p.cu_seqlens[i + 1] - p.cu_seqlens[i];
   const int kti = ((n + 63) >> 6) * 4;
   const int t = (int)(tile - p.bias_tiles[i]);
-  const int j = (t / kti) * 16 + l16, k0 = (t % kti) * 16 + 4 * g;
+  const int j = (t / kti) * 16 + l16, kt0 = (t % kti) * 16 + 4 * g;
   const bf16* bh = p.bias + (int64_t)h * p.ld_bias_head + (int64_t)p.cu_pairs[i] * p.ld_bias;
-  bf16x4 o;
+  const bool adjacent = p.axis != 1 && p.ld_bias == 1;
+  bf16x4 raw[4];
 #pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const int k = k0 + e;
-    float b = j < n ? -INFINITY : 0.f;
-    if (j < n && k < n) b = (float)bh[(p.axis != 1 ? (int64_t)j * n + k : (int64_t)k * n + j) * p.ld_bias] * p.inv_scale;
-    o[e] = (bf16)b;
+  for (int u = 0; u < 4; ++u) {
+    const int k0 = kt0 + 16 * u;
+    raw[u] = bf16x4{};
+    if (adjacent && j < n && k0 + 4 <= n) {
+      __builtin_memcpy(&raw[u], bh + (int64_t)j * n + k0, 8);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int k = k0 + e;
+        if (j < n && k < n) raw[u][e] = bh[(p.axis != 1 ? (int64_t)j * n + k : (int64_t)k * n + j) * p.ld_bias];
+      }
+    }
   }
-  *reinterpret_cast<bf16x4*>(&p.img[(int64_t)h * p.tiles * 64 + tile * 64 + lane]) = o;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    bf16x4 o;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      float b = j < n ? -INFINITY : 0.f;
+      if (j < n && kt0 + 16 * u + e < n) b = (float)raw[u][e] * p.inv_scale;
+      o[e] = (bf16)b;
+    }
+    *reinterpret_cast<bf16x4*>(&p.img[(int64_t)h * p.tiles * 64 + (tile + u) * 64 + lane]) = o;
+  }
 }
 
 // ---------------------------------------------------------------- shared pieces
@@ -388,9 +410,12 @@ __device__ __forceinline__ float query_max(float v) {
 }
 
 // ---------------------------------------------------------------- pair attention, head_dim 32
-// Pair attention for head_dim 32 and N_i <= kAttnLongLen, organised so that
-// the exponentials are nearly the only vector work.  A workgroup of NW waves
-// runs a stretch of pair rows of one head, a block of up to 16 NW queries:
+// Pair attention for head_dim 32 and the samples up to kAttnShortLen, organised
+// so that the exponentials are nearly the only vector work.  Persistent: one
+// workgroup of 16 waves per CU (all queries of a row, so a row's keys and values
+// are copied once per CU; 64 KB of LDS, four waves per SIMD) runs a stretch of
+// pair rows of one head, an equal share of the rows' cost; longer samples are
+// skipped, their rows are attention_row_kernel's.
 //   * the bias of (query, key) does not depend on the pair row, so each lane
 //     keeps the bias of its query for its 4-key groups of every key tile in
 //     registers while the rows belong to one sample -- read from the bias
@@ -405,19 +430,11 @@ __device__ __forceinline__ float query_max(float v) {
 //     ones operand, on the same bf16 probabilities as the numerator.
 // Scores are kept transposed (S^T = K Q^T), so a lane holds 16 keys of one
 // query per 64-key chunk and the running max is mostly lane-local.
-// Instances:
-//   * N <= 256, persistent, with 16 waves (all queries of a row in one
-//     workgroup, so a row's keys and values are copied once per CU; 64 KB of
-//     LDS, four waves per SIMD, one workgroup per CU with an equal share of
-//     the rows' cost; samples longer than 256 are skipped, their rows are
-//     attention_row_kernel's);
-//   * N <= 512, 8 waves, each wave all keys (the single attention of axis 3,
-//     one row per sample).
-template <int NMAX, int NW, bool PERSIST, bool GATE = false>
-__global__ void __launch_bounds__(64 * NW, NMAX <= 256 ? 4 : 2) attention_pair_kernel(PairAttnArgs p) {
+template <int NMAX, int NW, bool GATE>
+__global__ void __launch_bounds__(64 * NW, 4) attention_pair_kernel(PairAttnArgs p) {
   constexpr int D = 32;
   constexpr int KT16 = NMAX / 16;               // key tiles
-  static_assert(!PERSIST || NW * 16 >= NMAX, "the persistent instance covers all queries of a row");
+  static_assert(NW * 16 >= NMAX && NMAX <= 256, "a workgroup covers all queries of a row");
   extern __shared__ __attribute__((aligned(16))) bf16 lds[];
   bf16* Kb0 = lds;                                         // key images: tile of 16 keys -> 512 elements
   bf16* Kb1 = Kb0 + NMAX * D;
@@ -426,65 +443,43 @@ __global__ void __launch_bounds__(64 * NW, NMAX <= 256 ? 4 : 2) attention_pair_k
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, g = lane >> 4;
 
-  // ---- rows of this workgroup: packed rows [row, row_end) of one head, a
-  // query block starting at tile qt0.
-  //   * work-list instance (axis 3): workgroup 8 (H k + h) + x runs on XCD x
-  //     and takes work position pos = 8 k + x, head h: the H heads of a
-  //     position are consecutive workgroups of one XCD; one row per sample.
-  //   * persistent instance (one workgroup per CU): XCD x takes the x-th
-  //     eighth of the cost of all short samples' rows, and its workgroups
-  //     split that range among the heads, workgroup k taking head k % H and
-  //     the (k / H)-th of the equal slices of that head (crossing sample
-  //     boundaries), so the heads of a row still run on one XCD together.
-  //     A row costs its 16-key tiles plus four for what does not depend on
-  //     its length.  Rows are counted by rows[], where longer samples have none.
-  int h, i, qt0, nqt_w = 0;
-  int64_t row, row_end;
-  const int32_t* rows = PERSIST ? p.cu_short : p.cu_seqlens;
-  if constexpr (PERSIST) {
-    const int x = blockIdx.x % kXcds, k = blockIdx.x / kXcds, per = (int)(gridDim.x / kXcds);
-    h = k % p.H;
-    const int m = k / p.H, M = (per - h + p.H - 1) / p.H;
-    const int64_t total = p.cu_cost[p.batch];
-    const int64_t xa = total * x / kXcds, xb = total * (x + 1) / kXcds;
-    // xa + (xb - xa) q / M, in 32 bits where they suffice (a 64-bit division costs about a microsecond)
-    auto slice = [&](int q) -> int64_t {
-      if (total < (int64_t(1) << 26)) return xa + (int64_t)((uint32_t)(xb - xa) * (uint32_t)q / (uint32_t)M);
-      return xa + (xb - xa) * q / M;
-    };
-    // first row whose cost starts at or past t, and its sample
-    auto row_at = [&](int64_t t, int& sample) -> int64_t {
-      int lo = 0, hi = p.batch;                 // cu_cost[lo] <= t, t < cu_cost[hi] (or hi = batch)
-      while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (p.cu_cost[mid] <= t) lo = mid;
-        else hi = mid;
-      }
-      const int nn = rows[lo + 1] - rows[lo], w = (nn + 15) / 16 + kAttnRowCost;
-      sample = lo;
-      return rows[lo] + min(nn, (int)(((uint32_t)(t - p.cu_cost[lo]) + (uint32_t)w - 1u) / (uint32_t)w));
-    };
-    row = row_at(slice(m), i);
-    int unused;
-    row_end = row_at(slice(m + 1), unused);
-    if (row >= row_end) return;
-    while (rows[i + 1] <= row) ++i;
-    i = __builtin_amdgcn_readfirstlane(i);
-    qt0 = 0;
-  } else {
-    const int x = blockIdx.x % kXcds, t = blockIdx.x / kXcds;
-    h = t % p.H;
-    const int pos = (t / p.H) * kXcds + x;
-    const int4 w4 = reinterpret_cast<const int4*>(p.work)[pos];
-    i = w4.x;
-    if (i < 0) return;
-    qt0 = w4.y;
-    row = p.cu_seqlens[i];
-    row_end = row + 1;
-    nqt_w = w4.w;
-  }
-  const int j0 = qt0 * 16;
-  const int jw = j0 + 16 * wave + l16;          // this lane's query
+  // ---- rows of this workgroup, [row, row_end) of one head (one workgroup per
+  // CU): XCD x takes the x-th eighth of the cost of all short samples' rows, and
+  // its workgroups split that range among the heads, workgroup k taking head
+  // k % H and the (k / H)-th of the equal slices of that head (crossing sample
+  // boundaries), so the heads of a row run on one XCD together.  A row costs
+  // its 16-key tiles plus kAttnRowCost for what does not depend on its length.
+  // Rows are counted by rows[], where longer samples have none.
+  const int32_t* rows = p.cu_short;
+  const int x = blockIdx.x % kXcds, k = blockIdx.x / kXcds, per = (int)(gridDim.x / kXcds);
+  const int h = __builtin_amdgcn_readfirstlane(k % p.H), m = __builtin_amdgcn_readfirstlane(k / p.H);
+  const int M = (per - h + p.H - 1) / p.H;
+  const int64_t total = p.cu_cost[p.batch];
+  const int64_t xa = total * x / kXcds, xb = total * (x + 1) / kXcds;
+  // xa + (xb - xa) q / M, in 32 bits where they suffice (a 64-bit division costs about a microsecond)
+  auto slice = [&](int q) -> int64_t {
+    if (total < (int64_t(1) << 26)) return xa + (int64_t)((uint32_t)(xb - xa) * (uint32_t)q / (uint32_t)M);
+    return xa + (xb - xa) * q / M;
+  };
+  // first row whose cost starts at or past t, and its sample
+  auto row_at = [&](int64_t t, int& sample) -> int64_t {
+    int lo = 0, hi = p.batch;                   // cu_cost[lo] <= t, t < cu_cost[hi] (or hi = batch)
+    while (hi - lo > 1) {
+      const int mid = (lo + hi) >> 1;
+      if (p.cu_cost[mid] <= t) lo = mid;
+      else hi = mid;
+    }
+    const int nn = rows[lo + 1] - rows[lo], w = (nn + 15) / 16 + kAttnRowCost;
+    sample = lo;
+    return rows[lo] + min(nn, (int)(((uint32_t)(t - p.cu_cost[lo]) + (uint32_t)w - 1u) / (uint32_t)w));
+  };
+  int i, unused;
+  int64_t row = row_at(slice(m), i);
+  const int64_t row_end = row_at(slice(m + 1), unused);
+  if (row >= row_end) return;
+  while (rows[i + 1] <= row) ++i;
+  i = __builtin_amdgcn_readfirstlane(i);
+  const int jw = 16 * wave + l16;               // this lane's query
 
   // ---- per-row staging: straight global -> LDS copies ---------------------
   // Each wave copies its key tiles (wave, wave + NW, ...; 16 keys each) with
@@ -504,7 +499,7 @@ __global__ void __launch_bounds__(64 * NW, NMAX <= 256 ? 4 : 2) attention_pair_k
   const bf16* gbase = GATE ? p.gate + hD : nullptr;
   auto dma_kv = [&](int sn, int64_t scu, int r, bf16* Kb, bf16* Vr) {
     const int snpad = (sn + 63) & ~63;
-    const int64_t ssr = p.axis == 0 ? sn : (p.axis == 1 ? 1 : 0), sst = p.axis == 1 ? sn : 1;
+    const int64_t ssr = p.axis == 0 ? sn : 1, sst = p.axis == 1 ? sn : 1;
     const int ln = opaque(lane);
 #pragma unroll
     for (int kt = wave; kt < KT16; kt += NW) {
@@ -525,7 +520,7 @@ __global__ void __launch_bounds__(64 * NW, NMAX <= 256 ? 4 : 2) attention_pair_k
   // pair offset scu (zero past N)
   auto load_q = [&](int sn, int64_t scu, int r) -> bf16x8 {
     if (jw >= sn) return bf16x8{};
-    const int64_t ssr = p.axis == 0 ? sn : (p.axis == 1 ? 1 : 0), sst = p.axis == 1 ? sn : 1;
+    const int64_t ssr = p.axis == 0 ? sn : 1, sst = p.axis == 1 ? sn : 1;
     return *reinterpret_cast<const bf16x8*>(qbase + (scu + (int64_t)r * ssr + (int64_t)jw * sst) * p.ld_qkv + g * 8);
   };
   const VtLane vl = vt_lane(l16, g);
@@ -542,22 +537,21 @@ __global__ void __launch_bounds__(64 * NW, NMAX <= 256 ? 4 : 2) attention_pair_k
   auto set_sample = [&](int si, int sn, int64_t scu) {
     n = sn;
     cu = scu;
-    sr = p.axis == 0 ? n : (p.axis == 1 ? 1 : 0);
+    sr = p.axis == 0 ? n : 1;
     st = p.axis == 1 ? n : 1;
-    wave_has_queries = wave < (PERSIST ? (n + 15) / 16 : nqt_w) && j0 + 16 * wave < n;
+    wave_has_queries = 16 * wave < n;
     qvalid = jw < n;
     const int kti = ((n + 63) & ~63) / 16;
     const uint2* img = p.bias_img && wave_has_queries
-                           ? p.bias_img + h * p.img_head + ((int64_t)p.bias_tiles[si] + (int64_t)(qt0 + wave) * kti) * 64 + lane
+                           ? p.bias_img + h * p.img_head + ((int64_t)p.bias_tiles[si] + (int64_t)wave * kti) * 64 + lane
                            : nullptr;
 #pragma unroll
     for (int kt = 0; kt < KT16; ++kt) {
       bias_r[kt] = img && kt < kti ? img[kt * 64] : make_uint2(0u, 0u);
     }
   };
-  // first cell of the sample: pair offset, or for axis 3 its first token
   set_sample(i, __builtin_amdgcn_readfirstlane(p.cu_seqlens[i + 1] - p.cu_seqlens[i]),
-             p.axis == 3 ? p.cu_seqlens[i] : p.cu_pairs[i]);
+             p.cu_pairs[i]);
   int r = __builtin_amdgcn_readfirstlane((int)(row - rows[i]));
   bf16x8 qf = load_q(n, cu, r);
   dma_kv(n, cu, r, Kb0, Vb0);
@@ -580,7 +574,7 @@ __global__ void __launch_bounds__(64 * NW, NMAX <= 256 ? 4 : 2) attention_pair_k
       while (rows[i2 + 1] <= row + 1) ++i2;
       r2 = 0;
       n2 = rows[i2 + 1] - rows[i2];
-      cu2 = p.axis == 3 ? p.cu_seqlens[i2] : p.cu_pairs[i2];
+      cu2 = p.cu_pairs[i2];
     }
     i2 = __builtin_amdgcn_readfirstlane(i2);
     r2 = __builtin_amdgcn_readfirstlane(r2);
@@ -694,10 +688,6 @@ __global__ void __launch_bounds__(64 * NW, NMAX <= 256 ? 4 : 2) attention_pair_k
       };
       run_sc(std::integral_constant<int, 0>{});
       run_sc(std::integral_constant<int, 1>{});
-      if constexpr (NMAX > 256) {
-        run_sc(std::integral_constant<int, 2>{});
-        run_sc(std::integral_constant<int, 3>{});
-      }
     }
     if (wave_has_queries) {
       // lane (l16, g) holds dims 4g .. 4g+3 and 16 + 4g .. +3 of its query;
@@ -755,7 +745,9 @@ __global__ void __launch_bounds__(64 * NW, NMAX <= 256 ? 4 : 2) attention_pair_k
 // Pair attention for head_dim 32 (axes 0 and 1) and samples longer than
 // kAttnShortLen: a workgroup of W waves copies the keys and values of one pair
 // row of one head into LDS (128 bytes per key), and its waves take the row's
-// 16-query tiles in turn, all keys of the row per tile.  The copy is the only
+// 16-query tiles in turn, all keys of the row per tile.  Single attention with
+// pair bias (axis 3) is the same with a sample's tokens as the row and up to
+// 128 of its queries per workgroup.  The copy is the only
 // barrier.  The bias of a tile is read in 64-key chunks from the bias image
 // (bf16, lane order, 512 bytes per 16 x 16 tile), one chunk ahead and across
 // tiles, so any row length that the LDS holds runs the same loop: registers
@@ -780,12 +772,17 @@ __global__ void __launch_bounds__(64 * W, 4) attention_row_kernel(PairAttnArgs p
   // share cache lines, follow each other on one XCD
   const int x = blockIdx.x % kXcds, t0 = blockIdx.x / kXcds;
   const int h = uni(t0 % p.H), pos = uni(t0 / p.H) * kXcds + x;
-  const int i = uni(p.work[2 * pos]), r = uni(p.work[2 * pos + 1]);
+  // axes 0 and 1: (sample, pair row); axis 3: (sample, first query tile, -, tiles)
+  const bool single = p.axis == 3;
+  const int32_t* item = p.work + (single ? 4 : 2) * pos;
+  const int i = uni(item[0]), r = uni(item[1]);
   if (i < 0) return;
   const int n = uni(p.cu_seqlens[i + 1] - p.cu_seqlens[i]);
+  const int q_first = single ? r : 0, q_end = single ? r + uni(item[3]) : (n + 15) >> 4;
   const int nch = (n + 63) >> 6, nt = 4 * nch;          // 64-key chunks, key tiles
   const int64_t cu = uni(p.cu_pairs[i]);
-  const int64_t base = p.axis == 0 ? cu + (int64_t)r * n : cu + r, st = p.axis == 0 ? 1 : n;
+  const int64_t base = single ? uni(p.cu_seqlens[i]) : p.axis == 0 ? cu + (int64_t)r * n : cu + r;
+  const int64_t st = p.axis == 1 ? n : 1;
   // rows of tile `tile` (16 elements of the pair row): a uniform 64-bit base
   // and a 32-bit byte offset per lane (the launcher checks that 16 rows span
   // less than 4 GB); rows (and whole tiles) past N repeat rows below N
@@ -807,7 +804,6 @@ __global__ void __launch_bounds__(64 * W, 4) attention_row_kernel(PairAttnArgs p
                                        (__attribute__((address_space(3))) void*)(lds + (nt + tile) * 512), 16, 0, 0);
     }
   }
-  const int nq = (n + 15) >> 4;
   const uint2* img = BIAS ? p.bias_img + (int64_t)h * p.img_head + (int64_t)uni(p.bias_tiles[i]) * 64 : nullptr;
   auto load_bias = [&](int qt, int c, uint2 (&b)[4]) {
     if constexpr (BIAS) {
@@ -818,16 +814,16 @@ __global__ void __launch_bounds__(64 * W, 4) attention_row_kernel(PairAttnArgs p
   };
   auto load_q = [&](int qt) { return *reinterpret_cast<const bf16x8*>(at(p.q + qoff, qt, l16, p.ld_qkv, g * 8)); };
   // the (query tile, chunk) steps of this wave, in order
-  int c = 0, qt = wave;
+  int c = 0, qt = q_first + wave;
   uint2 b0[4], b1[4];
   bf16x8 qf = bf16x8{}, qn = bf16x8{};
-  if (qt < nq) {
+  if (qt < q_end) {
     load_bias(qt, 0, b0);
     qn = load_q(qt);
   }
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
-  if (qt >= nq) return;
+  if (qt >= q_end) return;
 
   const uint32_t lds0 = lds_addr(lds), fo = (uint32_t)((g * 16 + (l16 ^ ((g & 1) << 3))) * 16), to = row_tr_offset(l16, g);
   const float sc = p.scale_log2, slack = 8.f / sc;
@@ -838,7 +834,7 @@ __global__ void __launch_bounds__(64 * W, 4) attention_row_kernel(PairAttnArgs p
   // Returns false after the last step.
   auto step = [&](const uint2 (&b)[4], uint2 (&bn)[4]) -> bool {
     const bool last = c + 1 == nch;
-    const int qtn = last && qt + W < nq ? qt + W : qt;    // after the last tile: a read that nothing uses
+    const int qtn = last && qt + W < q_end ? qt + W : qt;    // after the last tile: a read that nothing uses
     load_bias(qtn, last ? 0 : c + 1, bn);
     if (c == 0) {
       qf = qn;
@@ -935,7 +931,7 @@ __global__ void __launch_bounds__(64 * W, 4) attention_row_kernel(PairAttnArgs p
         *reinterpret_cast<uint4*>(const_cast<char*>(at(p.o + base * p.ld_o + h * D, qt, l16, p.ld_o, d0))) =
             make_uint4(ow[0][0], ow[0][1], ow[1][0], ow[1][1]);
       }
-      if (qt + W >= nq) return false;
+      if (qt + W >= q_end) return false;
       qt = qtn;
       c = 0;
       return true;
@@ -1256,7 +1252,7 @@ hipError_t launch_bias_image(const nt_layout& L, int axis, int H, const void* bi
   if (tiles == 0) return hipSuccess;
   BiasImgArgs b{axis, L.batch, (const bf16*)bias, ld_bias, ld_bias_head, mul, (uint2*)img, tiles,
                 L.d_bias_tiles, L.d_cu_seqlens, L.d_cu_pairs};
-  bias_image_kernel<<<dim3((unsigned)((tiles + 3) / 4), (unsigned)H), dim3(256), 0, s>>>(b);
+  bias_image_kernel<<<dim3((unsigned)((tiles + 15) / 16), (unsigned)H), dim3(256), 0, s>>>(b);
   return hipGetLastError();
 }
 
@@ -1390,13 +1386,9 @@ hipError_t launch_attention(const nt_layout& L, int axis, int H, int D, const vo
                    img, tiles * 64, L.d_bias_tiles, L.batch, L.d_cu_short,
                    reinterpret_cast<const int64_t*>(L.d_cu_short_cost), (const bf16*)gate, ld_gate};
     if (axis == 3) {
-      // single attention with pair bias: one row per sample, the 8-wave
-      // instance over the 1-D attention's (sample, 128-query block) items
+      // the 1-D attention's (sample, 128-query block) items
       if (L.sattn_items() == 0) return hipSuccess;
-      const size_t smem3 = sizeof(bf16) * 4 * (size_t)kAttnLongLen * 32;
-      hipFuncSetAttribute((const void*)attention_pair_kernel<kAttnLongLen, 8, false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem3);
-      attention_pair_kernel<kAttnLongLen, 8, false><<<dim3((unsigned)(L.sattn_items() * H)), dim3(512), smem3, s>>>(a);
-      return hipGetLastError();
+      return launch_attention_rows<8>(a, L.sattn_items(), (L.max_len + 63) & ~63, s);
     }
     if (longer) {
       PairAttnArgs al = a;
@@ -1414,11 +1406,11 @@ hipError_t launch_attention(const nt_layout& L, int axis, int H, int D, const vo
     const size_t smem = sizeof(bf16) * 4 * (size_t)kAttnShortLen * 32;
     const dim3 gridp((unsigned)(std::max(H, compute_units() / kXcds / H * H) * kXcds));
     if (gate) {
-      hipFuncSetAttribute((const void*)attention_pair_kernel<kAttnShortLen, 16, true, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-      attention_pair_kernel<kAttnShortLen, 16, true, true><<<gridp, dim3(1024), smem, s>>>(a);
-    } else {
       hipFuncSetAttribute((const void*)attention_pair_kernel<kAttnShortLen, 16, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
       attention_pair_kernel<kAttnShortLen, 16, true><<<gridp, dim3(1024), smem, s>>>(a);
+    } else {
+      hipFuncSetAttribute((const void*)attention_pair_kernel<kAttnShortLen, 16, false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+      attention_pair_kernel<kAttnShortLen, 16, false><<<gridp, dim3(1024), smem, s>>>(a);
     }
     return hipGetLastError();
   }
