@@ -219,6 +219,7 @@ struct PairAttnArgs {
   int batch;             // samples (persistent instance: rows are found from cu_seqlens)
   const int32_t* cu_short;   // persistent instance: prefix of the short samples' rows and of their cost
   const int64_t* cu_cost;
+  int64_t total_cost;
   const bf16* gate;      // gated output: o = sigmoid(gate) * attention, gate [rows, >= H*D] (GATE instances)
   int64_t ld_gate;
 };
@@ -454,30 +455,42 @@ __global__ void __launch_bounds__(64 * NW, 4) attention_pair_kernel(PairAttnArgs
   const int x = blockIdx.x % kXcds, k = blockIdx.x / kXcds, per = (int)(gridDim.x / kXcds);
   const int h = __builtin_amdgcn_readfirstlane(k % p.H), m = __builtin_amdgcn_readfirstlane(k / p.H);
   const int M = (per - h + p.H - 1) / p.H;
-  const int64_t total = p.cu_cost[p.batch];
+  const int64_t total = p.total_cost;
   const int64_t xa = total * x / kXcds, xb = total * (x + 1) / kXcds;
   // xa + (xb - xa) q / M, in 32 bits where they suffice (a 64-bit division costs about a microsecond)
   auto slice = [&](int q) -> int64_t {
     if (total < (int64_t(1) << 26)) return xa + (int64_t)((uint32_t)(xb - xa) * (uint32_t)q / (uint32_t)M);
     return xa + (xb - xa) * q / M;
   };
-  // first row whose cost starts at or past t, and its sample
-  auto row_at = [&](int64_t t, int& sample) -> int64_t {
+  // the row boundary nearest to cost t: index r0 of sample i, which has n0 rows
+  // counted from first and its cells from cu0 (every table entry is read once
+  // and side by side: a dependent load is most of a microsecond of a small call)
+  int i = 0, n0, first, r0, cu0;
+  auto row_at = [&](int64_t t) {
     int lo = 0, hi = p.batch;                   // cu_cost[lo] <= t, t < cu_cost[hi] (or hi = batch)
     while (hi - lo > 1) {
       const int mid = (lo + hi) >> 1;
       if (p.cu_cost[mid] <= t) lo = mid;
       else hi = mid;
     }
-    const int nn = rows[lo + 1] - rows[lo], w = (nn + 15) / 16 + kAttnRowCost;
-    sample = lo;
-    return rows[lo] + min(nn, (int)(((uint32_t)(t - p.cu_cost[lo]) + (uint32_t)w - 1u) / (uint32_t)w));
+    i = __builtin_amdgcn_readfirstlane(lo);
+    first = rows[i];
+    n0 = rows[i + 1] - first;
+    cu0 = p.cu_pairs[i];
+    const int w = (n0 + 15) / 16 + kAttnRowCost;
+    r0 = min(n0, (int)(((uint32_t)(t - p.cu_cost[i]) + (uint32_t)w / 2u) / (uint32_t)w));
   };
-  int i, unused;
-  int64_t row = row_at(slice(m), i);
-  const int64_t row_end = row_at(slice(m + 1), unused);
+  row_at(slice(m + 1));
+  const int64_t row_end = first + r0;
+  row_at(slice(m));
+  int64_t row = first + r0;
   if (row >= row_end) return;
-  while (rows[i + 1] <= row) ++i;
+  if (r0 == n0) {                               // the first row of the next non-empty sample
+    do ++i; while (rows[i + 1] <= row);
+    n0 = rows[i + 1] - (int)row;
+    cu0 = p.cu_pairs[i];
+    r0 = 0;
+  }
   i = __builtin_amdgcn_readfirstlane(i);
   const int jw = 16 * wave + l16;               // this lane's query
 
@@ -550,9 +563,8 @@ __global__ void __launch_bounds__(64 * NW, 4) attention_pair_kernel(PairAttnArgs
       bias_r[kt] = img && kt < kti ? img[kt * 64] : make_uint2(0u, 0u);
     }
   };
-  set_sample(i, __builtin_amdgcn_readfirstlane(p.cu_seqlens[i + 1] - p.cu_seqlens[i]),
-             p.cu_pairs[i]);
-  int r = __builtin_amdgcn_readfirstlane((int)(row - rows[i]));
+  set_sample(i, __builtin_amdgcn_readfirstlane(n0), __builtin_amdgcn_readfirstlane(cu0));
+  int r = __builtin_amdgcn_readfirstlane(r0);
   bf16x8 qf = load_q(n, cu, r);
   dma_kv(n, cu, r, Kb0, Vb0);
   __builtin_amdgcn_s_waitcnt(0);                // this wave's copies have landed
@@ -1384,7 +1396,7 @@ hipError_t launch_attention(const nt_layout& L, int axis, int H, int D, const vo
     PairAttnArgs a{axis, (const bf16*)q, (const bf16*)k, (const bf16*)v, ld_qkv, (const bf16*)bias, ld_bias,
                    ld_bias_head, scale * kLog2e, (bf16*)o, ld_o, L.d_sattn_work, L.d_cu_seqlens, L.d_cu_pairs, H,
                    img, tiles * 64, L.d_bias_tiles, L.batch, L.d_cu_short,
-                   reinterpret_cast<const int64_t*>(L.d_cu_short_cost), (const bf16*)gate, ld_gate};
+                   reinterpret_cast<const int64_t*>(L.d_cu_short_cost), L.short_cost(), (const bf16*)gate, ld_gate};
     if (axis == 3) {
       // the 1-D attention's (sample, 128-query block) items
       if (L.sattn_items() == 0) return hipSuccess;

@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <cstring>
 #include <string>
 #include <vector>
 
@@ -91,6 +92,11 @@ struct nt_layout {
   int64_t lattn_items() const { return (int64_t)lattn_work.size() / 2; }
   int64_t tri_items() const { return (int64_t)tri_work.size() / 4; }
   int64_t seq_items() const { return (int64_t)seq_work.size() / 2; }
+  int64_t short_cost() const {
+    int64_t c = 0;
+    if (!cu_short_cost.empty()) std::memcpy(&c, &cu_short_cost[cu_short_cost.size() - 2], sizeof(c));
+    return c;
+  }
   int64_t short_rows() const { return cu_short.empty() ? 0 : cu_short.back(); }
   int64_t sattn_items() const { return (int64_t)sattn_work.size() / 4; }
   int64_t bias_tiles_total() const { return bias_tiles.empty() ? 0 : bias_tiles.back(); }
