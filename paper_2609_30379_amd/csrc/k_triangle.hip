@@ -319,6 +319,79 @@ __global__ void __launch_bounds__(256) pack_tiled_kernel(const T* __restrict__ s
   }
 }
 
+// The same for plain bf16 operands with C a multiple of 64: one workgroup per
+// 16 x 32 tile and 64 channels.  The tile's 512 cells are copied straight into
+// LDS, 128 bytes (a whole line) each, at their fragment-order position, and
+// transposed on the way out: ds_read_b64_tr_b16 hands each lane four cells of
+// one channel, two reads make a 16-byte piece of a plane (positions outside the
+// sample zeroed).  16-byte piece s of position q is channels 8 (s ^ 2 f(q)),
+// f(q) = bit 1 of q + 2 bit 3 of q, which spreads the reads of a wave (four rows
+// of four octets, one half of the banks) over all banks.  The kernel moves
+// bytes only; loading 16 bytes of every cell per step and parking them with
+// 2-byte LDS writes ran at 2.3 TB/s (60 us for 68 MB and back at C = 128).
+constexpr int kPackChan = 64;
+
+template <bool TRANS>
+__global__ void __launch_bounds__(512) pack_lines_kernel(const bf16* __restrict__ src, int64_t ld_src,
+                                                         bf16* __restrict__ dst, int64_t ld_dst, int batch,
+                                                         const int32_t* __restrict__ cu_seqlens,
+                                                         const int32_t* __restrict__ cu_pairs,
+                                                         const int32_t* __restrict__ cu_pad) {
+  __shared__ __attribute__((aligned(16))) bf16 cells[512 * kPackChan];
+  const int64_t tile_pos = (int64_t)blockIdx.x * 512;
+  int lo = 0, hi = batch - 1;                       // sample: largest i with cu_pad[i] <= tile_pos
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (cu_pad[mid] <= tile_pos) lo = mid; else hi = mid - 1;
+  }
+  const int i = __builtin_amdgcn_readfirstlane(lo);
+  const int n = __builtin_amdgcn_readfirstlane(cu_seqlens[i + 1] - cu_seqlens[i]);
+  const int nkt = (n + 31) >> 5;
+  const int lt = __builtin_amdgcn_readfirstlane((int)((tile_pos - cu_pad[i]) >> 9));
+  const int rt = __builtin_amdgcn_readfirstlane(lt / nkt), kt = lt - rt * nkt;
+  const int c0 = blockIdx.y * kPackChan;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  // ---- copy: octet o (8 consecutive k of row o % 16) per instruction, lane ->
+  // cell lane / 8, piece at its swizzled place; cells outside the sample repeat
+  // one inside
+  const bf16* base = src + (int64_t)__builtin_amdgcn_readfirstlane(cu_pairs[i]) * ld_src + c0;
+#pragma unroll
+  for (int u = 0; u < 8; ++u) {
+    const int o = wave * 8 + u, ro = lane >> 3;
+    const int r = min(rt * 16 + (o & 15), n - 1), k = min(kt * 32 + (o >> 4) * 8 + ro, n - 1);
+    const int piece = (lane & 7) ^ (2 * (((ro >> 1) & 1) | ((o & 1) << 1)));
+    const bf16* from = base + ((int64_t)(TRANS ? k : r) * n + (TRANS ? r : k)) * ld_src + piece * 8;
+    __builtin_amdgcn_global_load_lds((const void*)from, (__attribute__((address_space(3))) void*)(cells + o * 8 * kPackChan), 16, 0, 0);
+  }
+  __builtin_amdgcn_s_waitcnt(0);
+  __syncthreads();
+  // ---- out: wave -> channels 16 cg .. +15, octets 32 (wave / 4) .. +31, four per step
+  const int l16 = lane & 15, g = lane >> 4, cg = wave & 3;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) bf16*)cells;
+  const bool edge = rt * 16 + 16 > n || kt * 32 + 32 > n;
+  bf16* out = dst + (int64_t)(c0 + cg * 16 + l16) * ld_dst + tile_pos;
+#pragma unroll
+  for (int u = 0; u < 8; ++u) {
+    const int o = (wave >> 2) * 32 + u * 4 + g, q = o * 8 + (l16 >> 2);
+    const int slot = (2 * cg + ((l16 & 3) >> 1)) ^ (2 * (((l16 >> 3) & 1) | ((o & 1) << 1)));
+    const uint32_t a = lds0 + q * (kPackChan * 2) + slot * 16 + (l16 & 1) * 8;
+    uint2 v[2];
+    asm volatile("ds_read_b64_tr_b16 %0, %2\n"
+                 "ds_read_b64_tr_b16 %1, %2 offset:512\n"
+                 "s_waitcnt lgkmcnt(0)"
+                 : "=&v"(v[0]), "=&v"(v[1])
+                 : "v"(a)
+                 : "memory");
+    uint32_t w[4] = {v[0].x, v[0].y, v[1].x, v[1].y};
+    if (edge) {
+      const int r = rt * 16 + (o & 15), left = r < n ? n - (kt * 32 + (o >> 4) * 8) : 0;   // cells of the octet inside
+#pragma unroll
+      for (int e = 0; e < 4; ++e) w[e] = 2 * e + 1 < left ? w[e] : 2 * e < left ? w[e] & 0xffffu : 0u;
+    }
+    *reinterpret_cast<uint4*>(out + o * 8) = make_uint4(w[0], w[1], w[2], w[3]);
+  }
+}
+
 }  // namespace
 
 size_t triangle_workspace_bytes(const nt_layout& L, int C, nt_tri_operands operands, nt_dtype dtype) {
@@ -335,6 +408,14 @@ hipError_t pack_planes(const nt_layout& L, const void* src, int64_t ld_src, bool
                        int64_t ldp, nt_dtype dtype, hipStream_t s, bool gated = false) {
   const dim3 grid((unsigned)(L.sum_pad / 512));
   if (grid.x == 0) return hipSuccess;
+  if (dtype == NT_BF16 && !gated && C % kPackChan == 0) {
+    const dim3 grid_c(grid.x, (unsigned)(C / kPackChan));
+    if (trans) pack_lines_kernel<true><<<grid_c, dim3(512), 0, s>>>((const bf16*)src, ld_src, (bf16*)dst, ldp, L.batch,
+                                                                     L.d_cu_seqlens, L.d_cu_pairs, L.d_cu_pad);
+    else pack_lines_kernel<false><<<grid_c, dim3(512), 0, s>>>((const bf16*)src, ld_src, (bf16*)dst, ldp, L.batch,
+                                                               L.d_cu_seqlens, L.d_cu_pairs, L.d_cu_pad);
+    return hipGetLastError();
+  }
 #define NT_PACK(T, TR, G) pack_tiled_kernel<T, TR, G><<<grid, dim3(256), 0, s>>>((const T*)src, ld_src, C, (T*)dst, \
                                                                         ldp, L.batch, L.d_cu_seqlens, L.d_cu_pairs, L.d_cu_pad)
 #define NT_PACK_G(T, TR) do { if (gated) NT_PACK(T, TR, true); else NT_PACK(T, TR, false); } while (0)
