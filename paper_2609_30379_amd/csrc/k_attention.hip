@@ -214,6 +214,7 @@ struct PairAttnArgs {
   const int32_t* cu_pairs;
   int H;                 // heads (interleaved in the grid)
   const uint2* bias_img; // bias image (see bias_image_kernel) or NULL for no bias
+  float bias_mul;        // RAW instances: the image holds the bias as it is, multiplied by this (1 / scale) in fp32
   int64_t img_head;      // uint2 entries per head of the image
   const int32_t* bias_tiles;
   int batch;             // samples (persistent instance: rows are found from cu_seqlens)
@@ -431,7 +432,7 @@ __device__ __forceinline__ float query_max(float v) {
 //     ones operand, on the same bf16 probabilities as the numerator.
 // Scores are kept transposed (S^T = K Q^T), so a lane holds 16 keys of one
 // query per 64-key chunk and the running max is mostly lane-local.
-template <int NMAX, int NW, bool GATE>
+template <int NMAX, int NW, bool GATE, bool RAW>
 __global__ void __launch_bounds__(64 * NW, 4) attention_pair_kernel(PairAttnArgs p) {
   constexpr int D = 32;
   constexpr int KT16 = NMAX / 16;               // key tiles
@@ -632,6 +633,7 @@ __global__ void __launch_bounds__(64 * NW, 4) attention_pair_kernel(PairAttnArgs
           const uint2 bb = bias_r[T0 + kt];
           S[kt] = f32x4{__uint_as_float(bb.x << 16), __uint_as_float(bb.x & 0xffff0000u),
                         __uint_as_float(bb.y << 16), __uint_as_float(bb.y & 0xffff0000u)};
+          if constexpr (RAW) S[kt] *= p.bias_mul;
           const bf16x8 kf = *reinterpret_cast<const bf16x8*>(&Kb[(T0 + kt) * 512 + lane * 8]);
           S[kt] = mfma16(kf, qf, S[kt]);
           // at most four key fragments in flight (registers)
@@ -773,7 +775,7 @@ __global__ void __launch_bounds__(64 * NW, 4) attention_pair_kernel(PairAttnArgs
 // it by more than 8 in log2 units, so most chunks need no exchange between
 // lanes.  A chunk whose keys are all masked (-inf) leaves a maximum of -inf
 // and weights of 0.
-template <int W, bool GATE, bool BIAS>
+template <int W, bool GATE, bool BIAS, bool RAW>
 __global__ void __launch_bounds__(64 * W, 4) attention_row_kernel(PairAttnArgs p) {
   constexpr int D = 32;
   extern __shared__ __attribute__((aligned(16))) bf16 lds[];
@@ -873,6 +875,7 @@ __global__ void __launch_bounds__(64 * W, 4) attention_row_kernel(PairAttnArgs p
       if constexpr (BIAS)
         S[t] = f32x4{__uint_as_float(b[t].x << 16), __uint_as_float(b[t].x & 0xffff0000u),
                      __uint_as_float(b[t].y << 16), __uint_as_float(b[t].y & 0xffff0000u)};
+      if constexpr (RAW) S[t] *= p.bias_mul;
       S[t] = mfma16(*reinterpret_cast<const bf16x8*>(ks + t * 1024), qf, S[t]);
     }
     if constexpr (!BIAS) {                              // keys past N (the image masks them)
@@ -1334,19 +1337,36 @@ hipError_t launch_cross_attention(const nt_layout& Lq, const nt_layout& Lkv, int
 }
 
 namespace {
-template <int W>
-hipError_t launch_attention_rows(const PairAttnArgs& a, int64_t items, int max_keys, hipStream_t s) {
-  const dim3 grid((unsigned)(items * a.H)), block(64 * W);
-  const size_t smem = (size_t)max_keys * 128;
-  const bool gate = a.gate != nullptr, bias = a.bias_img != nullptr;
-  const void* fn = gate ? (bias ? (const void*)attention_row_kernel<W, true, true> : (const void*)attention_row_kernel<W, true, false>)
-                        : (bias ? (const void*)attention_row_kernel<W, false, true> : (const void*)attention_row_kernel<W, false, false>);
-  const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+template <int W, bool GATE, bool BIAS, bool RAW>
+hipError_t launch_row_instance(const PairAttnArgs& a, dim3 grid, size_t smem, hipStream_t s) {
+  const hipError_t e = hipFuncSetAttribute((const void*)attention_row_kernel<W, GATE, BIAS, RAW>,
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
   if (e != hipSuccess) return e;
-  if (gate && bias) attention_row_kernel<W, true, true><<<grid, block, smem, s>>>(a);
-  else if (gate) attention_row_kernel<W, true, false><<<grid, block, smem, s>>>(a);
-  else if (bias) attention_row_kernel<W, false, true><<<grid, block, smem, s>>>(a);
-  else attention_row_kernel<W, false, false><<<grid, block, smem, s>>>(a);
+  attention_row_kernel<W, GATE, BIAS, RAW><<<grid, dim3(64 * W), smem, s>>>(a);
+  return hipGetLastError();
+}
+
+template <int W>
+hipError_t launch_attention_rows(const PairAttnArgs& a, bool raw, int64_t items, int max_keys, hipStream_t s) {
+  const dim3 grid((unsigned)(items * a.H));
+  const size_t smem = (size_t)max_keys * 128;
+  if (!a.bias_img)
+    return a.gate ? launch_row_instance<W, true, false, false>(a, grid, smem, s)
+                  : launch_row_instance<W, false, false, false>(a, grid, smem, s);
+  if (raw)
+    return a.gate ? launch_row_instance<W, true, true, true>(a, grid, smem, s)
+                  : launch_row_instance<W, false, true, true>(a, grid, smem, s);
+  return a.gate ? launch_row_instance<W, true, true, false>(a, grid, smem, s)
+                : launch_row_instance<W, false, true, false>(a, grid, smem, s);
+}
+
+template <bool GATE, bool RAW>
+hipError_t launch_pair_instance(const PairAttnArgs& a, dim3 grid, hipStream_t s) {
+  const size_t smem = sizeof(bf16) * 4 * (size_t)kAttnShortLen * 32;
+  const hipError_t e = hipFuncSetAttribute((const void*)attention_pair_kernel<kAttnShortLen, 16, GATE, RAW>,
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+  if (e != hipSuccess) return e;
+  attention_pair_kernel<kAttnShortLen, 16, GATE, RAW><<<grid, dim3(1024), smem, s>>>(a);
   return hipGetLastError();
 }
 }  // namespace
@@ -1383,48 +1403,51 @@ hipError_t launch_attention(const nt_layout& L, int axis, int H, int D, const vo
   // and that instance took 416 and 406 us together.
   const bool longer = L.max_len > kAttnShortLen;
   const int64_t ld_max = std::max(std::max(ld_qkv, ld_o), gate ? ld_gate : 0);
-  const bool rows_ok = (!bias || workspace) && 32 * ld_max * L.max_len < (int64_t(1) << 32);
+  // Past kAttnLongLen the bias image keeps the bias as it is and the kernels
+  // multiply it by 1 / scale in fp32, so the score is as exact as where the
+  // per-row kernel adds the gathered bias; the running maximum is taken before
+  // the scale, so scales that are zero, negative or too small to divide by
+  // stay with the per-row kernel.  The multiplication costs 1 % (gated column
+  // attention layer of a B = 16 batch up to 586: 1030 -> 1042 us).
+  const bool raw = L.max_len > kAttnLongLen;
+  const bool rows_ok = (!bias || workspace) && 32 * ld_max * L.max_len < (int64_t(1) << 32) &&
+                       (!raw || scale >= 1e-6f);
   if (D == 32 && (axis == 3 || (axis <= 1 && (!longer || rows_ok)))) {
     const int64_t tiles = L.bias_tiles_total();
     const uint2* img = nullptr;
     if (bias && tiles > 0) {
       // the caller's workspace receives the bias image
-      const hipError_t e = launch_bias_image(L, axis, H, bias, ld_bias, ld_bias_head, 1.f / scale, workspace, s);
+      const hipError_t e = launch_bias_image(L, axis, H, bias, ld_bias, ld_bias_head, raw ? 1.f : 1.f / scale, workspace,
+                                             s);
       if (e != hipSuccess) return e;
       img = (const uint2*)workspace;
     }
     PairAttnArgs a{axis, (const bf16*)q, (const bf16*)k, (const bf16*)v, ld_qkv, (const bf16*)bias, ld_bias,
                    ld_bias_head, scale * kLog2e, (bf16*)o, ld_o, L.d_sattn_work, L.d_cu_seqlens, L.d_cu_pairs, H,
-                   img, tiles * 64, L.d_bias_tiles, L.batch, L.d_cu_short,
+                   img, 1.f / scale, tiles * 64, L.d_bias_tiles, L.batch, L.d_cu_short,
                    reinterpret_cast<const int64_t*>(L.d_cu_short_cost), L.short_cost(), (const bf16*)gate, ld_gate};
     if (axis == 3) {
       // the 1-D attention's (sample, 128-query block) items
       if (L.sattn_items() == 0) return hipSuccess;
-      return launch_attention_rows<8>(a, L.sattn_items(), (L.max_len + 63) & ~63, s);
+      return launch_attention_rows<8>(a, false, L.sattn_items(), (L.max_len + 63) & ~63, s);
     }
     if (longer) {
       PairAttnArgs al = a;
       al.work = L.d_lattn_work;
       const int keys = (L.max_len + 63) & ~63;
       // 8 waves where two workgroups share a CU's 160 KB of LDS, else 16: four waves per SIMD either way
-      const hipError_t e = keys <= 640 ? launch_attention_rows<8>(al, L.lattn_items(), keys, s)
-                                       : launch_attention_rows<16>(al, L.lattn_items(), keys, s);
+      const hipError_t e = keys <= 640 ? launch_attention_rows<8>(al, raw, L.lattn_items(), keys, s)
+                                       : launch_attention_rows<16>(al, raw, L.lattn_items(), keys, s);
       if (e != hipSuccess) return e;
     }
     if (L.short_rows() == 0) return hipSuccess;
     // persistent: one workgroup of 16 waves per CU (all queries of a row); per
     // XCD a multiple of H workgroups, at least H, so every head gets an equal
     // share of each XCD's rows
-    const size_t smem = sizeof(bf16) * 4 * (size_t)kAttnShortLen * 32;
     const dim3 gridp((unsigned)(std::max(H, compute_units() / kXcds / H * H) * kXcds));
-    if (gate) {
-      hipFuncSetAttribute((const void*)attention_pair_kernel<kAttnShortLen, 16, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-      attention_pair_kernel<kAttnShortLen, 16, true><<<gridp, dim3(1024), smem, s>>>(a);
-    } else {
-      hipFuncSetAttribute((const void*)attention_pair_kernel<kAttnShortLen, 16, false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-      attention_pair_kernel<kAttnShortLen, 16, false><<<gridp, dim3(1024), smem, s>>>(a);
-    }
-    return hipGetLastError();
+    if (raw && img)
+      return gate ? launch_pair_instance<true, true>(a, gridp, s) : launch_pair_instance<false, true>(a, gridp, s);
+    return gate ? launch_pair_instance<true, false>(a, gridp, s) : launch_pair_instance<false, false>(a, gridp, s);
   }
   const int npad = (L.max_len + 63) & ~63;
   if (axis == 2 && L.max_len <= kAttnLongLen)

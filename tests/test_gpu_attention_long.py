@@ -1,6 +1,6 @@
 """Pair attention on batches with samples longer than 512: the row kernel's
 8- and 16-wave instances at the edges of their LDS (640, 641, 1024 keys) and of
-a 64-key chunk, shorter samples of the same batch on the work-list kernel, with
+a 64-key chunk, shorter samples of the same batch on the persistent kernel, with
 and without bias and gate, masked keys, and a call without room for the bias
 image."""
 import numpy as np
@@ -16,7 +16,7 @@ pytestmark = pytest.mark.gpu
 D = 32
 
 
-def _run(L, H, axis, bias=True, gate=False, masked=False, image=True):
+def _run(L, H, axis, bias=True, gate=False, masked=False, image=True, scale=None):
     import torch
     from paper_2609_30379_amd import binding as B
     lay = B.NestedLayout(L)
@@ -39,12 +39,12 @@ def _run(L, H, axis, bias=True, gate=False, masked=False, image=True):
     ws = None if image else torch.empty(16, dtype=torch.uint8, device="cuda")
     call = lambda: B.nt_pair_row_attention(lay, axis, H, D, xd[:, :c], xd[:, c:2 * c], xd[:, 2 * c:3 * c], out,  # noqa: E731
                                            bias=dev(np.ascontiguousarray(bv.T), "bf16") if bias else None,
-                                           bias_layout="heads", workspace=ws, gate=xd[:, 3 * c:] if gate else None)
+                                           bias_layout="heads", workspace=ws, gate=xd[:, 3 * c:] if gate else None, scale=scale)
     call()
     first = host(out)
     call()
     assert np.array_equal(host(out), first)
-    ref = O.pair_row_attention(x[:, :c], x[:, c:2 * c], x[:, 2 * c:3 * c], bv, L, H, D, axis=axis,
+    ref = O.pair_row_attention(x[:, :c], x[:, c:2 * c], x[:, 2 * c:3 * c], bv, L, H, D, axis=axis, scale=scale,
                                gate=x[:, 3 * c:] if gate else None)
     check(first, ref, "bf16", f"long pair attention axis {axis} {L} H={H} bias {bias} gate {gate} masked {masked} image {image}")
 
@@ -57,6 +57,9 @@ def _run(L, H, axis, bias=True, gate=False, masked=False, image=True):
     ([641, 1], 1, dict(gate=True)),            # the 16-wave instance
     ([530, 65], 1, dict(bias=False)),
     ([520, 33], 1, dict(image=False)),
+    ([514, 20], 1, dict(scale=0.0)),           # the bias image cannot be divided by these scales
+    ([514, 20], 1, dict(scale=-0.2, gate=True)),
+    ([514, 20], 1, dict(scale=0.0, bias=False)),
 ])
 def test_long_pair_attention(axis, L, H, kw):
     _run(L, H, axis, **kw)
