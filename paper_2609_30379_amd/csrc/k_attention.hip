@@ -214,7 +214,6 @@ struct PairAttnArgs {
   const int32_t* cu_pairs;
   int H;                 // heads (interleaved in the grid)
   const uint2* bias_img; // bias image (see bias_image_kernel) or NULL for no bias
-  float bias_mul;        // RAW instances: the image holds the bias as it is, multiplied by this (1 / scale) in fp32
   int64_t img_head;      // uint2 entries per head of the image
   const int32_t* bias_tiles;
   int batch;             // samples (persistent instance: rows are found from cu_seqlens)
@@ -228,10 +227,12 @@ struct PairAttnArgs {
 // Pair bias image: for head h, sample i, 16-query tile qt and 16-key tile kt
 // (kt < round_up(N_i,64)/16), lane l = l16 + 16 g of tile
 // ((h * T + bias_tiles[i] + qt * KT_i + kt) holds the four values
-// bias(j, k) / scale, j = 16 qt + l16, k = 16 kt + 4 g .. +3, each rounded to
-// bf16 -- exactly the register image the attention lanes keep.  Keys past N
-// hold -inf (for queries inside N), so the scores they seed are masked
-// without further work; queries past N hold 0.
+// bias(j, k) * mul, j = 16 qt + l16, k = 16 kt + 4 g .. +3, each rounded to
+// bf16 -- exactly the register image the attention lanes keep.  Finite values
+// stay within +-limit, so a finite mask is still finite where it is multiplied
+// (by mul here or in fp32 later); infinities and NaN pass.  Keys past N hold
+// -inf (for queries inside N), so the scores they seed are masked without
+// further work; queries past N hold 0.
 // bias(j, k) is the head-h bias of cell(j, k) for axis 0 and of cell(k, j)
 // for axis 1, read at cell * ld_bias + h * ld_bias_head; the sample is found by
 // bisection.
@@ -239,7 +240,7 @@ struct BiasImgArgs {
   int axis, batch;
   const bf16* bias;
   int64_t ld_bias, ld_bias_head;
-  float inv_scale;
+  float mul, limit;
   uint2* img;
   int64_t tiles;          // tiles per head
   const int32_t* bias_tiles;
@@ -288,7 +289,10 @@ __global__ void __launch_bounds__(256) bias_image_kernel(BiasImgArgs p) {
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       float b = j < n ? -INFINITY : 0.f;
-      if (j < n && kt0 + 16 * u + e < n) b = (float)raw[u][e] * p.inv_scale;
+      if (j < n && kt0 + 16 * u + e < n) {
+        b = (float)raw[u][e] * p.mul;
+        if ((__builtin_bit_cast(uint16_t, (bf16)raw[u][e]) & 0x7f80) != 0x7f80) b = fminf(fmaxf(b, -p.limit), p.limit);
+      }
       o[e] = (bf16)b;
     }
     *reinterpret_cast<bf16x4*>(&p.img[(int64_t)h * p.tiles * 64 + (tile + u) * 64 + lane]) = o;
@@ -411,6 +415,26 @@ __device__ __forceinline__ float query_max(float v) {
   return fmaxf(__uint_as_float(s32[0]), __uint_as_float(s32[1]));
 }
 
+// Scores against the reference maximum m: the weight is 2^((S - m) c).  With
+// nm = -fl(m c) it takes one fused multiply-add per score, and the rounding
+// error of m c, up to 2^-24 of it, scales every weight of the chunk alike: no
+// more than the fp32 score's own error, but a power of two that overflows or
+// vanishes, and differs between chunks, once |m| is that of a finite mask
+// (-1e9 and beyond).  Past kFarMax, and where m is still -inf because every key
+// so far is masked, the difference is taken first (against 0 for -inf); a
+// chunk's keys pay for it only then.
+constexpr float kFarMax = 4096.f;
+// factor of the accumulators when the maximum moves from m to m_new
+__device__ __forceinline__ float rescale(float m, float m_new, float c) {
+  return m_new == -INFINITY ? 1.f : __builtin_amdgcn_exp2f((m - m_new) * c);
+}
+// scale log2(e) S + log2(e) bias: the score in log2 units, in fp32
+__device__ __forceinline__ f32x4 log2_scores(f32x4 S, float scale_log2, f32x4 bias) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) S[e] = fmaf(S[e], scale_log2, bias[e] * kLog2e);
+  return S;
+}
+
 // ---------------------------------------------------------------- pair attention, head_dim 32
 // Pair attention for head_dim 32 and the samples up to kAttnShortLen, organised
 // so that the exponentials are nearly the only vector work.  Persistent: one
@@ -420,10 +444,11 @@ __device__ __forceinline__ float query_max(float v) {
 // skipped, their rows are attention_row_kernel's.
 //   * the bias of (query, key) does not depend on the pair row, so each lane
 //     keeps the bias of its query for its 4-key groups of every key tile in
-//     registers while the rows belong to one sample -- read from the bias
-//     image, already divided by the softmax scale (one bf16 rounding) -- and
-//     it seeds the score accumulators: the matrix cores produce
-//     bias/scale + q.k directly;
+//     registers while the rows belong to one sample, read from the bias
+//     image.  Divided by the softmax scale there (one bf16 rounding) it seeds
+//     the score accumulators: the matrix cores produce bias/scale + q.k
+//     directly.  EXACT instances read the bias itself and form the score in
+//     log2 units in fp32 (see attention_row_kernel);
 //   * keys and values of a row are copied straight into LDS (keys as fragment
 //     images: 64 lanes x 16 bytes, read as one contiguous 1 KB per wave) in
 //     two buffers, the next row's copies in flight while the current row
@@ -432,7 +457,7 @@ __device__ __forceinline__ float query_max(float v) {
 //     ones operand, on the same bf16 probabilities as the numerator.
 // Scores are kept transposed (S^T = K Q^T), so a lane holds 16 keys of one
 // query per 64-key chunk and the running max is mostly lane-local.
-template <int NMAX, int NW, bool GATE, bool RAW>
+template <int NMAX, int NW, bool GATE, bool EXACT>
 __global__ void __launch_bounds__(64 * NW, 4) attention_pair_kernel(PairAttnArgs p) {
   constexpr int D = 32;
   constexpr int KT16 = NMAX / 16;               // key tiles
@@ -614,7 +639,8 @@ __global__ void __launch_bounds__(64 * NW, 4) attention_pair_kernel(PairAttnArgs
     // double its registers
 #pragma unroll
     for (int kt = 0; kt < KT16; ++kt) asm volatile("" : "+v"(bias_r[kt].x), "+v"(bias_r[kt].y));
-    float m_s = -INFINITY;                        // running max of bias/scale + q.k
+    float m_s = -INFINITY;                        // running max of bias/scale + q.k (EXACT: of the log2 score)
+    bool far = true;                              // some lane's m_s is -inf or beyond kFarMax
     f32x4 O[3];                                   // dims 0-15, 16-31, row sum
 #pragma unroll
     for (int u = 0; u < 3; ++u) O[u] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -631,11 +657,11 @@ __global__ void __launch_bounds__(64 * NW, 4) attention_pair_kernel(PairAttnArgs
 #pragma unroll
         for (int kt = 0; kt < NT; ++kt) {
           const uint2 bb = bias_r[T0 + kt];
-          S[kt] = f32x4{__uint_as_float(bb.x << 16), __uint_as_float(bb.x & 0xffff0000u),
-                        __uint_as_float(bb.y << 16), __uint_as_float(bb.y & 0xffff0000u)};
-          if constexpr (RAW) S[kt] *= p.bias_mul;
+          const f32x4 b4 = {__uint_as_float(bb.x << 16), __uint_as_float(bb.x & 0xffff0000u),
+                            __uint_as_float(bb.y << 16), __uint_as_float(bb.y & 0xffff0000u)};
           const bf16x8 kf = *reinterpret_cast<const bf16x8*>(&Kb[(T0 + kt) * 512 + lane * 8]);
-          S[kt] = mfma16(kf, qf, S[kt]);
+          S[kt] = mfma16(kf, qf, EXACT ? f32x4{0.f, 0.f, 0.f, 0.f} : b4);
+          if constexpr (EXACT) S[kt] = log2_scores(S[kt], c, b4);
           // at most four key fragments in flight (registers)
           if (kt % 4 == 3) __builtin_amdgcn_sched_barrier(0);
         }
@@ -655,20 +681,30 @@ __global__ void __launch_bounds__(64 * NW, 4) attention_pair_kernel(PairAttnArgs
         // the reference max moves only when some query's max grew by more
         // than 8 (log2 units): probabilities then stay below 2^8, and most
         // super-chunks skip rescaling the accumulators
-        if (__any((mloc - m_s) * c > 8.f)) {
+        constexpr float kUnits = 8.f;
+        if (__any((EXACT ? mloc - m_s : (mloc - m_s) * c) > kUnits)) {
           const float m_new = fmaxf(m_s, mloc);
-          const float alpha = __builtin_amdgcn_exp2f((m_s - m_new) * c);
+          const float alpha = rescale(m_s, m_new, EXACT ? 1.f : c);
           m_s = m_new;
+          far = __any(fabsf(m_s) > kFarMax);
 #pragma unroll
           for (int u = 0; u < 3; ++u) O[u] *= alpha;
         }
-        const float nm = -m_s * c;
+        float nm = EXACT ? (m_s == -INFINITY ? 0.f : -m_s) : -m_s * c;
+        if (!EXACT && far) {
+          nm = m_s == -INFINITY ? 0.f : m_s;
+#pragma unroll
+          for (int kt = 0; kt < NT; ++kt) S[kt] -= nm;
+          nm = 0.f;
+        }
         bf16x8 P[NT / 2];
 #pragma unroll
         for (int kt = 0; kt < NT; ++kt)
 #pragma unroll
-          for (int ii = 0; ii < 4; ++ii)
-            P[kt >> 1][(kt & 1) * 4 + ii] = (bf16)__builtin_amdgcn_exp2f(fmaf(S[kt][ii], c, nm));
+          for (int ii = 0; ii < 4; ++ii) {
+            const float w = __builtin_amdgcn_exp2f(EXACT ? S[kt][ii] + nm : fmaf(S[kt][ii], c, nm));
+            P[kt >> 1][(kt & 1) * 4 + ii] = (bf16)w;
+          }
         const bf16x8 ones = ones_bf16x8();
 #pragma unroll
         for (int pp = 0; pp + 1 < NT / 2; pp += 2) {
@@ -736,7 +772,7 @@ __global__ void __launch_bounds__(64 * NW, 4) attention_pair_kernel(PairAttnArgs
       }
       if (qvalid) {
         bf16* orow = obase + (cu + (int64_t)r * sr + (int64_t)jw * st) * p.ld_o;
-        const int d0 = (g & 1) ? 16 + 4 * (g - 1) : 4 * g;
+        const int go = opaque(g), d0 = (go & 1) ? 16 + 4 * (go - 1) : 4 * go;
         *reinterpret_cast<uint4*>(orow + d0) = make_uint4(ow[0][0], ow[0][1], ow[1][0], ow[1][1]);
       }
     }
@@ -775,7 +811,11 @@ __global__ void __launch_bounds__(64 * NW, 4) attention_pair_kernel(PairAttnArgs
 // it by more than 8 in log2 units, so most chunks need no exchange between
 // lanes.  A chunk whose keys are all masked (-inf) leaves a maximum of -inf
 // and weights of 0.
-template <int W, bool GATE, bool BIAS, bool RAW>
+//
+// EXACT instances read the bias itself and form scale S + bias in log2 units
+// in fp32 (any scale, and no rounding of bias / scale): one more vector
+// instruction per score.
+template <int W, bool GATE, bool BIAS, bool EXACT>
 __global__ void __launch_bounds__(64 * W, 4) attention_row_kernel(PairAttnArgs p) {
   constexpr int D = 32;
   extern __shared__ __attribute__((aligned(16))) bf16 lds[];
@@ -840,9 +880,10 @@ __global__ void __launch_bounds__(64 * W, 4) attention_row_kernel(PairAttnArgs p
   if (qt >= q_end) return;
 
   const uint32_t lds0 = lds_addr(lds), fo = (uint32_t)((g * 16 + (l16 ^ ((g & 1) << 3))) * 16), to = row_tr_offset(l16, g);
-  const float sc = p.scale_log2, slack = 8.f / sc;
+  const float sc = p.scale_log2, slack = EXACT ? 8.f : 8.f / sc;
   const bf16x8 ones = ones_bf16x8();
-  float m_s = -INFINITY, nm = 0.f;                      // running maximum of bias/scale + q.k, and -m_s sc
+  float m_s = -INFINITY, nm = 0.f;                      // running maximum of bias/scale + q.k, and -m_s sc (0 where far)
+  bool far = true;                                      // some lane's m_s is -inf or beyond kFarMax
   f32x4 O[3];                                           // dims 0-15, 16-31, row sum
   // one step with the bias in b; the next step's bias is read into bn.
   // Returns false after the last step.
@@ -854,6 +895,7 @@ __global__ void __launch_bounds__(64 * W, 4) attention_row_kernel(PairAttnArgs p
       qf = qn;
       m_s = -INFINITY;
       nm = 0.f;
+      far = true;
 #pragma unroll
       for (int u = 0; u < 3; ++u) O[u] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
@@ -871,12 +913,13 @@ __global__ void __launch_bounds__(64 * W, 4) attention_row_kernel(PairAttnArgs p
     f32x4 S[4];
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
-      S[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+      f32x4 b4 = {0.f, 0.f, 0.f, 0.f};
       if constexpr (BIAS)
-        S[t] = f32x4{__uint_as_float(b[t].x << 16), __uint_as_float(b[t].x & 0xffff0000u),
-                     __uint_as_float(b[t].y << 16), __uint_as_float(b[t].y & 0xffff0000u)};
-      if constexpr (RAW) S[t] *= p.bias_mul;
-      S[t] = mfma16(*reinterpret_cast<const bf16x8*>(ks + t * 1024), qf, S[t]);
+        b4 = f32x4{__uint_as_float(b[t].x << 16), __uint_as_float(b[t].x & 0xffff0000u),
+                   __uint_as_float(b[t].y << 16), __uint_as_float(b[t].y & 0xffff0000u)};
+      S[t] = mfma16(*reinterpret_cast<const bf16x8*>(ks + t * 1024), qf, EXACT ? f32x4{0.f, 0.f, 0.f, 0.f} : b4);
+      if constexpr (EXACT && BIAS) S[t] = log2_scores(S[t], sc, b4);
+      else if constexpr (EXACT) S[t] *= sc;
     }
     if constexpr (!BIAS) {                              // keys past N (the image masks them)
       if (64 * c + 64 > n) {
@@ -894,18 +937,26 @@ __global__ void __launch_bounds__(64 * W, 4) attention_row_kernel(PairAttnArgs p
       for (int e = 0; e < 4; ++e) mx = fmaxf(mx, S[t][e]);
     if (__any(mx > m_s + slack)) {
       const float m_new = fmaxf(m_s, query_max(mx));
-      nm = m_new == -INFINITY ? 0.f : -m_new * sc;
-      const float alpha = __builtin_amdgcn_exp2f(fmaf(m_s, sc, nm));
+      const float alpha = rescale(m_s, m_new, EXACT ? 1.f : sc);
       m_s = m_new;
+      far = __any(fabsf(m_s) > kFarMax);
+      nm = EXACT ? (m_s == -INFINITY ? 0.f : -m_s) : far ? 0.f : -m_s * sc;
 #pragma unroll
       for (int u = 0; u < 3; ++u) O[u] *= alpha;
+    }
+    if (!EXACT && far) {
+      const float ms = m_s == -INFINITY ? 0.f : m_s;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) S[t] -= ms;
     }
     bf16x8 P[2];
 #pragma unroll
     for (int t = 0; t < 4; ++t)
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
-        P[t >> 1][(t & 1) * 4 + e] = (bf16)__builtin_amdgcn_exp2f(fmaf(S[t][e], sc, nm));
+      for (int e = 0; e < 4; ++e) {
+        const float w = __builtin_amdgcn_exp2f(EXACT ? S[t][e] + nm : fmaf(S[t][e], sc, nm));
+        P[t >> 1][(t & 1) * 4 + e] = (bf16)w;
+      }
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
       bf16x8 vf[2];
@@ -1262,10 +1313,10 @@ hipError_t noalloc_scratch(void** ptr) {
 size_t bias_image_bytes(const nt_layout& L, int H) { return (size_t)H * (size_t)L.bias_tiles_total() * 512; }
 
 hipError_t launch_bias_image(const nt_layout& L, int axis, int H, const void* bias, int64_t ld_bias,
-                             int64_t ld_bias_head, float mul, void* img, hipStream_t s) {
+                             int64_t ld_bias_head, float mul, float limit, void* img, hipStream_t s) {
   const int64_t tiles = L.bias_tiles_total();
   if (tiles == 0) return hipSuccess;
-  BiasImgArgs b{axis, L.batch, (const bf16*)bias, ld_bias, ld_bias_head, mul, (uint2*)img, tiles,
+  BiasImgArgs b{axis, L.batch, (const bf16*)bias, ld_bias, ld_bias_head, mul, limit, (uint2*)img, tiles,
                 L.d_bias_tiles, L.d_cu_seqlens, L.d_cu_pairs};
   bias_image_kernel<<<dim3((unsigned)((tiles + 15) / 16), (unsigned)H), dim3(256), 0, s>>>(b);
   return hipGetLastError();
@@ -1337,36 +1388,44 @@ hipError_t launch_cross_attention(const nt_layout& Lq, const nt_layout& Lkv, int
 }
 
 namespace {
-template <int W, bool GATE, bool BIAS, bool RAW>
+template <int W, bool GATE, bool BIAS, bool EXACT>
 hipError_t launch_row_instance(const PairAttnArgs& a, dim3 grid, size_t smem, hipStream_t s) {
-  const hipError_t e = hipFuncSetAttribute((const void*)attention_row_kernel<W, GATE, BIAS, RAW>,
+  const hipError_t e = hipFuncSetAttribute((const void*)attention_row_kernel<W, GATE, BIAS, EXACT>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
   if (e != hipSuccess) return e;
-  attention_row_kernel<W, GATE, BIAS, RAW><<<grid, dim3(64 * W), smem, s>>>(a);
+  attention_row_kernel<W, GATE, BIAS, EXACT><<<grid, dim3(64 * W), smem, s>>>(a);
   return hipGetLastError();
 }
 
-template <int W>
-hipError_t launch_attention_rows(const PairAttnArgs& a, bool raw, int64_t items, int max_keys, hipStream_t s) {
+template <int W, bool EXACT>
+hipError_t launch_attention_rows(const PairAttnArgs& a, int64_t items, int max_keys, hipStream_t s) {
   const dim3 grid((unsigned)(items * a.H));
   const size_t smem = (size_t)max_keys * 128;
   if (!a.bias_img)
-    return a.gate ? launch_row_instance<W, true, false, false>(a, grid, smem, s)
-                  : launch_row_instance<W, false, false, false>(a, grid, smem, s);
-  if (raw)
-    return a.gate ? launch_row_instance<W, true, true, true>(a, grid, smem, s)
-                  : launch_row_instance<W, false, true, true>(a, grid, smem, s);
-  return a.gate ? launch_row_instance<W, true, true, false>(a, grid, smem, s)
-                : launch_row_instance<W, false, true, false>(a, grid, smem, s);
+    return a.gate ? launch_row_instance<W, true, false, EXACT>(a, grid, smem, s)
+                  : launch_row_instance<W, false, false, EXACT>(a, grid, smem, s);
+  return a.gate ? launch_row_instance<W, true, true, EXACT>(a, grid, smem, s)
+                : launch_row_instance<W, false, true, EXACT>(a, grid, smem, s);
 }
 
-template <bool GATE, bool RAW>
+// The row kernel's instances: exact (see the dispatch below).  8 waves where two workgroups share a CU's 160 KB of
+// LDS and for single attention's blocks of 128 queries, else 16: four waves per
+// SIMD either way.
+hipError_t launch_attention_rows(const PairAttnArgs& a, bool exact, int64_t items, int max_keys,
+                                 hipStream_t s) {
+  if (a.axis == 3 || max_keys <= 640)
+    return exact ? launch_attention_rows<8, true>(a, items, max_keys, s)
+                 : launch_attention_rows<8, false>(a, items, max_keys, s);
+  return launch_attention_rows<16, true>(a, items, max_keys, s);   // past kAttnLongLen: exact
+}
+
+template <bool GATE, bool EXACT>
 hipError_t launch_pair_instance(const PairAttnArgs& a, dim3 grid, hipStream_t s) {
   const size_t smem = sizeof(bf16) * 4 * (size_t)kAttnShortLen * 32;
-  const hipError_t e = hipFuncSetAttribute((const void*)attention_pair_kernel<kAttnShortLen, 16, GATE, RAW>,
+  const hipError_t e = hipFuncSetAttribute((const void*)attention_pair_kernel<kAttnShortLen, 16, GATE, EXACT>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
   if (e != hipSuccess) return e;
-  attention_pair_kernel<kAttnShortLen, 16, GATE, RAW><<<grid, dim3(1024), smem, s>>>(a);
+  attention_pair_kernel<kAttnShortLen, 16, GATE, EXACT><<<grid, dim3(1024), smem, s>>>(a);
   return hipGetLastError();
 }
 }  // namespace
@@ -1402,42 +1461,35 @@ hipError_t launch_attention(const nt_layout& L, int axis, int H, int D, const vo
   // on the persistent one 118 us; with the line at 320 or 400 the row kernel
   // and that instance took 416 and 406 us together.
   const bool longer = L.max_len > kAttnShortLen;
+  // EXACT instances for batches with samples past kAttnLongLen, whose bias stays
+  // fp32.
+  const bool exact = L.max_len > kAttnLongLen;
   const int64_t ld_max = std::max(std::max(ld_qkv, ld_o), gate ? ld_gate : 0);
-  // Past kAttnLongLen the bias image keeps the bias as it is and the kernels
-  // multiply it by 1 / scale in fp32, so the score is as exact as where the
-  // per-row kernel adds the gathered bias; the running maximum is taken before
-  // the scale, so scales that are zero, negative or too small to divide by
-  // stay with the per-row kernel.  The multiplication costs 1 % (gated column
-  // attention layer of a B = 16 batch up to 586: 1030 -> 1042 us).
-  const bool raw = L.max_len > kAttnLongLen;
-  const bool rows_ok = (!bias || workspace) && 32 * ld_max * L.max_len < (int64_t(1) << 32) &&
-                       (!raw || scale >= 1e-6f);
+  const bool rows_ok = (!bias || workspace) && 32 * ld_max * L.max_len < (int64_t(1) << 32);
   if (D == 32 && (axis == 3 || (axis <= 1 && (!longer || rows_ok)))) {
     const int64_t tiles = L.bias_tiles_total();
     const uint2* img = nullptr;
     if (bias && tiles > 0) {
-      // the caller's workspace receives the bias image
-      const hipError_t e = launch_bias_image(L, axis, H, bias, ld_bias, ld_bias_head, raw ? 1.f : 1.f / scale, workspace,
-                                             s);
+      // The caller's workspace receives the bias image.  A finite value stays
+      // finite where it is divided by the scale, or multiplied by log2(e) in fp32.
+      const float mul = exact ? 1.f : 1.f / scale, limit = exact ? 2.33e38f : kMaxBf16;
+      const hipError_t e = launch_bias_image(L, axis, H, bias, ld_bias, ld_bias_head, mul, limit, workspace, s);
       if (e != hipSuccess) return e;
       img = (const uint2*)workspace;
     }
     PairAttnArgs a{axis, (const bf16*)q, (const bf16*)k, (const bf16*)v, ld_qkv, (const bf16*)bias, ld_bias,
                    ld_bias_head, scale * kLog2e, (bf16*)o, ld_o, L.d_sattn_work, L.d_cu_seqlens, L.d_cu_pairs, H,
-                   img, 1.f / scale, tiles * 64, L.d_bias_tiles, L.batch, L.d_cu_short,
+                   img, tiles * 64, L.d_bias_tiles, L.batch, L.d_cu_short,
                    reinterpret_cast<const int64_t*>(L.d_cu_short_cost), L.short_cost(), (const bf16*)gate, ld_gate};
+    const int keys = (L.max_len + 63) & ~63;
     if (axis == 3) {
       // the 1-D attention's (sample, 128-query block) items
-      if (L.sattn_items() == 0) return hipSuccess;
-      return launch_attention_rows<8>(a, false, L.sattn_items(), (L.max_len + 63) & ~63, s);
+      return L.sattn_items() == 0 ? hipSuccess : launch_attention_rows(a, exact, L.sattn_items(), keys, s);
     }
     if (longer) {
       PairAttnArgs al = a;
       al.work = L.d_lattn_work;
-      const int keys = (L.max_len + 63) & ~63;
-      // 8 waves where two workgroups share a CU's 160 KB of LDS, else 16: four waves per SIMD either way
-      const hipError_t e = keys <= 640 ? launch_attention_rows<8>(al, raw, L.lattn_items(), keys, s)
-                                       : launch_attention_rows<16>(al, raw, L.lattn_items(), keys, s);
+      const hipError_t e = launch_attention_rows(al, exact, L.lattn_items(), keys, s);
       if (e != hipSuccess) return e;
     }
     if (L.short_rows() == 0) return hipSuccess;
@@ -1445,7 +1497,7 @@ hipError_t launch_attention(const nt_layout& L, int axis, int H, int D, const vo
     // XCD a multiple of H workgroups, at least H, so every head gets an equal
     // share of each XCD's rows
     const dim3 gridp((unsigned)(std::max(H, compute_units() / kXcds / H * H) * kXcds));
-    if (raw && img)
+    if (exact)
       return gate ? launch_pair_instance<true, true>(a, gridp, s) : launch_pair_instance<false, true>(a, gridp, s);
     return gate ? launch_pair_instance<true, false>(a, gridp, s) : launch_pair_instance<false, false>(a, gridp, s);
   }

@@ -558,9 +558,9 @@ hipError_t launch_attention_backward(const nt_layout& L, int axis, int H, const 
     char* img = static_cast<char*>(workspace) + images_offset(L, H);
     a.img_q = reinterpret_cast<const uint2*>(img);
     a.img_k = reinterpret_cast<const uint2*>(img + bias_image_bytes(L, H));
-    hipError_t e = launch_bias_image(L, axis, H, bias, ld_bias, ld_bias_head, 1.f, (void*)a.img_q, s);
+    hipError_t e = launch_bias_image(L, axis, H, bias, ld_bias, ld_bias_head, 1.f, kMaxBf16, (void*)a.img_q, s);
     // by keys: the image of the transposed bias
-    if (e == hipSuccess) e = launch_bias_image(L, 1 - axis, H, bias, ld_bias, ld_bias_head, 1.f, (void*)a.img_k, s);
+    if (e == hipSuccess) e = launch_bias_image(L, 1 - axis, H, bias, ld_bias, ld_bias_head, 1.f, kMaxBf16, (void*)a.img_k, s);
     if (e != hipSuccess) return e;
   }
   const int nt_max = (L.max_len + 31) / 32 * 2;

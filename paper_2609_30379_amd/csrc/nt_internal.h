@@ -221,10 +221,12 @@ hipError_t launch_attention_backward(const nt_layout& L, int axis, int H, const 
                                      size_t workspace_bytes, hipStream_t s);
 
 // Image of a pair bias (k_attention.hip, bias_image_kernel): bias(j, k) *
-// mul rounded to bf16, in the lanes' register order, -inf past N.
+// mul, finite values within +-limit, rounded to bf16, in the lanes' register
+// order, -inf past N.
+constexpr float kMaxBf16 = 3.3895313892515355e38f;
 size_t bias_image_bytes(const nt_layout& L, int H);
 hipError_t launch_bias_image(const nt_layout& L, int axis, int H, const void* bias, int64_t ld_bias,
-                             int64_t ld_bias_head, float mul, void* img, hipStream_t s);
+                             int64_t ld_bias_head, float mul, float limit, void* img, hipStream_t s);
 
 // Bias-image bytes that a pair attention call must be given (0: none), and
 // those of its fastest path: a call with a sample longer than kAttnLongLen
