@@ -454,7 +454,8 @@ __device__ __forceinline__ f32x4 log2_scores(f32x4 S, float scale_log2, f32x4 bi
 //     two buffers, the next row's copies in flight while the current row
 //     runs: one barrier per row;
 //   * the softmax denominator comes from one more matrix-core product with a
-//     ones operand, on the same bf16 probabilities as the numerator.
+//     ones operand, on the same bf16 probabilities as the numerator (EXACT:
+//     from the fp32 weights, added per lane).
 // Scores are kept transposed (S^T = K Q^T), so a lane holds 16 keys of one
 // query per 64-key chunk and the running max is mostly lane-local.
 template <int NMAX, int NW, bool GATE, bool EXACT>
@@ -641,6 +642,7 @@ __global__ void __launch_bounds__(64 * NW, 4) attention_pair_kernel(PairAttnArgs
     for (int kt = 0; kt < KT16; ++kt) asm volatile("" : "+v"(bias_r[kt].x), "+v"(bias_r[kt].y));
     float m_s = -INFINITY;                        // running max of bias/scale + q.k (EXACT: of the log2 score)
     bool far = true;                              // some lane's m_s is -inf or beyond kFarMax
+    float l_s = 0.f;                              // EXACT: this lane's part of the row sum
     f32x4 O[3];                                   // dims 0-15, 16-31, row sum
 #pragma unroll
     for (int u = 0; u < 3; ++u) O[u] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -687,8 +689,9 @@ __global__ void __launch_bounds__(64 * NW, 4) attention_pair_kernel(PairAttnArgs
           const float alpha = rescale(m_s, m_new, EXACT ? 1.f : c);
           m_s = m_new;
           far = __any(fabsf(m_s) > kFarMax);
+          l_s *= alpha;
 #pragma unroll
-          for (int u = 0; u < 3; ++u) O[u] *= alpha;
+          for (int u = 0; u < (EXACT ? 2 : 3); ++u) O[u] *= alpha;
         }
         float nm = EXACT ? (m_s == -INFINITY ? 0.f : -m_s) : -m_s * c;
         if (!EXACT && far) {
@@ -703,6 +706,7 @@ __global__ void __launch_bounds__(64 * NW, 4) attention_pair_kernel(PairAttnArgs
 #pragma unroll
           for (int ii = 0; ii < 4; ++ii) {
             const float w = __builtin_amdgcn_exp2f(EXACT ? S[kt][ii] + nm : fmaf(S[kt][ii], c, nm));
+            if constexpr (EXACT) l_s += w;
             P[kt >> 1][(kt & 1) * 4 + ii] = (bf16)w;
           }
         const bf16x8 ones = ones_bf16x8();
@@ -712,17 +716,17 @@ __global__ void __launch_bounds__(64 * NW, 4) attention_pair_kernel(PairAttnArgs
           v_frags2(Vb, SC * 4 + pp, vf);
           O[0] = mfma16(vf[0], P[pp], O[0]);
           O[1] = mfma16(vf[1], P[pp], O[1]);
-          O[2] = mfma16(ones, P[pp], O[2]);
+          if constexpr (!EXACT) O[2] = mfma16(ones, P[pp], O[2]);
           O[0] = mfma16(vf[2], P[pp + 1], O[0]);
           O[1] = mfma16(vf[3], P[pp + 1], O[1]);
-          O[2] = mfma16(ones, P[pp + 1], O[2]);
+          if constexpr (!EXACT) O[2] = mfma16(ones, P[pp + 1], O[2]);
         }
         if constexpr ((NT / 2) % 2 == 1) {
           bf16x8 vf[2];
           v_frags1(Vb, SC * 4 + NT / 2 - 1, vf);
           O[0] = mfma16(vf[0], P[NT / 2 - 1], O[0]);
           O[1] = mfma16(vf[1], P[NT / 2 - 1], O[1]);
-          O[2] = mfma16(ones, P[NT / 2 - 1], O[2]);
+          if constexpr (!EXACT) O[2] = mfma16(ones, P[NT / 2 - 1], O[2]);
         }
       };
       // keys left at super-chunk SC: more than 96 take all 8 tiles (the
@@ -745,7 +749,7 @@ __global__ void __launch_bounds__(64 * NW, 4) attention_pair_kernel(PairAttnArgs
       // 4g .. 4g+7 and an odd one 16 + 4(g-1) .. +7: one 16-byte store per
       // lane instead of two 8-byte ones (each store instruction gathers 16
       // cells and holds the texture-address unit the copies also need)
-      const float inv = 1.f / O[2][0];
+      const float inv = 1.f / (EXACT ? sum_over_kgroups(l_s) : O[2][0]);
       uint32_t ow[2][2];
 #pragma unroll
       for (int dt = 0; dt < 2; ++dt) {
@@ -813,8 +817,9 @@ __global__ void __launch_bounds__(64 * NW, 4) attention_pair_kernel(PairAttnArgs
 // and weights of 0.
 //
 // EXACT instances read the bias itself and form scale S + bias in log2 units
-// in fp32 (any scale, and no rounding of bias / scale): one more vector
-// instruction per score.
+// in fp32 (any scale, and no rounding of bias / scale), and the denominator is
+// the sum of the fp32 weights: two more vector instructions per score, two
+// matrix-core products less per chunk.
 template <int W, bool GATE, bool BIAS, bool EXACT>
 __global__ void __launch_bounds__(64 * W, 4) attention_row_kernel(PairAttnArgs p) {
   constexpr int D = 32;
@@ -884,6 +889,7 @@ __global__ void __launch_bounds__(64 * W, 4) attention_row_kernel(PairAttnArgs p
   const bf16x8 ones = ones_bf16x8();
   float m_s = -INFINITY, nm = 0.f;                      // running maximum of bias/scale + q.k, and -m_s sc (0 where far)
   bool far = true;                                      // some lane's m_s is -inf or beyond kFarMax
+  float l_s = 0.f;                                      // EXACT: this lane's part of the row sum
   f32x4 O[3];                                           // dims 0-15, 16-31, row sum
   // one step with the bias in b; the next step's bias is read into bn.
   // Returns false after the last step.
@@ -896,6 +902,7 @@ __global__ void __launch_bounds__(64 * W, 4) attention_row_kernel(PairAttnArgs p
       m_s = -INFINITY;
       nm = 0.f;
       far = true;
+      l_s = 0.f;
 #pragma unroll
       for (int u = 0; u < 3; ++u) O[u] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
@@ -941,8 +948,9 @@ __global__ void __launch_bounds__(64 * W, 4) attention_row_kernel(PairAttnArgs p
       m_s = m_new;
       far = __any(fabsf(m_s) > kFarMax);
       nm = EXACT ? (m_s == -INFINITY ? 0.f : -m_s) : far ? 0.f : -m_s * sc;
+      l_s *= alpha;
 #pragma unroll
-      for (int u = 0; u < 3; ++u) O[u] *= alpha;
+      for (int u = 0; u < (EXACT ? 2 : 3); ++u) O[u] *= alpha;
     }
     if (!EXACT && far) {
       const float ms = m_s == -INFINITY ? 0.f : m_s;
@@ -955,6 +963,7 @@ __global__ void __launch_bounds__(64 * W, 4) attention_row_kernel(PairAttnArgs p
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const float w = __builtin_amdgcn_exp2f(EXACT ? S[t][e] + nm : fmaf(S[t][e], sc, nm));
+        if constexpr (EXACT) l_s += w;
         P[t >> 1][(t & 1) * 4 + e] = (bf16)w;
       }
 #pragma unroll
@@ -963,12 +972,12 @@ __global__ void __launch_bounds__(64 * W, 4) attention_row_kernel(PairAttnArgs p
       row_tr_frags(lds0 + kt0 + (uint32_t)(nt * 1024 + u * 2048) + to, vf);
       O[0] = mfma16(vf[0], P[u], O[0]);
       O[1] = mfma16(vf[1], P[u], O[1]);
-      O[2] = mfma16(ones, P[u], O[2]);
+      if constexpr (!EXACT) O[2] = mfma16(ones, P[u], O[2]);
     }
     if (last) {
       // lane (l16, g) holds dims 4g .. 4g+3 and 16 + 4g .. +3 of its query;
       // the rows g, g ^ 1 trade halves so that every lane stores 16 bytes
-      const float inv = 1.f / O[2][0];
+      const float inv = 1.f / (EXACT ? sum_over_kgroups(l_s) : O[2][0]);
       uint32_t ow[2][2];
 #pragma unroll
       for (int dt = 0; dt < 2; ++dt) {
@@ -1461,8 +1470,8 @@ hipError_t launch_attention(const nt_layout& L, int axis, int H, int D, const vo
   // on the persistent one 118 us; with the line at 320 or 400 the row kernel
   // and that instance took 416 and 406 us together.
   const bool longer = L.max_len > kAttnShortLen;
-  // EXACT instances for batches with samples past kAttnLongLen, whose bias stays
-  // fp32.
+  // EXACT instances for batches with samples past kAttnLongLen, whose bias and
+  // softmax denominator stay fp32.
   const bool exact = L.max_len > kAttnLongLen;
   const int64_t ld_max = std::max(std::max(ld_qkv, ld_o), gate ? ld_gate : 0);
   const bool rows_ok = (!bias || workspace) && 32 * ld_max * L.max_len < (int64_t(1) << 32);

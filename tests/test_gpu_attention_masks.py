@@ -1,7 +1,8 @@
 """Pair attention where the bias leaves the ordinary range: finite masks from
 -1e9 to the lowest bf16 value on whole leading chunks of keys and on whole rows,
 and -inf on leading chunks, for samples on each side of 256 and of 512 keys (axes
-0 and 1) and for single attention (axis 3)."""
+0 and 1) and for single attention (axis 3); past 512 the softmax denominator is
+the sum of the fp32 weights."""
 import functools
 
 import numpy as np
@@ -96,3 +97,35 @@ def test_masked_chunks(L, H, axis):
             b[whole] = value
         check(_call(list(L), H, axis, x, b), _masked_reference(L, H, axis, bool(finite)), "bf16",
               f"masked attention axis {axis} {L} mask {value:g}")
+
+
+@pytest.mark.parametrize("L", [[520], [648, 200]])
+def test_denominator_past_512_sums_fp32_weights(L):
+    """Zero queries: an eighth of the keys have weight 1 and values v, the others
+    weight exp(b) and value 0, where bf16 rounds exp(b) by 0.4 %.  The output is
+    v n1 / (n1 + n2 w) up to fp32 errors; with rounded weights in the
+    denominator it is up to 0.3 % larger, more than half of bf16's rounding
+    interval of many of the 32 values."""
+    b = -1.359375                              # exp(b) = 0.256821, in bf16 0.255859
+    w, wr = np.exp(b), 0.255859375
+    R = sum(n * n for n in L)
+    x = np.zeros((R, 4 * D))
+    bias = np.full((R, 1), b)
+    v = synth.snap_bf16(np.linspace(0.5, 1.0, D, endpoint=False).astype(np.float32)).astype(np.float64)
+    o, want, rounded = 0, [], []
+    for n in L:
+        n1 = n // 8
+        vals = np.zeros((n, n, D))
+        vals[:, :n1] = v
+        x[o:o + n * n, 2 * D:3 * D] = vals.reshape(-1, D)
+        bias[o:o + n * n].reshape(n, n)[:, :n1] = 0.0
+        for f, ww in ((want, w), (rounded, wr)):
+            f.append(np.broadcast_to(v * n1 / (n1 + (n - n1) * ww), (n * n, D)))
+        o += n * n
+    want, rounded = np.concatenate(want), np.concatenate(rounded)
+    snap = lambda t: synth.snap_bf16(t.astype(np.float32)).astype(np.float64)      # noqa: E731
+    # off the boundary between two bf16 values by more than any fp32 error, the result is exact
+    clear = snap(want * (1 + 2.0 ** -18)) == snap(want * (1 - 2.0 ** -18))
+    assert np.mean(clear & (snap(want) != snap(rounded))) > 0.2
+    got = _call(L, 1, 0, x, bias)
+    assert np.array_equal(got[clear], snap(want)[clear])
