@@ -1471,8 +1471,9 @@ hipError_t launch_attention(const nt_layout& L, int axis, int H, int D, const vo
   // and that instance took 416 and 406 us together.
   const bool longer = L.max_len > kAttnShortLen;
   // EXACT instances for batches with samples past kAttnLongLen, whose bias and
-  // softmax denominator stay fp32.
-  const bool exact = L.max_len > kAttnLongLen;
+  // softmax denominator stay fp32, and for scales that are zero, negative or too
+  // small to divide the bias by (the others take the maximum before the scale).
+  const bool exact = L.max_len > kAttnLongLen || !(scale >= 1e-6f);
   const int64_t ld_max = std::max(std::max(ld_qkv, ld_o), gate ? ld_gate : 0);
   const bool rows_ok = (!bias || workspace) && 32 * ld_max * L.max_len < (int64_t(1) << 32);
   if (D == 32 && (axis == 3 || (axis <= 1 && (!longer || rows_ok)))) {

@@ -1,8 +1,9 @@
-"""Pair attention where the bias leaves the ordinary range: finite masks from
--1e9 to the lowest bf16 value on whole leading chunks of keys and on whole rows,
-and -inf on leading chunks, for samples on each side of 256 and of 512 keys (axes
-0 and 1) and for single attention (axis 3); past 512 the softmax denominator is
-the sum of the fp32 weights."""
+"""Pair attention where the bias or the scale leaves the ordinary range: finite
+masks from -1e9 to the lowest bf16 value on whole leading chunks of keys and on
+whole rows, -inf on leading chunks, scales that are zero, negative or too small
+to divide by, for samples on each side of 256 and of 512 keys (axes 0 and 1) and
+for single attention (axis 3); past 512 the softmax denominator is the sum of
+the fp32 weights."""
 import functools
 
 import numpy as np
@@ -97,6 +98,22 @@ def test_masked_chunks(L, H, axis):
             b[whole] = value
         check(_call(list(L), H, axis, x, b), _masked_reference(L, H, axis, bool(finite)), "bf16",
               f"masked attention axis {axis} {L} mask {value:g}")
+
+
+@pytest.mark.parametrize("scale", [0.0, -0.2, 1e-7])
+@pytest.mark.parametrize("L,H,axis,kw", [
+    ((200, 20), 2, 0, {}), ((200, 20), 2, 1, dict(gate=True)), ((130,), 1, 0, dict(bias=False)),
+    ((300, 20), 1, 0, dict(gate=True)), ((300, 20), 1, 1, {}), ((300,), 1, 1, dict(bias=False)),
+    ((514, 20), 1, 0, {}),
+    ((140, 300), 2, 3, {}), ((140, 300), 2, 3, dict(bias=False)),
+])
+def test_scales(L, H, axis, kw, scale):
+    x, bv = _inputs(L, H, axis)
+    if not kw.get("bias", True):
+        bv = None
+    gate = kw.get("gate", False)
+    check(_call(list(L), H, axis, x, bv, scale, gate), _reference(list(L), H, axis, x, bv, scale, gate), "bf16",
+          f"attention axis {axis} {L} scale {scale} {kw}")
 
 
 @pytest.mark.parametrize("L", [[520], [648, 200]])
