@@ -820,7 +820,8 @@ __global__ void __launch_bounds__(64 * NW, 4) attention_pair_kernel(PairAttnArgs
 // in fp32 (any scale, and no rounding of bias / scale), and the denominator is
 // the sum of the fp32 weights: two more vector instructions per score, two
 // matrix-core products less per chunk.
-template <int W, bool GATE, bool BIAS, bool EXACT>
+// WIDE instances take 64-bit offsets within a tile of 16 rows.
+template <int W, bool GATE, bool BIAS, bool EXACT, bool WIDE>
 __global__ void __launch_bounds__(64 * W, 4) attention_row_kernel(PairAttnArgs p) {
   constexpr int D = 32;
   extern __shared__ __attribute__((aligned(16))) bf16 lds[];
@@ -843,12 +844,13 @@ __global__ void __launch_bounds__(64 * W, 4) attention_row_kernel(PairAttnArgs p
   const int64_t base = single ? uni(p.cu_seqlens[i]) : p.axis == 0 ? cu + (int64_t)r * n : cu + r;
   const int64_t st = p.axis == 1 ? n : 1;
   // rows of tile `tile` (16 elements of the pair row): a uniform 64-bit base
-  // and a 32-bit byte offset per lane (the launcher checks that 16 rows span
-  // less than 4 GB); rows (and whole tiles) past N repeat rows below N
+  // and a 32-bit byte offset per lane (16 rows span less than 4 GB, else WIDE);
+  // rows (and whole tiles) past N repeat rows below N
   auto at = [&](const bf16* b, int tile, int row_in_tile, int64_t ld, int dim) {
     tile = min(tile, (n - 1) >> 4);
     const int rl = min(row_in_tile, n - 1 - 16 * tile);
     const char* u = reinterpret_cast<const char*>(b + (int64_t)(16 * tile) * st * ld);
+    if constexpr (WIDE) return u + ((int64_t)rl * st * ld + dim) * 2;
     return u + ((uint32_t)rl * (uint32_t)(st * ld) + (uint32_t)dim) * 2u;
   };
   const int64_t qoff = base * p.ld_qkv + h * D;
@@ -1397,35 +1399,37 @@ hipError_t launch_cross_attention(const nt_layout& Lq, const nt_layout& Lkv, int
 }
 
 namespace {
-template <int W, bool GATE, bool BIAS, bool EXACT>
+template <int W, bool GATE, bool BIAS, bool EXACT, bool WIDE>
 hipError_t launch_row_instance(const PairAttnArgs& a, dim3 grid, size_t smem, hipStream_t s) {
-  const hipError_t e = hipFuncSetAttribute((const void*)attention_row_kernel<W, GATE, BIAS, EXACT>,
+  const hipError_t e = hipFuncSetAttribute((const void*)attention_row_kernel<W, GATE, BIAS, EXACT, WIDE>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
   if (e != hipSuccess) return e;
-  attention_row_kernel<W, GATE, BIAS, EXACT><<<grid, dim3(64 * W), smem, s>>>(a);
+  attention_row_kernel<W, GATE, BIAS, EXACT, WIDE><<<grid, dim3(64 * W), smem, s>>>(a);
   return hipGetLastError();
 }
 
-template <int W, bool EXACT>
+template <int W, bool EXACT, bool WIDE>
 hipError_t launch_attention_rows(const PairAttnArgs& a, int64_t items, int max_keys, hipStream_t s) {
   const dim3 grid((unsigned)(items * a.H));
   const size_t smem = (size_t)max_keys * 128;
   if (!a.bias_img)
-    return a.gate ? launch_row_instance<W, true, false, EXACT>(a, grid, smem, s)
-                  : launch_row_instance<W, false, false, EXACT>(a, grid, smem, s);
-  return a.gate ? launch_row_instance<W, true, true, EXACT>(a, grid, smem, s)
-                : launch_row_instance<W, false, true, EXACT>(a, grid, smem, s);
+    return a.gate ? launch_row_instance<W, true, false, EXACT, WIDE>(a, grid, smem, s)
+                  : launch_row_instance<W, false, false, EXACT, WIDE>(a, grid, smem, s);
+  return a.gate ? launch_row_instance<W, true, true, EXACT, WIDE>(a, grid, smem, s)
+                : launch_row_instance<W, false, true, EXACT, WIDE>(a, grid, smem, s);
 }
 
-// The row kernel's instances: exact (see the dispatch below).  8 waves where two workgroups share a CU's 160 KB of
+// The row kernel's instances: exact (see the dispatch below) and wide (64-bit
+// offsets, always exact).  8 waves where two workgroups share a CU's 160 KB of
 // LDS and for single attention's blocks of 128 queries, else 16: four waves per
 // SIMD either way.
-hipError_t launch_attention_rows(const PairAttnArgs& a, bool exact, int64_t items, int max_keys,
+hipError_t launch_attention_rows(const PairAttnArgs& a, bool exact, bool wide, int64_t items, int max_keys,
                                  hipStream_t s) {
+  if (wide) return launch_attention_rows<16, true, true>(a, items, max_keys, s);
   if (a.axis == 3 || max_keys <= 640)
-    return exact ? launch_attention_rows<8, true>(a, items, max_keys, s)
-                 : launch_attention_rows<8, false>(a, items, max_keys, s);
-  return launch_attention_rows<16, true>(a, items, max_keys, s);   // past kAttnLongLen: exact
+    return exact ? launch_attention_rows<8, true, false>(a, items, max_keys, s)
+                 : launch_attention_rows<8, false, false>(a, items, max_keys, s);
+  return launch_attention_rows<16, true, false>(a, items, max_keys, s);   // past kAttnLongLen: exact
 }
 
 template <bool GATE, bool EXACT>
@@ -1461,22 +1465,24 @@ hipError_t launch_attention(const nt_layout& L, int axis, int H, int D, const vo
     return hipGetLastError();
   }
   // Samples longer than kAttnShortLen go to the row kernel, the others to the
-  // persistent one.  The row kernel wants the bias image in the workspace and
-  // 32-bit lane offsets (16 rows of a tensor within 4 GB); without either the
-  // per-row kernel below takes the batch.  The line is where one workgroup of
+  // persistent one; the row kernel reads the bias from the image in the
+  // workspace, and without one the per-row kernel below takes a batch that has
+  // longer samples.  The line is where one workgroup of
   // 16 waves stops covering a row's queries: splitting the keys of longer rows
   // between wave pairs of a persistent instance took 412 us on the four-block
   // stack (N 48..420), its rows past 256 on the row kernel 221 us and the rest
   // on the persistent one 118 us; with the line at 320 or 400 the row kernel
   // and that instance took 416 and 406 us together.
   const bool longer = L.max_len > kAttnShortLen;
+  // 16 rows of a tile, 2 bytes an element, past 4 GB
+  const int64_t ld_max = std::max(std::max(ld_qkv, ld_o), gate ? ld_gate : 0);
+  const bool wide = 32 * ld_max * (axis == 1 ? L.max_len : 1) >= (int64_t(1) << 32);
   // EXACT instances for batches with samples past kAttnLongLen, whose bias and
   // softmax denominator stay fp32, and for scales that are zero, negative or too
-  // small to divide the bias by (the others take the maximum before the scale).
-  const bool exact = L.max_len > kAttnLongLen || !(scale >= 1e-6f);
-  const int64_t ld_max = std::max(std::max(ld_qkv, ld_o), gate ? ld_gate : 0);
-  const bool rows_ok = (!bias || workspace) && 32 * ld_max * L.max_len < (int64_t(1) << 32);
-  if (D == 32 && (axis == 3 || (axis <= 1 && (!longer || rows_ok)))) {
+  // small to divide the bias by (the others take the maximum before the scale);
+  // the wide ones are always exact.
+  const bool exact = wide || L.max_len > kAttnLongLen || !(scale >= 1e-6f);
+  if (D == 32 && (axis == 3 || (axis <= 1 && (!longer || !bias || workspace)))) {
     const int64_t tiles = L.bias_tiles_total();
     const uint2* img = nullptr;
     if (bias && tiles > 0) {
@@ -1494,12 +1500,12 @@ hipError_t launch_attention(const nt_layout& L, int axis, int H, int D, const vo
     const int keys = (L.max_len + 63) & ~63;
     if (axis == 3) {
       // the 1-D attention's (sample, 128-query block) items
-      return L.sattn_items() == 0 ? hipSuccess : launch_attention_rows(a, exact, L.sattn_items(), keys, s);
+      return L.sattn_items() == 0 ? hipSuccess : launch_attention_rows(a, exact, wide, L.sattn_items(), keys, s);
     }
     if (longer) {
       PairAttnArgs al = a;
       al.work = L.d_lattn_work;
-      const hipError_t e = launch_attention_rows(al, exact, L.lattn_items(), keys, s);
+      const hipError_t e = launch_attention_rows(al, exact, wide, L.lattn_items(), keys, s);
       if (e != hipSuccess) return e;
     }
     if (L.short_rows() == 0) return hipSuccess;

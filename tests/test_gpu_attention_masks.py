@@ -146,3 +146,16 @@ def test_denominator_past_512_sums_fp32_weights(L):
     assert np.mean(clear & (snap(want) != snap(rounded))) > 0.2
     got = _call(L, 1, 0, x, bias)
     assert np.array_equal(got[clear], snap(want)[clear])
+
+
+def test_row_strides_past_4_gb():
+    """Sixteen rows of a tile span more than 4 GB: a row every 3 x 2^27 bytes."""
+    import torch
+    from paper_2609_30379_amd import binding as B
+    L, H = [3, 17], 1
+    x, bv = _inputs(L, H, 3)
+    rows = torch.empty((sum(L), 3 << 26), dtype=torch.bfloat16, device="cuda")[:, :4 * D]
+    rows[:, :3 * D] = dev(x[:, :3 * D], "bf16")
+    B.nt_pair_row_attention(B.NestedLayout(L), 3, H, D, rows[:, :D], rows[:, D:2 * D], rows[:, 2 * D:3 * D], rows[:, 3 * D:],
+                            bias=dev(np.ascontiguousarray(bv.T), "bf16"), bias_layout="heads")
+    check(host(rows[:, 3 * D:].contiguous()), _reference(L, H, 3, x, bv), "bf16", "single attention, row stride 3 x 2^26")
