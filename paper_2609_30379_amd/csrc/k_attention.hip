@@ -216,7 +216,7 @@ struct PairAttnArgs {
   const uint2* bias_img; // bias image (see bias_image_kernel) or NULL for no bias
   int64_t img_head;      // uint2 entries per head of the image
   const int32_t* bias_tiles;
-  int batch;             // samples (persistent instance: rows are found from cu_seqlens)
+  int batch;             // samples (persistent instance: rows are found from cu_short and cu_cost)
   const int32_t* cu_short;   // persistent instance: prefix of the short samples' rows and of their cost
   const int64_t* cu_cost;
   int64_t total_cost;
@@ -248,12 +248,13 @@ struct BiasImgArgs {
   const int32_t* cu_pairs;
 };
 
-// One wave per four key tiles of a query tile (the tile count of a sample is a
-// multiple of four).  Where the keys of a query are adjacent (axes 0 and 3, unit
-// cell stride) a lane reads its four values at once, at whatever 2-byte
+// One wave per U (1 or 4) key tiles of a query tile (the tile count of a sample
+// is a multiple of four).  Where the keys of a query are adjacent (axes 0 and 3,
+// unit cell stride) a lane reads its four values at once, at whatever 2-byte
 // boundary they start: 12 heads of N 32..512, B = 8 took 27 us value by value.
+template <int U>
 __global__ void __launch_bounds__(256) bias_image_kernel(BiasImgArgs p) {
-  const int64_t tile = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * 4;
+  const int64_t tile = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * U;
   if (tile >= p.tiles) return;
   const int h = blockIdx.y, lane = threadIdx.x & 63, l16 = lane & 15, g = lane >> 4;
   int lo = 0, hi = p.batch - 1;                 // sample: largest i with bias_tiles[i] <= tile
@@ -268,9 +269,9 @@ __global__ void __launch_bounds__(256) bias_image_kernel(BiasImgArgs p) {
   const int j = (t / kti) * 16 + l16, kt0 = (t % kti) * 16 + 4 * g;
   const bf16* bh = p.bias + (int64_t)h * p.ld_bias_head + (int64_t)p.cu_pairs[i] * p.ld_bias;
   const bool adjacent = p.axis != 1 && p.ld_bias == 1;
-  bf16x4 raw[4];
+  bf16x4 raw[U];
 #pragma unroll
-  for (int u = 0; u < 4; ++u) {
+  for (int u = 0; u < U; ++u) {
     const int k0 = kt0 + 16 * u;
     raw[u] = bf16x4{};
     if (adjacent && j < n && k0 + 4 <= n) {
@@ -284,7 +285,7 @@ __global__ void __launch_bounds__(256) bias_image_kernel(BiasImgArgs p) {
     }
   }
 #pragma unroll
-  for (int u = 0; u < 4; ++u) {
+  for (int u = 0; u < U; ++u) {
     bf16x4 o;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -472,50 +473,68 @@ __global__ void __launch_bounds__(64 * NW, 4) attention_pair_kernel(PairAttnArgs
   const int l16 = lane & 15, g = lane >> 4;
 
   // ---- rows of this workgroup, [row, row_end) of one head (one workgroup per
-  // CU): XCD x takes the x-th eighth of the cost of all short samples' rows, and
-  // its workgroups split that range among the heads, workgroup k taking head
-  // k % H and the (k / H)-th of the equal slices of that head (crossing sample
-  // boundaries), so the heads of a row run on one XCD together.  A row costs
-  // its 16-key tiles plus kAttnRowCost for what does not depend on its length.
-  // Rows are counted by rows[], where longer samples have none.
+  // CU): the rows of all short samples are cut into 8 M slices of equal cost
+  // (attn_row_cost, crossing sample boundaries).  XCD x takes the x-th M of
+  // them for every head, its workgroup k head k % H and slice k / H, so the
+  // heads of a row run on one XCD together.  Rows are counted by rows[], where
+  // longer samples have none.  The cuts are rounded once, to the nearest row:
+  // cutting the XCDs' shares first and those into slices gave one workgroup 28
+  // rows where 27 suffice (B=8, N 208..222).
   const int32_t* rows = p.cu_short;
-  const int x = blockIdx.x % kXcds, k = blockIdx.x / kXcds, per = (int)(gridDim.x / kXcds);
+  const int x = blockIdx.x % kXcds, k = blockIdx.x / kXcds;
   const int h = __builtin_amdgcn_readfirstlane(k % p.H), m = __builtin_amdgcn_readfirstlane(k / p.H);
-  const int M = (per - h + p.H - 1) / p.H;
-  const int64_t total = p.total_cost;
-  const int64_t xa = total * x / kXcds, xb = total * (x + 1) / kXcds;
-  // xa + (xb - xa) q / M, in 32 bits where they suffice (a 64-bit division costs about a microsecond)
-  auto slice = [&](int q) -> int64_t {
-    if (total < (int64_t(1) << 26)) return xa + (int64_t)((uint32_t)(xb - xa) * (uint32_t)q / (uint32_t)M);
-    return xa + (xb - xa) * q / M;
+  const int M = __builtin_amdgcn_readfirstlane((int)(gridDim.x / kXcds) / p.H);   // the grid is a multiple of 8 H
+  const int slice = x * M + m;
+  // total_cost q / (8 M), in 32 bits where they suffice (a 64-bit division costs about a microsecond)
+  auto cost_at = [&](int q) -> int64_t {
+    if (p.total_cost * (kXcds * M) < (int64_t(1) << 32)) return (uint32_t)p.total_cost * (uint32_t)q / (uint32_t)(kXcds * M);
+    return p.total_cost * q / (kXcds * M);
+  };
+  // The table entries of the sample at cost t, found by the lanes together: 64
+  // entries a step, one step for batches up to 63, and both ends of the slice
+  // side by side.  A dependent load is most of a microsecond of a small call: with
+  // two bisections the launch took 124 us instead of 122 at B=8, N 208..222, and
+  // 112 instead of 110 on the four-block stack's samples.
+  struct Window { int lo; int64_t cost; int rows, pairs, tiles; };
+  auto window = [&](int64_t t) {
+    int lo = 0;
+    for (int cnt = p.batch; cnt > 63;) {        // the sample is one of cnt from lo on
+      const int step = (cnt + 63) / 64;
+      const bool le = lane * step < cnt && p.cu_cost[lo + lane * step] <= t;
+      const int j = __popcll(__ballot(le)) - 1;
+      lo += j * step;
+      cnt = min(step, cnt - j * step);
+    }
+    const int at = min(lo + lane, p.batch);
+    return Window{lo, p.cu_cost[at], rows[at], p.cu_pairs[at], p.bias_tiles[at]};
   };
   // the row boundary nearest to cost t: index r0 of sample i, which has n0 rows
-  // counted from first and its cells from cu0 (every table entry is read once
-  // and side by side: a dependent load is most of a microsecond of a small call)
-  int i = 0, n0, first, r0, cu0;
-  auto row_at = [&](int64_t t) {
-    int lo = 0, hi = p.batch;                   // cu_cost[lo] <= t, t < cu_cost[hi] (or hi = batch)
-    while (hi - lo > 1) {
-      const int mid = (lo + hi) >> 1;
-      if (p.cu_cost[mid] <= t) lo = mid;
-      else hi = mid;
-    }
-    i = __builtin_amdgcn_readfirstlane(lo);
-    first = rows[i];
-    n0 = rows[i + 1] - first;
-    cu0 = p.cu_pairs[i];
-    const int w = (n0 + 15) / 16 + kAttnRowCost;
-    r0 = min(n0, (int)(((uint32_t)(t - p.cu_cost[i]) + (uint32_t)w / 2u) / (uint32_t)w));
+  // counted from first, its cells from cu0 and its image tiles from bt0
+  int i, n0, first, r0, cu0, bt0;
+  auto row_at = [&](int64_t t, const Window& w) {
+    const int j = __builtin_amdgcn_readfirstlane(__popcll(__ballot(lane < 63 && w.lo + lane < p.batch && w.cost <= t)) - 1);
+    i = w.lo + j;
+    first = __builtin_amdgcn_readlane(w.rows, j);
+    n0 = __builtin_amdgcn_readlane(w.rows, j + 1) - first;
+    cu0 = __builtin_amdgcn_readlane(w.pairs, j);
+    bt0 = __builtin_amdgcn_readlane(w.tiles, j);
+    // within one sample, whose cost fits 32 bits
+    const int c = (int)((uint32_t)t - (uint32_t)__builtin_amdgcn_readlane((int)w.cost, j)) - kAttnSampleCost;
+    const uint32_t u = (uint32_t)attn_row_cost(n0);
+    r0 = min(n0, (int)(((uint32_t)max(c, 0) + u / 2u) / u));
   };
-  row_at(slice(m + 1));
+  const int64_t ta = cost_at(slice), tb = cost_at(slice + 1);
+  const Window wa = window(ta), wb = window(tb);
+  row_at(tb, wb);
   const int64_t row_end = first + r0;
-  row_at(slice(m));
+  row_at(ta, wa);
   int64_t row = first + r0;
   if (row >= row_end) return;
   if (r0 == n0) {                               // the first row of the next non-empty sample
     do ++i; while (rows[i + 1] <= row);
     n0 = rows[i + 1] - (int)row;
     cu0 = p.cu_pairs[i];
+    bt0 = p.bias_tiles[i];
     r0 = 0;
   }
   i = __builtin_amdgcn_readfirstlane(i);
@@ -574,7 +593,7 @@ __global__ void __launch_bounds__(64 * NW, 4) attention_pair_kernel(PairAttnArgs
   // lane's bias: query 16*wave + l16, keys 16*kt + 4g .. +3 of every key
   // tile, read from the bias image (one contiguous 512 bytes per wave and tile)
   uint2 bias_r[KT16];
-  auto set_sample = [&](int si, int sn, int64_t scu) {
+  auto set_sample = [&](int tiles, int sn, int64_t scu) {
     n = sn;
     cu = scu;
     sr = p.axis == 0 ? n : 1;
@@ -583,14 +602,14 @@ __global__ void __launch_bounds__(64 * NW, 4) attention_pair_kernel(PairAttnArgs
     qvalid = jw < n;
     const int kti = ((n + 63) & ~63) / 16;
     const uint2* img = p.bias_img && wave_has_queries
-                           ? p.bias_img + h * p.img_head + ((int64_t)p.bias_tiles[si] + (int64_t)wave * kti) * 64 + lane
+                           ? p.bias_img + h * p.img_head + (tiles + (int64_t)wave * kti) * 64 + lane
                            : nullptr;
 #pragma unroll
     for (int kt = 0; kt < KT16; ++kt) {
       bias_r[kt] = img && kt < kti ? img[kt * 64] : make_uint2(0u, 0u);
     }
   };
-  set_sample(i, __builtin_amdgcn_readfirstlane(n0), __builtin_amdgcn_readfirstlane(cu0));
+  set_sample(__builtin_amdgcn_readfirstlane(bt0), __builtin_amdgcn_readfirstlane(n0), __builtin_amdgcn_readfirstlane(cu0));
   int r = __builtin_amdgcn_readfirstlane(r0);
   bf16x8 qf = load_q(n, cu, r);
   dma_kv(n, cu, r, Kb0, Vb0);
@@ -606,7 +625,7 @@ __global__ void __launch_bounds__(64 * NW, 4) attention_pair_kernel(PairAttnArgs
     // the next row: same sample, or the first row of the next non-empty one
     // (sample extents are read only when the sample changes: a global load
     // here would make the wave wait for every copy and store in flight)
-    int i2 = i, r2 = r + 1, n2 = n;
+    int i2 = i, r2 = r + 1, n2 = n, bt2 = 0;
     int64_t cu2 = cu;
     if (more && r2 >= n) {
       i2 = i + 1;
@@ -614,10 +633,12 @@ __global__ void __launch_bounds__(64 * NW, 4) attention_pair_kernel(PairAttnArgs
       r2 = 0;
       n2 = rows[i2 + 1] - rows[i2];
       cu2 = p.cu_pairs[i2];
+      bt2 = p.bias_tiles[i2];
     }
     i2 = __builtin_amdgcn_readfirstlane(i2);
     r2 = __builtin_amdgcn_readfirstlane(r2);
     n2 = __builtin_amdgcn_readfirstlane(n2);
+    bt2 = __builtin_amdgcn_readfirstlane(bt2);
     cu2 = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(cu2 >> 32)) << 32) |
                     (uint32_t)__builtin_amdgcn_readfirstlane((int)cu2));
     // gate of this lane's outputs (GATE): issued before the next row's
@@ -641,7 +662,7 @@ __global__ void __launch_bounds__(64 * NW, 4) attention_pair_kernel(PairAttnArgs
 #pragma unroll
     for (int kt = 0; kt < KT16; ++kt) asm volatile("" : "+v"(bias_r[kt].x), "+v"(bias_r[kt].y));
     float m_s = -INFINITY;                        // running max of bias/scale + q.k (EXACT: of the log2 score)
-    bool far = true;                              // some lane's m_s is -inf or beyond kFarMax
+    bool far = false;                             // some lane's m_s is -inf or beyond kFarMax
     float l_s = 0.f;                              // EXACT: this lane's part of the row sum
     f32x4 O[3];                                   // dims 0-15, 16-31, row sum
 #pragma unroll
@@ -683,8 +704,10 @@ __global__ void __launch_bounds__(64 * NW, 4) attention_pair_kernel(PairAttnArgs
         // the reference max moves only when some query's max grew by more
         // than 8 (log2 units): probabilities then stay below 2^8, and most
         // super-chunks skip rescaling the accumulators
-        constexpr float kUnits = 8.f;
-        if (__any((EXACT ? mloc - m_s : (mloc - m_s) * c) > kUnits)) {
+        if constexpr (SC == 0) {                  // the row's first: nothing to rescale
+          m_s = mloc;
+          far = __any(fabsf(m_s) > kFarMax);
+        } else if (__any((EXACT ? mloc - m_s : (mloc - m_s) * c) > 8.f)) {
           const float m_new = fmaxf(m_s, mloc);
           const float alpha = rescale(m_s, m_new, EXACT ? 1.f : c);
           m_s = m_new;
@@ -780,14 +803,11 @@ __global__ void __launch_bounds__(64 * NW, 4) attention_pair_kernel(PairAttnArgs
         *reinterpret_cast<uint4*>(orow + d0) = make_uint4(ow[0][0], ow[0][1], ow[1][0], ow[1][1]);
       }
     }
+    // bias of the next sample, landed before the back edge, so the loop head has
+    // no load pending and waits for none of the next row's copies
+    if (i2 != i) set_sample(bt2, n2, cu2);
     __builtin_amdgcn_s_waitcnt(0);              // copies for the next row have landed
     __syncthreads();
-    if (i2 != i) {                              // bias of the next sample
-      set_sample(i2, n2, cu2);
-      // landed before the back edge, so the loop head has no load pending
-      // and waits for none of the next row's copies
-      __builtin_amdgcn_s_waitcnt(0);
-    }
     i = i2;
     r = r2;
     qf = qn;
@@ -1329,7 +1349,11 @@ hipError_t launch_bias_image(const nt_layout& L, int axis, int H, const void* bi
   if (tiles == 0) return hipSuccess;
   BiasImgArgs b{axis, L.batch, (const bf16*)bias, ld_bias, ld_bias_head, mul, limit, (uint2*)img, tiles,
                 L.d_bias_tiles, L.d_cu_seqlens, L.d_cu_pairs};
-  bias_image_kernel<<<dim3((unsigned)((tiles + 15) / 16), (unsigned)H), dim3(256), 0, s>>>(b);
+  // A tile per wave where all of them are in flight at once (256 CUs, 32 waves
+  // each): 832 tiles took 3.8 us against 4.7 with four per wave, 7168 tiles 5.0
+  // against 5.6, 32400 tiles (12 heads, N 32..512, B = 8) 20.1 against 14.8.
+  if (tiles * H <= 8192) bias_image_kernel<1><<<dim3((unsigned)((tiles + 3) / 4), (unsigned)H), dim3(256), 0, s>>>(b);
+  else bias_image_kernel<4><<<dim3((unsigned)((tiles + 15) / 16), (unsigned)H), dim3(256), 0, s>>>(b);
   return hipGetLastError();
 }
 

@@ -212,7 +212,7 @@ nt_status plan_layout(const int32_t* lengths, int32_t batch, nt_layout* L, const
   for (int32_t i = 0; i < batch; ++i) {
     const int32_t n = lengths[i] <= kAttnShortLen ? lengths[i] : 0;
     L->cu_short[i + 1] = L->cu_short[i] + n;
-    cost[i + 1] = cost[i] + (int64_t)n * ((n + 15) / 16 + kAttnRowCost);
+    cost[i + 1] = cost[i] + (n ? (int64_t)n * attn_row_cost(n) + kAttnSampleCost : 0);
   }
   L->cu_short_cost.assign(2 * (size_t)(batch + 1), 0);
   std::memcpy(L->cu_short_cost.data(), cost.data(), cost.size() * sizeof(int64_t));

@@ -19,7 +19,13 @@ constexpr int kSeqQBlock = 64;    // 1-D attention: queries per workgroup
 constexpr int kLinRows = 128;     // rows per projection workgroup (pair-row table granularity)
 constexpr int kAttnQB = 128;      // pair attention (head_dim 32): queries per workgroup (8 waves x 16)
 constexpr int kAttnShortLen = 256;  // longest sample of the persistent pair attention and of the 256-key 1-D kernel
-constexpr int kAttnRowCost = 4;     // persistent pair attention: cost of a row besides its 16-key tiles, in tiles
+// Persistent pair attention: cost of a pair row of N <= kAttnShortLen, in units
+// of 0.13 us.  Its N / 16 waves take turns on four SIMDs and walk the keys 32 at
+// a time, and a row's barrier, copies and stores take eight units at any length
+// (measured at 4 heads: 1.1, 1.3, 2.0, 2.15, 3.05, 3.55, 4.5 and 5.2 us for
+// ceil(N / 32) = 1 .. 8).
+constexpr int attn_row_cost(int n) { return (n + 63) / 64 * ((n + 31) / 32) + 8; }
+constexpr int kAttnSampleCost = 18;   // and of going on to the next sample's bias
 constexpr int kAttnLongLen = 512;   // longest sample of the 512-key instances (axes 2 and 3, cross-attention)
 
 // Samples whose tables the pair-tiled projection kernels cache in LDS.
@@ -57,7 +63,7 @@ struct nt_layout {
   int32_t tri_xcd_items = 0;         // largest item count of one XCD
   std::vector<int32_t> seq_work;     // pairs (sample, query block); count multiple of 8
   std::vector<int32_t> cu_short;     // [B+1] prefix of N_i over the samples up to kAttnShortLen (0 for longer ones)
-  std::vector<int32_t> cu_short_cost;  // [B+1] int64 prefix of their rows' cost, N_i (ceil(N_i/16) + kAttnRowCost)
+  std::vector<int32_t> cu_short_cost;  // [B+1] int64 prefix of their rows' cost, N_i attn_row_cost(N_i) + kAttnSampleCost
   std::vector<int32_t> bias_tiles;   // [B+1] prefix of ceil(N_i/16) * round_up(N_i,64)/16: bias image tiles
   std::vector<int32_t> sattn_work;   // 1-D attention: quads (sample, first 16-query tile, 0, tile count)
   std::vector<int32_t> blk_prow;     // [ceil(sum N^2 / kLinRows)] pair row holding cell kLinRows*b
