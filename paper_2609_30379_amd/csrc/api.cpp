@@ -62,7 +62,7 @@ nt_status upload(nt_layout* L, hipStream_t s) {
       {&L->cu_short_cost, &L->d_cu_short_cost}, {&L->bias_tiles, &L->d_bias_tiles},
       {&L->sattn_work, &L->d_sattn_work},
       {&L->bc_cu_tiles, &L->d_bc_cu_tiles},
-      {&L->cu_qblk, &L->d_cu_qblk},       {&L->tri_split, &L->d_tri_split},
+      {&L->cu_bgrad, &L->d_cu_bgrad},       {&L->tri_split, &L->d_tri_split},
       {&L->cu_cols, &L->d_cu_cols},       {&L->col_sample, &L->d_col_sample},
   };
   size_t total = 0;

@@ -23,8 +23,10 @@
 // The vector units bound the rows kernel: per score it spends about 16 vector
 // instructions on the 3-way splits and one exponential in each of three
 // passes (statistics, dQ, dK/dV), against 30 products per 512 scores.  At
-// B=8, N 66..317, 4 heads: 568 us; one thread per query or key with fp32 FMAs
+// B=8, N 66..317, 4 heads: 500 us; one thread per query or key with fp32 FMAs
 // took 12.2 ms (and the bias gradient 5.8 ms).
+#include <algorithm>
+
 #include "nt_device.h"
 #include "nt_internal.h"
 
@@ -55,6 +57,7 @@ struct AttnBwdArgs {
   float* dsum;                         // workspace: D, same layout
   int64_t cells;                       // sum N^2
   const int32_t* work;                 // (sample, row) pairs; -1 = idle
+  int64_t row_blocks;                  // workgroups of the rows kernel: work positions x heads
   const int32_t* cu_seqlens;
   const int32_t* cu_pairs;
   // bias images (IMG instances): tile (a, b) of head h at
@@ -63,7 +66,18 @@ struct AttnBwdArgs {
   const uint2* img_k;                  // lane l16 + 16 g: bias(16 b + 4 g + e, 16 a + l16)
   int64_t img_tiles;
   const int32_t* bias_tiles;
+  const int32_t* cu_bgrad;             // [batch + 1] prefix of the bias-gradient blocks of one head
+  int batch;
 };
+
+// Workgroups of a launch, in rows of at most kGridX: HIP refuses a launch whose
+// grid x times the block size reaches 2^32.  kGridX is a multiple of 8, so
+// workgroup id still runs on XCD id % 8.
+constexpr int64_t kGridX = 1 << 21;
+dim3 folded_grid(int64_t blocks) {
+  return dim3((unsigned)std::min(blocks, kGridX), (unsigned)((blocks + kGridX - 1) / kGridX));
+}
+__device__ __forceinline__ uint32_t block_id() { return blockIdx.y * gridDim.x + blockIdx.x; }
 
 // a value that is the same in all lanes, as a scalar
 __device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
@@ -142,7 +156,7 @@ __device__ __forceinline__ float bias_at(const AttnBwdArgs& p, int64_t cu, int n
   return (float)p.bias[cell * p.ld_bias + (int64_t)h * p.ld_bias_head];
 }
 
-// sum over the four lanes l16 + 16 g (g = 0..3)
+// maximum over the four lanes l16 + 16 g (g = 0..3)
 __device__ __forceinline__ float max_over_kgroups(float v) {
   const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
   v = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
@@ -181,7 +195,9 @@ __global__ void __launch_bounds__(64 * NW, 4) attn_bwd_rows_kernel(AttnBwdArgs p
   extern __shared__ __attribute__((aligned(16))) bf16 lds[];
   // workgroup 8 (H k + h) + x runs on XCD x: the heads of a pair row, which
   // share cache lines, run on one XCD one after the other
-  const int x = blockIdx.x % kXcds, t0 = blockIdx.x / kXcds;
+  const uint32_t id = block_id();
+  if (id >= p.row_blocks) return;
+  const int x = id % kXcds, t0 = id / kXcds;
   // everything derived from the block index is the same in all lanes: kept in scalars
   const int h = uni(t0 % p.H), pos = uni(t0 / p.H) * kXcds + x;
   const int i = uni(p.work[2 * pos]), r = uni(p.work[2 * pos + 1]);
@@ -365,10 +381,12 @@ __global__ void __launch_bounds__(64 * NW, 4) attn_bwd_rows_kernel(AttnBwdArgs p
 // Bias gradient: workgroup = (sample, head, 64 queries, 64 keys), 8 waves of
 // 16 x 32 sums each.  It walks all pair rows; a row's 64 q, dO, k and v rows
 // (16 KB) and softmax statistics are copied into one of kBiasStages LDS
-// stages, kBiasStages - 1 rows ahead, with one barrier per row.  The items of
-// a sample are cut into eight equal stretches, one per XCD, ordered by head,
+// stages, kBiasStages - 1 rows ahead, with one barrier per row.  The blocks of
+// all samples are cut into eight equal stretches, one per XCD, head after head,
 // so the rows that the workgroups of an XCD walk together come from its own
-// L2.  The texture-address unit bounds it (each copy instruction gathers 16
+// L2, and a batch launches the blocks that it has (the longest sample's number
+// for every sample took 239 us instead of 224 at B=8, N 66..317, 4 heads, and
+// passed a launch's limit on batches of one long and thousands of short ones).  The texture-address unit bounds it (each copy instruction gathers 16
 // rows of 64 bytes), so operands are shared by 64 x 64 blocks: a wave loading
 // its own 16 x 64 block straight into registers took 761 us at B=8,
 // N 66..317, 4 heads (2.5 KB per 256 scores instead of 1 KB, and every row's
@@ -388,18 +406,25 @@ __device__ __forceinline__ void wait_vm(int left) {
   }
 }
 
-__global__ void __launch_bounds__(512, 4) attn_bwd_bias_kernel(AttnBwdArgs p, int nb, int chunk, float* partial) {
+__global__ void __launch_bounds__(512, 4) attn_bwd_bias_kernel(AttnBwdArgs p, int chunk, float* partial) {
   __shared__ __attribute__((aligned(16))) unsigned char stages[kBiasStages * kBiasStageBytes];
-  const int i = uni(blockIdx.x / nb), blk = uni(blockIdx.x % nb);   // nb workgroups per sample, a multiple of 8
+  // item x S + k of head h runs on XCD x: equal stretches of the samples' (row
+  // chunk, query block, key block) lists, numbered for one chunk per 64 rows
+  const int total = p.cu_bgrad[p.batch], per = (total + kXcds - 1) / kXcds;
+  const uint32_t id = block_id(), t0 = id / kXcds;
+  const int h = uni(t0 / per), slot = uni(t0 - h * per), item = (int)(id % kXcds) * per + slot;
+  if (h >= p.H || item >= total) return;
+  int lo = 0, hi = p.batch - 1;                           // sample: largest i with cu_bgrad[i] <= item
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (p.cu_bgrad[mid] <= item) lo = mid; else hi = mid - 1;
+  }
+  const int i = uni(lo);
   const int n = uni(p.cu_seqlens[i + 1] - p.cu_seqlens[i]);
   const int nq = (n + kBiasBlk - 1) / kBiasBlk;
-  const int nc = uni((n + chunk - 1) / chunk);
-  const int items = p.H * nc * nq * nq;                   // (head, row chunk, query block, key block)
-  const int per = (items + kXcds - 1) / kXcds;
-  const int slot = blk / kXcds, item = (blk % kXcds) * per + slot;
-  if (slot >= per || item >= items) return;
-  const int hc = uni(item / (nq * nq)), h = uni(hc / nc), rc = hc - h * nc;
-  const int qk = item - hc * nq * nq, qb = uni(qk / nq);
+  const int li = uni(item - p.cu_bgrad[i]), rc = uni(li / (nq * nq));
+  if (rc * chunk >= n) return;                            // chunks of more than 64 rows: fewer of them
+  const int qk = li - rc * nq * nq, qb = uni(qk / nq);
   const int j0 = qb * kBiasBlk, k0 = (qk - qb * nq) * kBiasBlk;
   const int r_first = rc * chunk, r_end = min(n, r_first + chunk);
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
@@ -498,10 +523,10 @@ __global__ void __launch_bounds__(512, 4) attn_bwd_bias_kernel(AttnBwdArgs p, in
 }
 
 // Sums the row chunks' partials of every cell and head in chunk order.
-__global__ void __launch_bounds__(256) bias_grad_sum_kernel(AttnBwdArgs p, int batch, int chunk, const float* partial) {
+__global__ void __launch_bounds__(256) bias_grad_sum_kernel(AttnBwdArgs p, int chunk, const float* partial) {
   const int64_t cell = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (cell >= p.cells) return;
-  int lo = 0, hi = batch - 1;                             // sample: largest i with cu_pairs[i] <= cell
+  int lo = 0, hi = p.batch - 1;                           // sample: largest i with cu_pairs[i] <= cell
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
     if (p.cu_pairs[mid] <= cell) lo = mid; else hi = mid - 1;
@@ -513,12 +538,13 @@ __global__ void __launch_bounds__(256) bias_grad_sum_kernel(AttnBwdArgs p, int b
 }
 
 template <int NW>
-hipError_t launch_rows(const AttnBwdArgs& a, int nt_max, unsigned grid, size_t smem, hipStream_t s) {
+hipError_t launch_rows(const AttnBwdArgs& a, int nt_max, size_t smem, hipStream_t s) {
   const void* fn = a.img_q ? (const void*)attn_bwd_rows_kernel<NW, true> : (const void*)attn_bwd_rows_kernel<NW, false>;
   const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
   if (e != hipSuccess) return e;
-  if (a.img_q) attn_bwd_rows_kernel<NW, true><<<dim3(grid), dim3(64 * NW), smem, s>>>(a, nt_max);
-  else attn_bwd_rows_kernel<NW, false><<<dim3(grid), dim3(64 * NW), smem, s>>>(a, nt_max);
+  const dim3 grid = folded_grid(a.row_blocks);
+  if (a.img_q) attn_bwd_rows_kernel<NW, true><<<grid, dim3(64 * NW), smem, s>>>(a, nt_max);
+  else attn_bwd_rows_kernel<NW, false><<<grid, dim3(64 * NW), smem, s>>>(a, nt_max);
   return hipGetLastError();
 }
 
@@ -548,7 +574,8 @@ hipError_t launch_attention_backward(const nt_layout& L, int axis, int H, const 
   AttnBwdArgs a{axis, H, (const bf16*)q, (const bf16*)k, (const bf16*)v, ld_qkv, (const bf16*)bias, ld_bias,
                 ld_bias_head, (const bf16*)dout, ld_dout, scale, (bf16*)dq, (bf16*)dk,
                 (bf16*)dv, ld_dqkv, dbias, ld_dbias, ld_dbias_head, lse, lse + L.sum_n2 * H, L.sum_n2, L.d_attn_work,
-                L.d_cu_seqlens, L.d_cu_pairs, nullptr, nullptr, L.bias_tiles_total(), L.d_bias_tiles};
+                L.attn_items() * H, L.d_cu_seqlens, L.d_cu_pairs, nullptr, nullptr, L.bias_tiles_total(), L.d_bias_tiles,
+                L.d_cu_bgrad, L.batch};
   // A workspace of the full size also holds two bias images, so that both
   // phases read the bias as whole 512-byte tiles, and the bias gradient's
   // partial sums; with one of the minimum size (statistics only) every score
@@ -565,22 +592,21 @@ hipError_t launch_attention_backward(const nt_layout& L, int axis, int H, const 
   }
   const int nt_max = (L.max_len + 31) / 32 * 2;
   const size_t smem = (size_t)nt_max * (4 * 1024 + 2 * 16 * sizeof(float));
-  const unsigned grid = (unsigned)(L.attn_items() * H);
   // Waves per workgroup: as many as keep four waves on each SIMD with the
   // workgroups that fit a CU's 160 KB of LDS, and no more than the tiles.
-  hipError_t e = nt_max <= 8 ? launch_rows<4>(a, nt_max, grid, smem, s)
-                 : smem <= 80 * 1024 ? launch_rows<8>(a, nt_max, grid, smem, s)
-                                     : launch_rows<16>(a, nt_max, grid, smem, s);
+  hipError_t e = nt_max <= 8 ? launch_rows<4>(a, nt_max, smem, s)
+                 : smem <= 80 * 1024 ? launch_rows<8>(a, nt_max, smem, s)
+                                     : launch_rows<16>(a, nt_max, smem, s);
   if (e != hipSuccess || !dbias) return e;
-  const int64_t nq = (L.max_len + kBiasBlk - 1) / kBiasBlk;
   const int chunk = full ? kBiasChunk : kAttnLongLen, nc = (L.max_len + chunk - 1) / chunk;
   float* partial = nc > 1 ? reinterpret_cast<float*>(static_cast<char*>(workspace) + images_offset(L, H) + 2 * bias_image_bytes(L, H))
                           : nullptr;
-  const int64_t nb = (nq * nq * nc * H + kXcds - 1) / kXcds * kXcds;   // workgroups of the longest sample
-  attn_bwd_bias_kernel<<<dim3((unsigned)(nb * L.batch)), dim3(512), 0, s>>>(a, (int)nb, chunk, partial);
+  static_assert(kBiasBlk == kBgradBlock && kBiasChunk == kBgradBlock, "cu_bgrad counts blocks of 64 queries, keys and rows");
+  const int64_t blocks = (int64_t)(L.cu_bgrad.back() + kXcds - 1) / kXcds * kXcds * H;
+  attn_bwd_bias_kernel<<<folded_grid(blocks), dim3(512), 0, s>>>(a, chunk, partial);
   e = hipGetLastError();
   if (e != hipSuccess || !partial) return e;
-  bias_grad_sum_kernel<<<dim3((unsigned)((L.sum_n2 + 255) / 256), (unsigned)H), dim3(256), 0, s>>>(a, L.batch, chunk, partial);
+  bias_grad_sum_kernel<<<dim3((unsigned)((L.sum_n2 + 255) / 256), (unsigned)H), dim3(256), 0, s>>>(a, chunk, partial);
   return hipGetLastError();
 }
 

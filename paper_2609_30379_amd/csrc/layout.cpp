@@ -186,9 +186,13 @@ nt_status plan_layout(const int32_t* lengths, int32_t batch, nt_layout* L, const
     }
   }
 
-  // 16-query blocks of every sample (bias gradient of the pair attention)
-  L->cu_qblk.assign(batch + 1, 0);
-  for (int32_t i = 0; i < batch; ++i) L->cu_qblk[i + 1] = L->cu_qblk[i] + (lengths[i] + 15) / 16;
+  // blocks of the attention bias gradient (64 queries x 64 keys x 64 pair rows;
+  // at most sum N^2 or max N / 2^18 times it, so within int32)
+  L->cu_bgrad.assign(batch + 1, 0);
+  for (int32_t i = 0; i < batch; ++i) {
+    const int32_t b = (lengths[i] + kBgradBlock - 1) / kBgradBlock;
+    L->cu_bgrad[i + 1] = L->cu_bgrad[i] + b * b * b;
+  }
 
   // pair-row attention: one item per (sample, pair row), cost N_i^2; and the
   // same for the samples longer than kAttnShortLen alone

@@ -26,6 +26,7 @@ constexpr int kAttnShortLen = 256;  // longest sample of the persistent pair att
 // ceil(N / 32) = 1 .. 8).
 constexpr int attn_row_cost(int n) { return (n + 63) / 64 * ((n + 31) / 32) + 8; }
 constexpr int kAttnSampleCost = 18;   // and of going on to the next sample's bias
+constexpr int kBgradBlock = 64;     // attention bias gradient: queries, keys and pair rows per block
 constexpr int kAttnLongLen = 512;   // longest sample of the 512-key instances (axes 2 and 3, cross-attention)
 
 // Samples whose tables the pair-tiled projection kernels cache in LDS.
@@ -68,7 +69,7 @@ struct nt_layout {
   std::vector<int32_t> sattn_work;   // 1-D attention: quads (sample, first 16-query tile, 0, tile count)
   std::vector<int32_t> blk_prow;     // [ceil(sum N^2 / kLinRows)] pair row holding cell kLinRows*b
   std::vector<int32_t> bc_cu_tiles;  // [B+1] prefix of N_i * ceil(N_i/16): broadcast tiles (16 cells of one pair row)
-  std::vector<int32_t> cu_qblk;      // [B+1] prefix of ceil(N_i/16): 16-query blocks (attention bias gradient)
+  std::vector<int32_t> cu_bgrad;     // [B+1] prefix of ceil(N_i/64)^3: bias-gradient blocks of one head
 
   bool has_device = false;
   int device = -1;
@@ -89,7 +90,7 @@ struct nt_layout {
   const int32_t* d_bias_tiles = nullptr;
   const int32_t* d_sattn_work = nullptr;
   const int32_t* d_bc_cu_tiles = nullptr;
-  const int32_t* d_cu_qblk = nullptr;
+  const int32_t* d_cu_bgrad = nullptr;
   const int32_t* d_tri_split = nullptr;
   const int32_t* d_cu_cols = nullptr;
   const int32_t* d_col_sample = nullptr;

@@ -20,6 +20,7 @@ CASES = [
     ([127, 128], 1),                   # the 4-wave instance at its limit
     ([129, 5, 161], 2),                # the 8-wave instance
     ([330], 1),                        # the 16-wave instance
+    ([512, 1], 1),                     # its longest sample: most LDS, eight row chunks
 ]
 
 

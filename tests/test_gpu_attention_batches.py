@@ -1,5 +1,6 @@
 """Pair attention on batches of many samples: the persistent forward kernel finds
-its rows among more than one step of samples, empty ones between them."""
+its rows among more than one step of samples, empty ones between them, and the
+backward's launches hold one long and very many short samples."""
 import numpy as np
 import pytest
 
@@ -42,3 +43,36 @@ def test_forward_many_samples(axis, L):
                             bias=dev(np.ascontiguousarray(bias.T), "bf16"), bias_layout="heads")
     ref = O.pair_row_attention(x[:, :c], x[:, c:2 * c], x[:, 2 * c:], bias, L, H, D, axis=axis)
     check(host(out), ref, "bf16", f"attention axis {axis}, {len(L)} samples of up to {max(L)}")
+
+
+@pytest.mark.parametrize("images", [True, False])
+def test_backward_one_long_and_many_short_samples(images):
+    """512 and 360000 samples of one element, 12 heads: 4.3 million workgroups of
+    16 waves, more than one row of a grid holds.  A sample of one element has
+    weight 1, so dv = dout and the other gradients are 0; the long sample's are
+    those of a batch of its own, to the bit."""
+    import torch
+    from paper_2609_30379_amd import binding as B
+    H, n, many = 12, 512, 360000
+    c, R = H * D, n * n + many
+    g = torch.Generator(device="cuda").manual_seed(1)
+    normal = lambda *s: torch.randn(*s, generator=g, device="cuda").to(torch.bfloat16)     # noqa: E731
+    qkv, dout, bias = normal(R, 3 * c), normal(R, c), normal(R, H)
+
+    def run(L, rows):
+        lay = B.NestedLayout(L)
+        nbytes = B.attention_backward_workspace_bytes(lay, 0, H, D) if images else 8 * H * rows
+        x, dqkv = qkv[:rows], torch.full((rows, 3 * c), float("nan"), dtype=torch.bfloat16, device="cuda")
+        dbias = torch.full((rows, H), float("nan"), device="cuda")
+        B.nt_pair_row_attention_backward(lay, 0, H, D, x[:, :c], x[:, c:2 * c], x[:, 2 * c:], dout[:rows], dqkv[:, :c],
+                                         dqkv[:, c:2 * c], dqkv[:, 2 * c:], bias=bias[:rows], dbias=dbias,
+                                         workspace=B.workspace_tensor(nbytes))
+        return dqkv, dbias
+
+    dqkv, dbias = run([n] + [1] * many, R)
+    alone, alone_bias = run([n], n * n)
+    assert torch.equal(dqkv[:n * n], alone) and torch.equal(dbias[:n * n], alone_bias)
+    short = dqkv[n * n:]
+    assert torch.equal(short[:, 2 * c:], dout[n * n:])
+    # dS = P (dP - D) with D = P dP / P: equal up to the last bit of dP, |dP| < 64
+    assert float(short[:, :2 * c].abs().max()) < 1e-3 and float(dbias[n * n:].abs().max()) < 1e-4
