@@ -230,7 +230,9 @@ struct PairAttnArgs {
 // bias(j, k) * mul, j = 16 qt + l16, k = 16 kt + 4 g .. +3, each rounded to
 // bf16 -- exactly the register image the attention lanes keep.  Finite values
 // stay within +-limit, so a finite mask is still finite where it is multiplied
-// (by mul here or in fp32 later); infinities and NaN pass.  Keys past N hold
+// (by mul here or in fp32 later); infinities and NaN pass.  A wave looks at its
+// values one by one only if one is past `far`: checking each took 15.0 us
+// instead of 14.1 at 12 heads, N 32..512, B = 8.  Keys past N hold
 // -inf (for queries inside N), so the scores they seed are masked without
 // further work; queries past N hold 0.
 // bias(j, k) is the head-h bias of cell(j, k) for axis 0 and of cell(k, j)
@@ -241,6 +243,7 @@ struct BiasImgArgs {
   const bf16* bias;
   int64_t ld_bias, ld_bias_head;
   float mul, limit;
+  float far;              // values up to this size are within the limit once multiplied
   uint2* img;
   int64_t tiles;          // tiles per head
   const int32_t* bias_tiles;
@@ -284,18 +287,28 @@ __global__ void __launch_bounds__(256) bias_image_kernel(BiasImgArgs p) {
       }
     }
   }
+  f32x4 b[U];
+  bool far = false;                             // some value may pass the limit
+#pragma unroll
+  for (int u = 0; u < U; ++u)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float v = (float)raw[u][e];
+      far |= fabsf(v) > p.far;
+      b[u][e] = v * p.mul;
+    }
+  if (__builtin_expect(__any(far), 0)) {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if ((__builtin_bit_cast(uint16_t, (bf16)raw[u][e]) & 0x7f80) != 0x7f80) b[u][e] = fminf(fmaxf(b[u][e], -p.limit), p.limit);
+  }
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     bf16x4 o;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      float b = j < n ? -INFINITY : 0.f;
-      if (j < n && kt0 + 16 * u + e < n) {
-        b = (float)raw[u][e] * p.mul;
-        if ((__builtin_bit_cast(uint16_t, (bf16)raw[u][e]) & 0x7f80) != 0x7f80) b = fminf(fmaxf(b, -p.limit), p.limit);
-      }
-      o[e] = (bf16)b;
-    }
+    for (int e = 0; e < 4; ++e) o[e] = (bf16)(j >= n ? 0.f : kt0 + 16 * u + e < n ? b[u][e] : -INFINITY);
     *reinterpret_cast<bf16x4*>(&p.img[(int64_t)h * p.tiles * 64 + (tile + u) * 64 + lane]) = o;
   }
 }
@@ -1347,7 +1360,7 @@ hipError_t launch_bias_image(const nt_layout& L, int axis, int H, const void* bi
                              int64_t ld_bias_head, float mul, float limit, void* img, hipStream_t s) {
   const int64_t tiles = L.bias_tiles_total();
   if (tiles == 0) return hipSuccess;
-  BiasImgArgs b{axis, L.batch, (const bf16*)bias, ld_bias, ld_bias_head, mul, limit, (uint2*)img, tiles,
+  BiasImgArgs b{axis, L.batch, (const bf16*)bias, ld_bias, ld_bias_head, mul, limit, 0.999f * limit / mul, (uint2*)img, tiles,
                 L.d_bias_tiles, L.d_cu_seqlens, L.d_cu_pairs};
   // A tile per wave where all of them are in flight at once (256 CUs, 32 waves
   // each): 832 tiles took 3.8 us against 4.7 with four per wave, 7168 tiles 5.0
