@@ -103,7 +103,7 @@ LIN_CASES = [
     (300, 384, 256, False, "none", "bf16", "bf16", 0),
     (600, 768, 2304, True, "none", "bf16", "bf16", 0),       # large-K path (LayerNorm rows in the workspace)
     (600, 768, 3072, True, "gelu", "bf16", "bf16", 0),
-    (600, 3072, 768, False, "residual", "bf16", "bf16", 0),  # no LayerNorm, <= 8192 rows: small-row kernel
+    (600, 3072, 768, False, "residual", "bf16", "bf16", 0),  # no LayerNorm, 38 x 12 small-row blocks > 256 CUs: large-K path
     (8500, 3072, 768, False, "residual", "bf16", "bf16", 0), # no LayerNorm, > 8192 rows: large-K path
     (200, 416, 136, True, "gelu", "bf16", "bf16", 0),        # large-K path: 13 k-steps, part of a channel tile
     (257, 1024, 520, True, "residual", "bf16", "bf16", 0),   # large-K path: one row past a row tile
