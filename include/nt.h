@@ -325,10 +325,16 @@ nt_status nt_layernorm_linear_workspace(const nt_linear_args* args, uint64_t* by
  *            are positive and in elements.
  *   scale    softmax scale (e.g. 1/sqrt(d)).
  *   o        [rows, H*d] row stride ld_o.
- * Workspace: with a bias, bf16, d = 32 and every N_i <= 512 the call first
- * writes bias/scale (rounded to bf16) in the per-lane order of the attention
- * kernel into the workspace: H * T * 512 bytes with
- * T = sum_i ceil(N_i/16) * ceil(N_i/64) * 4 (nt_pair_row_attention_workspace).
+ * Workspace: with a bias, bf16, d = 32 and axis 0, 1 or 3 the call first writes
+ * an image of the bias (rounded to bf16) in the per-lane order of the attention
+ * kernels into the workspace: H * T * 512 bytes with
+ * T = sum_i ceil(N_i/16) * ceil(N_i/64) * 4.  Where every N_i <= 512 it needs
+ * them (nt_pair_row_attention_workspace).  With a longer sample it needs none,
+ * but a 16-byte aligned workspace of at least that size
+ * (nt_pair_row_attention_full_workspace) is written too and the call runs
+ * faster; a smaller or misaligned one is left as it is.  The image holds
+ * bias/scale, or the bias itself with a sample longer than 512, a scale below
+ * 1e-6 or row strides past 32-bit offsets.
  * Errors: NT_ERR_INVALID_ARG (also a missing or too small workspace),
  * NT_ERR_UNSUPPORTED (d, or N_i beyond the on-chip limit: 1024 for d=32,
  * 512 for d=64), NT_ERR_HIP.                                                 */

@@ -17,7 +17,7 @@ constexpr int kXcds = 8;          // MI355X: 8 XCDs, workgroups dispatched round
 constexpr int kTriTile = 64;      // triangle output tile: 64 x 64 cells
 constexpr int kSeqQBlock = 64;    // 1-D attention: queries per workgroup
 constexpr int kLinRows = 128;     // rows per projection workgroup (pair-row table granularity)
-constexpr int kAttnQB = 128;      // pair attention (head_dim 32): queries per workgroup (8 waves x 16)
+constexpr int kAttnQB = 128;      // attention over singles (axes 2 and 3): queries per workgroup (8 waves x 16)
 constexpr int kAttnShortLen = 256;  // longest sample of the persistent pair attention and of the 256-key 1-D kernel
 // Persistent pair attention: cost of a pair row of N <= kAttnShortLen, in units
 // of 0.13 us.  Its N / 16 waves take turns on four SIMDs and walk the keys 32 at
@@ -212,12 +212,10 @@ size_t linear_backward_workspace_bytes(const nt_linear_bwd_args& a);
 hipError_t launch_linear_backward(const nt_linear_bwd_args& a, void* ws, hipStream_t s);
 
 // Attention backward (k_attention_backward.hip): bf16, head_dim 32, axes 0
-// and 1, N_i <= 512.  Workspace: the softmax statistics of every query
-// element
-// and, for the full size, two bias images and the bias gradient's partial
-// sums; a call with at least
-// attention_backward_min_workspace_bytes(L, H) (the statistics alone) also
-// runs, gathering the bias.
+// and 1, N_i <= 512.  Workspace: the softmax statistics of every query element
+// and, at the full size (attention_backward_workspace_bytes), two bias images
+// and the bias gradient's partial sums.  A call with at least the statistics
+// (attention_backward_min_workspace_bytes) also runs, gathering the bias.
 size_t attention_backward_min_workspace_bytes(const nt_layout& L, int H);
 size_t attention_backward_workspace_bytes(const nt_layout& L, int H);
 hipError_t launch_attention_backward(const nt_layout& L, int axis, int H, const void* q, const void* k,
