@@ -23,8 +23,8 @@
 // The vector units bound the rows kernel: per score it spends about 16 vector
 // instructions on the 3-way splits and one exponential in each of three
 // passes (statistics, dQ, dK/dV), against 30 products per 512 scores.  At
-// B=8, N 66..317, 4 heads: 500 us; one thread per query or key with fp32 FMAs
-// took 12.2 ms (and the bias gradient 5.8 ms).
+// B=8, N 66..317, 4 heads: 558 us; one thread per query or key with fp32 FMAs
+// took 12.2 ms (and the bias gradient 5.8 ms, now 233 us).
 #include <algorithm>
 
 #include "nt_device.h"
@@ -386,8 +386,9 @@ __global__ void __launch_bounds__(64 * NW, 4) attn_bwd_rows_kernel(AttnBwdArgs p
 // so the rows that the workgroups of an XCD walk together come from its own
 // L2, and a batch launches the blocks that it has (the longest sample's number
 // for every sample took 239 us instead of 224 at B=8, N 66..317, 4 heads, and
-// passed a launch's limit on batches of one long and thousands of short ones).  The texture-address unit bounds it (each copy instruction gathers 16
-// rows of 64 bytes), so operands are shared by 64 x 64 blocks: a wave loading
+// passed a launch's limit on batches of one long and thousands of short ones).
+// The texture-address unit bounds it (each copy instruction gathers 16 rows of
+// 64 bytes), so operands are shared by 64 x 64 blocks: a wave loading
 // its own 16 x 64 block straight into registers took 761 us at B=8,
 // N 66..317, 4 heads (2.5 KB per 256 scores instead of 1 KB, and every row's
 // latency exposed).  With room for partial sums a workgroup walks
