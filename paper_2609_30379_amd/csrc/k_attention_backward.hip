@@ -57,7 +57,7 @@ struct AttnBwdArgs {
   float* dsum;                         // workspace: D, same layout
   int64_t cells;                       // sum N^2
   const int32_t* work;                 // (sample, row) pairs; -1 = idle
-  int64_t row_blocks;                  // workgroups of the rows kernel: work positions x heads
+  uint32_t row_blocks;                 // workgroups of the rows kernel: work positions x heads
   const int32_t* cu_seqlens;
   const int32_t* cu_pairs;
   // bias images (IMG instances): tile (a, b) of head h at
@@ -69,15 +69,6 @@ struct AttnBwdArgs {
   const int32_t* cu_bgrad;             // [batch + 1] prefix of the bias-gradient blocks of one head
   int batch;
 };
-
-// Workgroups of a launch, in rows of at most kGridX: HIP refuses a launch whose
-// grid x times the block size reaches 2^32.  kGridX is a multiple of 8, so
-// workgroup id still runs on XCD id % 8.
-constexpr int64_t kGridX = 1 << 21;
-dim3 folded_grid(int64_t blocks) {
-  return dim3((unsigned)std::min(blocks, kGridX), (unsigned)((blocks + kGridX - 1) / kGridX));
-}
-__device__ __forceinline__ uint32_t block_id() { return blockIdx.y * gridDim.x + blockIdx.x; }
 
 // a value that is the same in all lanes, as a scalar
 __device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
@@ -575,7 +566,7 @@ hipError_t launch_attention_backward(const nt_layout& L, int axis, int H, const 
   AttnBwdArgs a{axis, H, (const bf16*)q, (const bf16*)k, (const bf16*)v, ld_qkv, (const bf16*)bias, ld_bias,
                 ld_bias_head, (const bf16*)dout, ld_dout, scale, (bf16*)dq, (bf16*)dk,
                 (bf16*)dv, ld_dqkv, dbias, ld_dbias, ld_dbias_head, lse, lse + L.sum_n2 * H, L.sum_n2, L.d_attn_work,
-                L.attn_items() * H, L.d_cu_seqlens, L.d_cu_pairs, nullptr, nullptr, L.bias_tiles_total(), L.d_bias_tiles,
+                (uint32_t)(L.attn_items() * H), L.d_cu_seqlens, L.d_cu_pairs, nullptr, nullptr, L.bias_tiles_total(), L.d_bias_tiles,
                 L.d_cu_bgrad, L.batch};
   // A workspace of the full size also holds two bias images, so that both
   // phases read the bias as whole 512-byte tiles, and the bias gradient's

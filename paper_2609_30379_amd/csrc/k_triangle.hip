@@ -52,8 +52,8 @@ __global__ void __launch_bounds__(kTriThreads, 1) triangle_mfma_kernel(TriArgs p
   // holds at once then cover 8 tiles x 4 channel blocks of one sample and
   // line group: an operand row block is fetched into that L2 for all tiles
   // that use it, and each z line by the four blocks that share it.
-  const int id = blockIdx.x, xcd = id % kXcds;
-  const int u = 4 * p.groups * p.split[xcd] + id / kXcds;
+  const uint32_t id = block_id();
+  const int xcd = (int)(id % kXcds), u = 4 * p.groups * p.split[xcd] + (int)(id / kXcds);
   if (u >= 4 * p.groups * p.split[xcd + 1]) return;
   const int v = u >> 2;
   const int e = v / p.groups;                         // an item of the same sample
@@ -442,8 +442,7 @@ hipError_t contract(const nt_layout& L, int C, const void* a, const void* b, int
   TriArgs t{C, nblk, (const bf16*)a, (const bf16*)b, ld_ab, (bf16*)z, ld_z, L.d_tri_work, L.d_cu_seqlens,
             L.d_cu_pairs, L.d_cu_pad, (int)items, groups, accumulate, L.d_tri_split};
   // every XCD gets as many workgroups as the widest of the item ranges needs
-  triangle_mfma_kernel<<<dim3((unsigned)((int64_t)L.tri_xcd_items * groups * 4 * kXcds)), dim3(kTriThreads), 0,
-                         s>>>(t);
+  triangle_mfma_kernel<<<folded_grid((int64_t)L.tri_xcd_items * groups * 4 * kXcds), dim3(kTriThreads), 0, s>>>(t);
   return hipGetLastError();
 }
 

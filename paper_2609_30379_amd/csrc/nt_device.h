@@ -14,6 +14,18 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kWave = 64;
 
+// Workgroups of a launch, in rows of at most kGridX: a launch whose grid x times
+// the block size reaches 2^32 is refused, or runs with that product modulo 2^32.
+// kGridX is a multiple of 8, so workgroup id still runs on XCD id % 8.  The last
+// of several rows may hold ids past the launch's own: the kernel returns on them.
+// The row length is the constant and not gridDim.x, which every workgroup would
+// load before its first table entry.
+constexpr int64_t kGridX = 1 << 21;
+inline dim3 folded_grid(int64_t blocks) {
+  return dim3((unsigned)(blocks < kGridX ? blocks : kGridX), (unsigned)((blocks + kGridX - 1) / kGridX));
+}
+__device__ __forceinline__ uint32_t block_id() { return blockIdx.y * (uint32_t)kGridX + blockIdx.x; }
+
 // D(16x16, f32) += A(16x32, bf16) * B(32x16, bf16).  Lane l supplies A row
 // l%16 and B column l%16, each with eight k values selected by l/16; the k
 // order is the same for A and B, so any consistent k permutation gives the

@@ -1,6 +1,7 @@
 """Pair attention on batches of many samples: the persistent forward kernel finds
-its rows among more than one step of samples, empty ones between them, and the
-backward's launches hold one long and very many short samples."""
+its rows among more than one step of samples, empty ones between them, and
+launches of more than 2^32 threads: the backward of one long and very many short
+samples, attention over the tokens of very many."""
 import numpy as np
 import pytest
 
@@ -76,3 +77,17 @@ def test_backward_one_long_and_many_short_samples(images):
     assert torch.equal(short[:, 2 * c:], dout[n * n:])
     # dS = P (dP - D) with D = P dP / P: equal up to the last bit of dP, |dP| < 64
     assert float(short[:, :2 * c].abs().max()) < 1e-3 and float(dbias[n * n:].abs().max()) < 1e-4
+
+
+@pytest.mark.parametrize("axis", [2, 3])
+def test_single_attention_of_very_many_samples(axis):
+    """720000 samples of one token, 12 heads: 8.64 million workgroups of 8 waves.
+    A sample of one token has weight 1, so o = v."""
+    import torch
+    from paper_2609_30379_amd import binding as B
+    H, many = 12, 720000
+    c = H * D
+    qkv = torch.randn(many, 3 * c, generator=torch.Generator(device="cuda").manual_seed(1), device="cuda").to(torch.bfloat16)
+    out = torch.full((many, c), float("nan"), dtype=torch.bfloat16, device="cuda")
+    B.nt_pair_row_attention(B.NestedLayout([1] * many), axis, H, D, qkv[:, :c], qkv[:, c:2 * c], qkv[:, 2 * c:], out)
+    assert torch.equal(out, qkv[:, 2 * c:])

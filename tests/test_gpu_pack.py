@@ -28,3 +28,15 @@ def test_packed_operands(C, direction):
     B.nt_triangle_mul(lay, direction, wide[:, 8:8 + C], wide[:, 8 + C:8 + 2 * C], z)
     ref = O.triangle_mul(ab[:, :C], ab[:, C:], L, "incoming" if direction else "outgoing")
     check(host(z), ref, "bf16", f"packed triangle C={C} direction {direction}")
+
+
+def test_contraction_of_very_many_channels():
+    """2560000 channels of one sample: more than 2^32 threads.  Planes of ones
+    contract to N, exactly."""
+    import torch
+    from paper_2609_30379_amd import binding as B
+    C, n = 2560000, 2
+    plane = torch.ones((C, 512), dtype=torch.bfloat16, device="cuda")
+    z = torch.zeros((n * n, C), dtype=torch.bfloat16, device="cuda")
+    B.nt_triangle_mul(B.NestedLayout([n]), 0, plane, plane, z, operands="pair_tiled")
+    assert bool((z == n).all())
