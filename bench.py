@@ -48,30 +48,30 @@ F32_PEAK_TFLOPS = 157.3        # fp32 vector
 FETCH_SCALE, WRITE_SCALE = 2.0, 1.0
 COUNTERS = {  # workload: {op: (kernel source, source hash, FETCH_SIZE KiB, WRITE_SIZE KiB)}
     "pairformer4_b16_lognormal192_bf16": {
-        "attention_row": ("k_attention.hip", "44fe08d102910416", 170009 + 126648 + 8232, 92947 + 81658 + 6472),
-        "attention_col": ("k_attention.hip", "44fe08d102910416", 170009 + 126648 + 8232, 92947 + 81658 + 6472),
-        "triangle_out": ("k_triangle.hip", "3d162e104bf38648", 640494, 176054),
-        "triangle_in": ("k_triangle.hip", "3d162e104bf38648", 640494, 176054),
-        "transition": ("k_transition.hip", "79c2db8e257d22b4", 100596 + 268, 174369 + 384),
-        "attn_proj": ("k_linear.hip", "14457045c3846305", 87681, 528988),
-        "tri_proj": ("k_linear.hip", "14457045c3846305", 87862, 386304),
-        "attn_out_residual": ("k_linear.hip", "14457045c3846305", 174597, 174375),
-        "pair_broadcast": ("k_segment.hip", "0217588212ab0b83", 68896, 174369),
-        "segment_mean": ("k_segment.hip", "0217588212ab0b83", 87298, 1492),
-        "single_proj": ("k_gemm.hip", "6824a37919ed8fe0", 1938, 1492),
-        "single_update": ("k_linear.hip", "14457045c3846305", 6023, 2237),
+        "attention_row": ("k_attention.hip", "49363e3c9ff6fa70", 170330 + 126647 + 8232, 92944 + 81658 + 6472),
+        "attention_col": ("k_attention.hip", "49363e3c9ff6fa70", 170330 + 126647 + 8232, 92944 + 81658 + 6472),
+        "triangle_out": ("k_triangle.hip", "0fa619bbc0265351", 638512, 175863),
+        "triangle_in": ("k_triangle.hip", "0fa619bbc0265351", 638512, 175863),
+        "transition": ("k_transition.hip", "66452d7c16a04ef7", 100611 + 268, 174369 + 384),
+        "attn_proj": ("k_linear.hip", "cb2c3505bd06eb38", 87681, 528983),
+        "tri_proj": ("k_linear.hip", "cb2c3505bd06eb38", 87767, 386304),
+        "attn_out_residual": ("k_linear.hip", "cb2c3505bd06eb38", 174596, 174373),
+        "pair_broadcast": ("k_segment.hip", "9d8ad32506208b50", 68897, 174369),
+        "segment_mean": ("k_segment.hip", "9d8ad32506208b50", 87298, 1492),
+        "single_proj": ("k_gemm.hip", "e8addba92d05a0a0", 1938, 1492),
+        "single_update": ("k_linear.hip", "cb2c3505bd06eb38", 6023, 2237),
     },
     "pair_b8_n208_224_bf16": {
-        "transition": ("k_transition.hip", "79c2db8e257d22b4", 53073 + 268, 90996 + 384),
-        "triangle_out": ("k_triangle.hip", "3d162e104bf38648", 221675, 96336),
-        "attention_row": ("k_attention.hip", "44fe08d102910416", 141463 + 3099, 90996 + 3520),
-        "attn_proj": ("k_linear.hip", "14457045c3846305", 45996, 276032),
-        "tri_proj": ("k_linear.hip", "14457045c3846305", 46241, 197120),
-        "bcast_ln_linear": ("k_linear.hip", "14457045c3846305", 2219, 90996),
-        "attn_out_residual": ("k_linear.hip", "14457045c3846305", 91224, 91002),
-        "segment_mean": ("k_segment.hip", "0217588212ab0b83", 45572, 853),
-        "single_proj": ("k_gemm.hip", "6824a37919ed8fe0", 1459, 853),
-        "single_update": ("k_linear.hip", "14457045c3846305", 3628, 1280),
+        "transition": ("k_transition.hip", "66452d7c16a04ef7", 53111 + 268, 90996 + 384),
+        "triangle_out": ("k_triangle.hip", "0fa619bbc0265351", 223333, 96076),
+        "attention_row": ("k_attention.hip", "49363e3c9ff6fa70", 141463 + 3099, 90996 + 3520),
+        "attn_proj": ("k_linear.hip", "cb2c3505bd06eb38", 45996, 276032),
+        "tri_proj": ("k_linear.hip", "cb2c3505bd06eb38", 46186, 197120),
+        "bcast_ln_linear": ("k_linear.hip", "cb2c3505bd06eb38", 2219, 90996),
+        "attn_out_residual": ("k_linear.hip", "cb2c3505bd06eb38", 91224, 91000),
+        "segment_mean": ("k_segment.hip", "9d8ad32506208b50", 45572, 853),
+        "single_proj": ("k_gemm.hip", "e8addba92d05a0a0", 1459, 853),
+        "single_update": ("k_linear.hip", "cb2c3505bd06eb38", 3628, 1280),
     },
 }
 

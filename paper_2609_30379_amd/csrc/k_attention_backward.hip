@@ -23,8 +23,8 @@
 // The vector units bound the rows kernel: per score it spends about 16 vector
 // instructions on the 3-way splits and one exponential in each of three
 // passes (statistics, dQ, dK/dV), against 30 products per 512 scores.  At
-// B=8, N 66..317, 4 heads: 558 us; one thread per query or key with fp32 FMAs
-// took 12.2 ms (and the bias gradient 5.8 ms, now 233 us).
+// B=8, N 66..317, 4 heads: 560 us; one thread per query or key with fp32 FMAs
+// took 12.2 ms (and the bias gradient 5.8 ms, now 232 us).
 #include <algorithm>
 
 #include "nt_device.h"
